@@ -36,133 +36,472 @@ __device__ __forceinline__ uint16_t f2bf(float x) {
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 // ------------------------------------------------------------------ GEMM --
-// C[m][n] = sum_k A(m,k) B(k,n) (+ bias[n]), FP32 out, BF16 in.
+// C[m][n] = sum_k A(m,k) B(k,n) on v_mfma_f32_32x32x16_bf16, FP32
+// accumulation with k ascending in groups of 16.
 // A(m,k) = TA ? a[k*lda + m] : a[m*lda + k];  B(k,n) = TB ? b[n*ldb + k] : b[k*ldb + n].
-// Block tile 128 x 128 x 32, 4 waves of 64 x 64 (2 x 2 MFMA 32x32x16).
-constexpr int BM = 128, BN = 128, BK = 32, KP = BK + 8;
+// A may also be the neighbourhood matrix of a convolution, gathered from the
+// channel array while its tile is loaded instead of being stored (Conv).
+//
+// Block tile TM x TN x 64 on 4 waves, two shapes: 128 x 128 (waves of 64 x
+// 64) and 64 x 64 (waves of 32 x 32).  The next k-tile travels into
+// registers while the current one is multiplied out of LDS.  LDS rows hold
+// 64 k values (128 bytes, eight 16-byte chunks), the chunk of row r stored
+// at chunk ^ swz(r): a wave reads one chunk of 32 consecutive rows, and the
+// eight rows that share a 128-byte LDS cycle land on eight different chunks
+// (padding the rows instead would misalign the 16-byte reads).  An operand
+// stored with its row index fastest is loaded as 4 (k) x 8 (row) patches and
+// transposed by v_perm_b32, one per output dword, on the way to LDS.
+//
+// What bounds it: the output layer's products (57600 x 4800 x 384 at 600 x
+// 60 x 120, batch 8) read the targets and write dY (1.7 GB), 0.63 ms; its two
+// gradients run at 0.6 and 0.5 PFLOP/s, limited by the load latency of a
+// k-tile.  A training step of that size went from 9.0 to 2.2 ms (batch 8 at
+// 150 x 30 x 60: 1.15 -> 0.40 ms) over the kernels that stored the
+// neighbourhood matrices, Y and every pre-activation gradient in FP32 and
+// summed them in passes of their own; the rounding is unchanged bit by bit.
+constexpr int BK = 64;
+__device__ __forceinline__ int swz(int r) { return (r & 7) ^ ((r & 8) >> 1); }
+__device__ __forceinline__ int lds_chunk(int r, int c) { return r * BK + ((c ^ swz(r)) << 3); }
 
-template <int T>
-__device__ __forceinline__ void load_tile(const uint16_t* __restrict__ g, int ld, int r0, int k0,
-                                          int R, int K, uint16_t (*s)[KP]) {
-  // s[r][k] for r in [0,128), k in [0,32): element (r0+r, k0+k) of a matrix
-  // stored K-contiguous (T = 0: g[r*ld + k]) or R-contiguous (T = 1: g[k*ld + r]).
-  const int tid = threadIdx.x;
-  for (int c = tid; c < 512; c += 256) {
-    if (T == 0) {
-      const int r = c >> 2, kc = (c & 3) * 8;
-      const int gr = r0 + r, gk = k0 + kc;
-      uint16_t v[8];
-      if (gr < R && gk + 8 <= K && (ld & 7) == 0) {
-        const uint4 q = *reinterpret_cast<const uint4*>(g + (long long)gr * ld + gk);
-        memcpy(v, &q, 16);
-      } else {
-        for (int i = 0; i < 8; ++i)
-          v[i] = (gr < R && gk + i < K) ? g[(long long)gr * ld + gk + i] : (uint16_t)0;
-      }
-      memcpy(&s[r][kc], v, 16);
-    } else {
-      const int k = c >> 4, rc = (c & 15) * 8;
-      const int gk = k0 + k, gr = r0 + rc;
-      uint16_t v[8];
-      if (gk < K && gr + 8 <= R && (ld & 7) == 0) {
-        const uint4 q = *reinterpret_cast<const uint4*>(g + (long long)gk * ld + gr);
-        memcpy(v, &q, 16);
-      } else {
-        for (int i = 0; i < 8; ++i)
-          v[i] = (gk < K && gr + i < R) ? g[(long long)gk * ld + gr + i] : (uint16_t)0;
-      }
-      for (int i = 0; i < 8; ++i) s[rc + i][k] = v[i];
-    }
-  }
+// The neighbourhood matrix of a convolution over 3 colatitude rows and nk
+// longitudes starting at offset dk0: row m = (b, j, k), column
+// tap * C + c = h[b][clamp(j + dj)][(k + dk) mod np][c],
+// tap = (dj + 1) * nk + (dk - dk0).
+struct Conv {
+  int nt, np, C, dk0, nk;
+};
+
+struct Operand {
+  const uint16_t* p;
+  int ld;
+  int vec;  // rows may be read 16 bytes at a time (base and stride aligned)
+  Conv cv;
+};
+
+struct ConvRow {  // one row of the neighbourhood matrix
+  int b, j, k;
+};
+__device__ __forceinline__ ConvRow conv_row(const Conv& cv, int m) {
+  ConvRow r;
+  r.k = m % cv.np;
+  const int q = m / cv.np;
+  r.j = q % cv.nt;
+  r.b = q / cv.nt;
+  return r;
+}
+// element offset of channel 0 of the row's neighbour at `tap`
+__device__ __forceinline__ long long conv_at(const Conv& cv, const ConvRow& r, int tap) {
+  const int d = tap / cv.nk;
+  int j = r.j + d - 1, k = r.k + tap - d * cv.nk + cv.dk0;
+  j = j < 0 ? 0 : (j >= cv.nt ? cv.nt - 1 : j);
+  k = k < 0 ? k + cv.np : (k >= cv.np ? k - cv.np : k);  // |dk| < np
+  return ((long long)(r.b * cv.nt + j) * cv.np + k) * cv.C;
 }
 
-template <int TA, int TB>
-__global__ void __launch_bounds__(256) k_gemm(const uint16_t* __restrict__ A,
-                                              const uint16_t* __restrict__ B,
-                                              float* __restrict__ C,
-                                              const float* __restrict__ bias, int M, int N,
-                                              int Kfull, int lda, int ldb, int ldc, int kchunk) {
-  __shared__ __attribute__((aligned(16))) uint16_t sA[BM][KP];
-  __shared__ __attribute__((aligned(16))) uint16_t sB[BN][KP];
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  // split K: block z covers k in [z kchunk, min(K, (z + 1) kchunk)) and writes
-  // its partial product to slab z of C (slabs M x ldc apart)
-  const int kbeg = blockIdx.z * kchunk;
-  const int K = Kfull < kbeg + kchunk ? Kfull : kbeg + kchunk;
-  C += (long long)blockIdx.z * M * ldc;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int wm = (w >> 1) * 64, wn = (w & 1) * 64;
-  f32x16 acc[2][2];
-  for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b)
-      for (int q = 0; q < 16; ++q) acc[a][b][q] = 0.f;
-  for (int k0 = kbeg; k0 < K; k0 += BK) {
-    __syncthreads();
-    load_tile<TA>(A, lda, m0, k0, M, K, sA);
-    load_tile<TB ? 0 : 1>(B, ldb, n0, k0, N, K, sB);
-    __syncthreads();
-    for (int ks = 0; ks < BK; ks += 16) {
-      const int kk = ks + (lane >> 5) * 8;
-      bf16x8 fa[2], fb[2];
-      for (int t = 0; t < 2; ++t) {
-        memcpy(&fa[t], &sA[wm + t * 32 + (lane & 31)][kk], 16);
-        memcpy(&fb[t], &sB[wn + t * 32 + (lane & 31)][kk], 16);
+// 8 consecutive elements (r, c .. c+7) of a matrix with rows of ld elements,
+// zero outside R x C.
+__device__ __forceinline__ uint4 fetch8(const Operand& o, int r, int c, int R, int C) {
+  uint4 q = make_uint4(0, 0, 0, 0);
+  if (r >= R || c >= C) return q;
+  const uint16_t* g = o.p + (long long)r * o.ld + c;
+  if (o.vec && c + 8 <= C) return *reinterpret_cast<const uint4*>(g);
+  uint16_t v[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] = c + i < C ? g[i] : (uint16_t)0;
+  memcpy(&q, v, 16);
+  return q;
+}
+
+// The same of the neighbourhood matrix: 16 bytes at once where 8 channels
+// never straddle two taps, else by channel pairs (even C), else one by one.
+__device__ __forceinline__ uint4 fetch8_conv(const Operand& o, const ConvRow& row, int c, int K) {
+  uint4 q = make_uint4(0, 0, 0, 0);
+  if (c >= K) return q;
+  const Conv& cv = o.cv;
+  if (o.vec) {
+    const int tap = c / cv.C;
+    return *reinterpret_cast<const uint4*>(o.p + conv_at(cv, row, tap) + (c - tap * cv.C));
+  }
+  uint16_t v[8];
+  if ((cv.C & 1) == 0) {
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) {
+      uint32_t w = 0;
+      if (c + i < K) {
+        const int tap = (c + i) / cv.C;
+        w = *reinterpret_cast<const uint32_t*>(o.p + conv_at(cv, row, tap) +
+                                               (c + i - tap * cv.C));
       }
-      for (int a = 0; a < 2; ++a)
-        for (int b = 0; b < 2; ++b)
+      memcpy(v + i, &w, 4);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      v[i] = 0;
+      if (c + i < K) {
+        const int tap = (c + i) / cv.C;
+        v[i] = o.p[conv_at(cv, row, tap) + (c + i - tap * cv.C)];
+      }
+    }
+  }
+  memcpy(&q, v, 16);
+  return q;
+}
+
+// One operand's k-tile, T rows x 64 k: T / 32 16-byte pieces per thread.
+// KR = 0: stored k-contiguous; piece q is chunk tid % 8 of row tid / 8 + 32 q.
+// KR = 1: stored row-contiguous; a 4 (k) x 8 (row) patch per 4 pieces.
+template <int T, int KR, int CONV>
+struct Tile {
+  static constexpr int NP = T / 32;
+  uint4 v[NP];
+  ConvRow row[CONV && !KR ? NP : 1];
+
+  __device__ __forceinline__ void init(const Operand& o, int r0, int R) {
+    if constexpr (CONV && !KR)
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        const int r = r0 + (threadIdx.x >> 3) + 32 * q;
+        row[q] = conv_row(o.cv, r < R ? r : R - 1);
+      }
+  }
+  // patch of this thread: 8 k-groups and 8 row-groups per wave
+  __device__ __forceinline__ static int patch_k(int w, int l) {
+    return 4 * ((l & 7) + 8 * (w & 1));
+  }
+  __device__ __forceinline__ static int patch_r(int w, int l) {
+    return 8 * ((l >> 3) + 8 * (w >> 1));
+  }
+  // rows r0 .. of R, k0 .. of K
+  __device__ __forceinline__ void load(const Operand& o, int r0, int k0, int R, int K) {
+    const int tid = threadIdx.x;
+    if constexpr (!KR) {
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        const int r = r0 + (tid >> 3) + 32 * q, k = k0 + (tid & 7) * 8;
+        if constexpr (CONV)
+          v[q] = r < R ? fetch8_conv(o, row[q], k, K) : make_uint4(0, 0, 0, 0);
+        else
+          v[q] = fetch8(o, r, k, R, K);
+      }
+    } else {
+      const int w = tid >> 6, l = tid & 63;
+      if (T < 128 && w >= 2) return;  // 64 rows: two waves hold all the patches
+      const int r = r0 + patch_r(w, l), k = k0 + patch_k(w, l);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if constexpr (CONV)
+          set(q, k + q < K && r < R ? fetch8_conv(o, conv_row(o.cv, k + q), r, R)
+                                    : make_uint4(0, 0, 0, 0));
+        else
+          set(q, fetch8(o, k + q, r, K, R));
+      }
+    }
+  }
+  uint4 x[KR && T < 128 ? 2 : 1];  // a patch is 4 pieces also where NP is 2
+  __device__ __forceinline__ void set(int q, uint4 a) {
+    if (q < NP) v[q < NP ? q : 0] = a; else x[q >= NP ? (q - NP) % (KR && T < 128 ? 2 : 1) : 0] = a;
+  }
+  __device__ __forceinline__ uint4 get(int q) const {
+    return q < NP ? v[q < NP ? q : 0] : x[q >= NP ? (q - NP) % (KR && T < 128 ? 2 : 1) : 0];
+  }
+  __device__ __forceinline__ void store(uint16_t* s) const {
+    const int tid = threadIdx.x;
+    if constexpr (!KR) {
+#pragma unroll
+      for (int q = 0; q < NP; ++q)
+        *reinterpret_cast<uint4*>(s + lds_chunk((tid >> 3) + 32 * q, tid & 7)) = v[q];
+    } else {
+      const int w = tid >> 6, l = tid & 63;
+      if (T < 128 && w >= 2) return;
+      const int r = patch_r(w, l), k = patch_k(w, l);
+      const uint4 p0 = get(0), p1 = get(1), p2 = get(2), p3 = get(3);
+      const uint32_t a0[4] = {p0.x, p0.y, p0.z, p0.w}, a1[4] = {p1.x, p1.y, p1.z, p1.w};
+      const uint32_t a2[4] = {p2.x, p2.y, p2.z, p2.w}, a3[4] = {p3.x, p3.y, p3.z, p3.w};
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {  // row r + i: its four k values
+        const uint32_t sel = i & 1 ? 0x07060302u : 0x05040100u;
+        const uint2 d = make_uint2(__builtin_amdgcn_perm(a1[i >> 1], a0[i >> 1], sel),
+                                   __builtin_amdgcn_perm(a3[i >> 1], a2[i >> 1], sel));
+        *reinterpret_cast<uint2*>(s + lds_chunk(r + i, k >> 3) + (k & 4)) = d;
+      }
+    }
+  }
+};
+
+// What happens to a finished tile.
+//   EP_OUT   C = acc (+ bias)
+//   EP_SILU  h = SiLU(acc + bias) in BF16; z = acc + bias kept where z is set
+//   EP_MSE   d = acc + bias - t: dY = 2 d scale in BF16, the block's sum of
+//            d^2, and the column sums of d over the block's rows
+//   EP_BACK  d = acc * SiLU'(z) in BF16 and its column sums
+enum { EP_OUT, EP_SILU, EP_MSE, EP_BACK };
+struct Epi {
+  float* c;           // EP_OUT: C; EP_SILU: z or NULL
+  const float* bias;  // or NULL
+  uint16_t* h;        // BF16 result
+  const float* t;     // EP_MSE: targets; EP_BACK: z
+  double* loss;       // EP_MSE: one per block
+  double* col;        // EP_MSE, EP_BACK: [row tiles][N]
+  float scale;
+  int ldc;            // row length of C (the other arrays: N)
+  int wide;           // every array given allows 16- (BF16: 8-) byte access
+};
+
+// h = SiLU(z) = z / (1 + exp(-z));  SiLU'(z) = s (1 + z (1 - s)), s = 1 / (1 + exp(-z))
+__device__ __forceinline__ float silu(float v) { return v / (1.f + expf(-v)); }
+__device__ __forceinline__ float silu_back(float dh, float v) {
+  const float s = 1.f / (1.f + expf(-v));
+  return dh * s * (1.f + v * (1.f - s));
+}
+
+// Tile order: workgroups go to the 8 XCDs in turn, each with its own L2, so
+// XCD x takes a contiguous range of the list; the list walks groups of 8 row
+// tiles column by column, so that a group's rows of A and one column panel
+// of B stay in that L2 while they are used.
+__device__ __forceinline__ void tile_of(int b, int nm, int nn, int& tm, int& tn) {
+  const int nb = nm * nn, x = b % 8, per = nb / 8, rem = nb % 8;
+  const int t = x * per + (x < rem ? x : rem) + b / 8;
+  const int g = t / (8 * nn), m0 = g * 8, h = nm - m0 < 8 ? nm - m0 : 8;
+  const int u = t - g * 8 * nn;
+  tm = m0 + u % h;
+  tn = u / h;
+}
+
+template <int TM, int TN, int TA, int TB, int CONV, int EP>
+__global__ void __launch_bounds__(256) k_gemm(Operand A, Operand B, Epi ep, int M, int N,
+                                              int Kfull, int kchunk) {
+  constexpr int FM = TM / 64, FN = TN / 64;  // 32 x 32 fragments of a wave
+  __shared__ __attribute__((aligned(16))) uint16_t sAB[(TM + TN) * BK];
+  uint16_t *sA = sAB, *sB = sAB + TM * BK;
+  const int nm = (M + TM - 1) / TM, nn = (N + TN - 1) / TN;
+  int tm, tn;
+  tile_of(blockIdx.x, nm, nn, tm, tn);
+  const int m0 = tm * TM, n0 = tn * TN;
+  // split K: slab z covers k in [z kchunk, min(K, (z + 1) kchunk)) and writes
+  // its partial product to slab z of C (slabs M x ldc apart)
+  const int kbeg = blockIdx.y * kchunk;
+  const int K = Kfull < kbeg + kchunk ? Kfull : kbeg + kchunk;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int wm = (w >> 1) * (TM / 2), wn = (w & 1) * (TN / 2);
+  f32x16 acc[FM][FN];
+#pragma unroll
+  for (int a = 0; a < FM; ++a)
+#pragma unroll
+    for (int b = 0; b < FN; ++b)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc[a][b][q] = 0.f;
+  Tile<TM, TA, CONV> ta;
+  Tile<TN, !TB, 0> tb;
+  ta.init(A, m0, M);
+  ta.load(A, m0, kbeg, M, K);
+  tb.load(B, n0, kbeg, N, K);
+  for (int k0 = kbeg; k0 < K; k0 += BK) {
+    __syncthreads();  // the previous k-tile has been read
+    ta.store(sA);
+    tb.store(sB);
+    __syncthreads();
+    if (k0 + BK < K) {
+      ta.load(A, m0, k0 + BK, M, K);
+      tb.load(B, n0, k0 + BK, N, K);
+    }
+#pragma unroll
+    for (int ks = 0; ks < BK / 16; ++ks) {
+      const int ch = 2 * ks + (lane >> 5);
+      bf16x8 fa[FM], fb[FN];
+#pragma unroll
+      for (int t = 0; t < FM; ++t)
+        memcpy(&fa[t], sA + lds_chunk(wm + t * 32 + (lane & 31), ch), 16);
+#pragma unroll
+      for (int t = 0; t < FN; ++t)
+        memcpy(&fb[t], sB + lds_chunk(wn + t * 32 + (lane & 31), ch), 16);
+#pragma unroll
+      for (int a = 0; a < FM; ++a)
+#pragma unroll
+        for (int b = 0; b < FN; ++b)
           acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
     }
   }
-  // accumulator element q = 4 i + j of a 32x32 tile holds row 8 i + 4 (lane / 32) + j,
-  // column lane % 32
-  for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b) {
-      const int n = n0 + wn + b * 32 + (lane & 31);
-      if (n >= N) continue;
-      const float bn = bias ? bias[n] : 0.f;
-      for (int i = 0; i < 4; ++i)
-        for (int j = 0; j < 4; ++j) {
-          const int m = m0 + wm + a * 32 + 8 * i + 4 * (lane >> 5) + j;
-          if (m < M) C[(long long)m * ldc + n] = acc[a][b][4 * i + j] + bn;
+  // The finished tile goes through LDS, 64 rows at a time, so that each
+  // thread holds four neighbouring columns: the epilogue's loads and stores
+  // are then 16 (FP32) or 8 (BF16) bytes a lane over whole rows.
+  // (accumulator element q = 4 i + j of a 32x32 fragment holds row
+  // 8 i + 4 (lane / 32) + j, column lane % 32)
+  float* sC = reinterpret_cast<float*>(sAB);  // [64][TN]: as large as the operand tiles
+  constexpr int TC = TN / 4, RP = 256 / TC, RN = 64 / RP;  // column groups, row phases, rows
+  float* C = ep.c ? ep.c + (EP == EP_OUT ? (long long)blockIdx.y * M * ep.ldc : 0) : nullptr;
+  const int cq = threadIdx.x % TC, rp = threadIdx.x / TC;
+  const int n = n0 + 4 * cq;
+  const int ldc = EP == EP_OUT ? ep.ldc : N;
+  const bool wide = n + 4 <= N && (N & 3) == 0 && (ldc & 3) == 0 && ep.wide;
+  float bn[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) bn[i] = ep.bias && n + i < N ? ep.bias[n + i] : 0.f;
+  double e2 = 0.0, cs[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int half = 0; half < TM / 64; ++half) {
+    float4 src[RN];
+    if constexpr (EP == EP_MSE || EP == EP_BACK) {
+#pragma unroll
+      for (int q = 0; q < RN; ++q) {
+        const int m = m0 + 64 * half + rp + RP * q;
+        src[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (m < M && wide) {
+          src[q] = *reinterpret_cast<const float4*>(ep.t + (long long)m * N + n);
+        } else if (m < M) {
+          float v[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v[i] = n + i < N ? ep.t[(long long)m * N + n + i] : 0.f;
+          src[q] = make_float4(v[0], v[1], v[2], v[3]);
         }
+      }
     }
+    __syncthreads();
+    if (TM == 64 || (w >> 1) == half) {
+      const int wr = TM == 64 ? wm : 0;
+#pragma unroll
+      for (int a = 0; a < FM; ++a)
+#pragma unroll
+        for (int b = 0; b < FN; ++b)
+#pragma unroll
+          for (int q = 0; q < 16; ++q)
+            sC[(wr + a * 32 + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3)) * TN + wn + b * 32 +
+               (lane & 31)] = acc[a][b][q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < RN; ++q) {
+      const int r = rp + RP * q, m = m0 + 64 * half + r;
+      if (m >= M) continue;
+      const float4 c4 = *reinterpret_cast<const float4*>(sC + r * TN + 4 * cq);
+      const float v[4] = {c4.x, c4.y, c4.z, c4.w};
+      const float s4[4] = {src[q].x, src[q].y, src[q].z, src[q].w};
+      float out[4];
+      uint16_t hb[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if constexpr (EP == EP_OUT) {
+          out[i] = v[i] + bn[i];
+        } else if constexpr (EP == EP_SILU) {
+          out[i] = v[i] + bn[i];
+          hb[i] = f2bf(silu(out[i]));
+        } else {
+          float d;
+          if constexpr (EP == EP_MSE) {
+            const float y = v[i] + bn[i];
+            d = y - s4[i];
+            hb[i] = f2bf(2.f * d * ep.scale);
+          } else {
+            d = silu_back(v[i], s4[i]);
+            hb[i] = f2bf(d);
+          }
+          if (n + i < N) {
+            if (EP == EP_MSE) e2 += (double)d * d;
+            cs[i] += (double)d;
+          }
+        }
+      }
+      const long long o = (long long)m * ldc + n;
+      if (wide) {
+        if ((EP == EP_OUT || EP == EP_SILU) && C)
+          *reinterpret_cast<float4*>(C + o) = make_float4(out[0], out[1], out[2], out[3]);
+        if constexpr (EP != EP_OUT)
+          *reinterpret_cast<ushort4*>(ep.h + o) = make_ushort4(hb[0], hb[1], hb[2], hb[3]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (n + i < N) {
+            if ((EP == EP_OUT || EP == EP_SILU) && C) C[o + i] = out[i];
+            if constexpr (EP != EP_OUT) ep.h[o + i] = hb[i];
+          }
+      }
+    }
+  }
+  if constexpr (EP == EP_MSE || EP == EP_BACK) {
+    // column sums over the tile's rows: the row phases in a fixed order
+    __syncthreads();
+    double* sc = reinterpret_cast<double*>(sAB);  // [RP][TN], then 4 wave sums
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sc[rp * TN + 4 * cq + i] = cs[i];
+    if (EP == EP_MSE) {
+      for (int o = 32; o > 0; o >>= 1) e2 += __shfl_xor(e2, o, 64);
+      if (lane == 0) sc[RP * TN + w] = e2;
+    }
+    __syncthreads();
+    if (threadIdx.x < TN && n0 + (int)threadIdx.x < N) {
+      double s = 0.0;
+#pragma unroll
+      for (int q = 0; q < RP; ++q) s += sc[q * TN + threadIdx.x];
+      ep.col[(long long)tm * N + n0 + threadIdx.x] = s;
+    }
+    if (EP == EP_MSE && threadIdx.x == 0) {
+      const double* se = sc + RP * TN;
+      ep.loss[blockIdx.x] = ((se[0] + se[1]) + se[2]) + se[3];
+    }
+  }
 }
 
-void gemm_launch(int ta, int tb, const uint16_t* A, const uint16_t* B, float* C,
-                 const float* bias, int M, int N, int K, int lda, int ldb, int ldc, int splits,
+// Tile shape: 128 x 128 where that fills the chip (256 CUs, two blocks each)
+// and the output is wider than one 64-column tile, else 64 x 64: with fewer
+// tiles CUs stay empty, and 64 output columns would leave half of a 128-wide
+// tile to padding.
+constexpr int TBIG = 128, TSMALL = 64;
+inline long long tiles(int t, int M, int N) {
+  return (long long)((M + t - 1) / t) * ((N + t - 1) / t);
+}
+inline int tile_for(int M, int N, int splits) {
+  return N > TSMALL && tiles(TBIG, M, N) * splits >= 512 ? TBIG : TSMALL;
+}
+
+Operand operand(const uint16_t* p, int ld) {
+  Operand o{};
+  o.p = p;
+  o.ld = ld;
+  o.vec = (ld & 7) == 0 && ((uintptr_t)p & 15) == 0;
+  return o;
+}
+Operand conv_operand(const uint16_t* p, const Conv& cv) {
+  Operand o{};
+  o.p = p;
+  o.cv = cv;
+  o.vec = (cv.C & 7) == 0 && ((uintptr_t)p & 15) == 0;
+  return o;
+}
+
+template <int TA, int TB, int CONV, int EP>
+void gemm_launch(const Operand& A, const Operand& B, Epi ep, int M, int N, int K, int splits,
                  int kchunk, hipStream_t s) {
-  const dim3 grid((N + BN - 1) / BN, (M + BM - 1) / BM, splits), blk(256);
-  if (!ta && !tb)
-    hipLaunchKernelGGL((k_gemm<0, 0>), grid, blk, 0, s, A, B, C, bias, M, N, K, lda, ldb, ldc,
-                       kchunk);
-  else if (!ta && tb)
-    hipLaunchKernelGGL((k_gemm<0, 1>), grid, blk, 0, s, A, B, C, bias, M, N, K, lda, ldb, ldc,
-                       kchunk);
-  else if (ta && !tb)
-    hipLaunchKernelGGL((k_gemm<1, 0>), grid, blk, 0, s, A, B, C, bias, M, N, K, lda, ldb, ldc,
+  ep.wide = ((((uintptr_t)ep.c | (uintptr_t)ep.t) & 15) | ((uintptr_t)ep.h & 7)) == 0;
+  const int t = tile_for(M, N, splits);
+  const dim3 grid((unsigned)tiles(t, M, N), splits), blk(256);
+  if (t == TBIG)
+    hipLaunchKernelGGL((k_gemm<TBIG, TBIG, TA, TB, CONV, EP>), grid, blk, 0, s, A, B, ep, M, N, K,
                        kchunk);
   else
-    hipLaunchKernelGGL((k_gemm<1, 1>), grid, blk, 0, s, A, B, C, bias, M, N, K, lda, ldb, ldc,
-                       kchunk);
+    hipLaunchKernelGGL((k_gemm<TSMALL, TSMALL, TA, TB, CONV, EP>), grid, blk, 0, s, A, B, ep, M,
+                       N, K, kchunk);
 }
 
-void gemm(int ta, int tb, const uint16_t* A, const uint16_t* B, float* C, const float* bias, int M,
-          int N, int K, int lda, int ldb, int ldc, hipStream_t s) {
-  gemm_launch(ta, tb, A, B, C, bias, M, N, K, lda, ldb, ldc, 1, (K + BK - 1) / BK * BK, s);
+template <int TA, int TB, int CONV, int EP>
+void gemm(const Operand& A, const Operand& B, const Epi& ep, int M, int N, int K, hipStream_t s) {
+  gemm_launch<TA, TB, CONV, EP>(A, B, ep, M, N, K, 1, (K + BK - 1) / BK * BK, s);
 }
 
 // Split of the reduction dimension for products whose output has few tiles
-// and whose K is long (the weight gradients, K = rows of the batch): enough
-// (tile, slab) blocks to fill the chip, each slab a multiple of BK.
+// and whose K is long (the weight gradients, K = rows of the batch): about
+// 1024 (128 x 128 tile, slab) blocks, each slab a multiple of 32 rows and at
+// least 256.  The slab sums are rounded to FP32 before they are added, so
+// this partition fixes the gradients' rounding: it does not follow BK or the
+// tile shape.
 struct Split {
   int slabs, kchunk;
 };
+int split_most(int M, int N) { return (int)((1024 + tiles(TBIG, M, N) - 1) / tiles(TBIG, M, N)); }
 Split ksplit(int M, int N, int K) {
-  const int tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-  int want = (1024 + tiles - 1) / tiles;
-  const int most = (K + 8 * BK - 1) / (8 * BK);  // at least 8 k-steps per slab
+  int want = split_most(M, N);
+  const int most = (K + 255) / 256;
   want = want < 1 ? 1 : (want > most ? most : want);
-  const int kchunk = ((K + want - 1) / want + BK - 1) / BK * BK;
+  const int kchunk = ((K + want - 1) / want + 31) / 32 * 32;
   return Split{(K + kchunk - 1) / kchunk, kchunk};
 }
 
@@ -172,19 +511,21 @@ __global__ void k_sum_slabs(const float* __restrict__ part, int slabs, long long
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   float acc = 0.f;
+#pragma unroll 8
   for (int z = 0; z < slabs; ++z) acc += part[(long long)z * n + i];
   C[i] = acc;
 }
 
-// weight gradient C [M][N] (contiguous) from a product over a long K
-void gemm_wgrad(int ta, int tb, const uint16_t* A, const uint16_t* B, float* C, int M, int N,
-                int K, int lda, int ldb, float* scratch, hipStream_t s) {
+// weight gradient C [M][N] (contiguous) = A^T B from a product over a long K
+template <int CONV>
+void gemm_wgrad(const Operand& A, const Operand& B, float* C, int M, int N, int K,
+                float* scratch, hipStream_t s) {
   const Split sp = ksplit(M, N, K);
-  if (sp.slabs == 1) {
-    gemm(ta, tb, A, B, C, nullptr, M, N, K, lda, ldb, N, s);
-    return;
-  }
-  gemm_launch(ta, tb, A, B, scratch, nullptr, M, N, K, lda, ldb, N, sp.slabs, sp.kchunk, s);
+  Epi ep{};
+  ep.ldc = N;
+  ep.c = sp.slabs == 1 ? C : scratch;
+  gemm_launch<1, 0, CONV, EP_OUT>(A, B, ep, M, N, K, sp.slabs, sp.kchunk, s);
+  if (sp.slabs == 1) return;
   const long long n = (long long)M * N;
   hipLaunchKernelGGL(k_sum_slabs, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, scratch,
                      sp.slabs, n, C);
@@ -196,160 +537,93 @@ __global__ void k_to_bf16(const float* __restrict__ x, uint16_t* __restrict__ y,
   if (i < n) y[i] = f2bf(x[i]);
 }
 
-// H = SiLU(Z) = Z / (1 + exp(-Z)) as BF16
-__global__ void k_silu(const float* __restrict__ z, uint16_t* __restrict__ h, long long n) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) {
-    const float v = z[i];
-    h[i] = f2bf(v / (1.f + expf(-v)));
-  }
-}
-
-// dZ = dH * SiLU'(Z), SiLU'(z) = s (1 + z (1 - s)), s = 1/(1+exp(-z)); FP32 and BF16 copies
-__global__ void k_silu_back(const float* __restrict__ dh, const float* __restrict__ z,
-                            float* __restrict__ dz, uint16_t* __restrict__ dzb, long long n) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) {
-    const float v = z[i], s = 1.f / (1.f + expf(-v));
-    const float d = dh[i] * s * (1.f + v * (1.f - s));
-    dz[i] = d;
-    dzb[i] = f2bf(d);
-  }
-}
-
-// neighbourhood gather over 3 colatitude rows and nk longitudes starting at offset dk0:
-// A[b, j, k][tap * C + c] = H[b, clamp(j + dj), (k + dk) mod np][c],
-// tap = (dj + 1) * nk + (dk - dk0), dj in {-1, 0, 1}, dk in [dk0, dk0 + nk)
-__global__ void k_im2col(const uint16_t* __restrict__ h, uint16_t* __restrict__ a, int B, int nt,
-                         int np, int C, int dk0, int nk) {
-  const int taps = 3 * nk;
-  const long long n = (long long)B * nt * np * taps * C;
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int c = (int)(i % C);
-  long long r = i / C;
-  const int tap = (int)(r % taps);
-  r /= taps;
-  const int k = (int)(r % np);
-  r /= np;
-  const int j = (int)(r % nt);
-  const int b = (int)(r / nt);
-  const int dj = tap / nk - 1, dk = tap % nk + dk0;
-  int jj = j + dj;
-  jj = jj < 0 ? 0 : (jj >= nt ? nt - 1 : jj);
-  int kk = (k + dk) % np;
-  if (kk < 0) kk += np;
-  a[i] = h[(((long long)b * nt + jj) * np + kk) * C + c];
-}
-
-// adjoint of k_im2col: dH[b, j', k'][c] = sum of dA over every (j, k, tap) that gathered (j', k')
-__global__ void k_col2im(const float* __restrict__ da, float* __restrict__ dh, int B, int nt,
-                         int np, int C, int dk0, int nk) {
-  const int taps = 3 * nk;
-  const long long n = (long long)B * nt * np * C;
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int c = (int)(i % C);
-  long long r = i / C;
-  const int k = (int)(r % np);
-  r /= np;
-  const int j = (int)(r % nt);
-  const int b = (int)(r / nt);
-  float s = 0.f;
-  for (int dj = -1; dj <= 1; ++dj) {
-    // source rows jsrc whose clamp(jsrc + dj) == j
-    int js[2], ns = 0;
-    const int j0 = j - dj;
-    if (j0 >= 0 && j0 < nt) js[ns++] = j0;
-    if (dj == -1 && j == 0) js[ns++] = 0;       // clamp(0 - 1) = 0
-    if (dj == 1 && j == nt - 1) js[ns++] = nt - 1;  // clamp(nt - 1 + 1) = nt - 1
-    for (int q = 0; q < ns; ++q)
-      for (int t = 0; t < nk; ++t) {
-        int ks = (k - (t + dk0)) % np;
-        if (ks < 0) ks += np;
-        const int tap = (dj + 1) * nk + t;
-        s += da[((((long long)b * nt + js[q]) * np + ks) * taps + tap) * C + c];
-      }
-  }
-  dh[i] = s;
-}
-
-// Column sums db[n] = sum_m dZ[m][n] in two passes with a fixed order:
-// block (x, slab) sums rows of its slab for 64 columns (4 row phases per
-// column, combined in order), then one thread per column adds the slabs.
-constexpr int CS_SLABS = 64;
-template <bool DIFF>
-__global__ void __launch_bounds__(256) k_colsum_part(const float* __restrict__ a,
-                                                     const float* __restrict__ b, int M, int N,
-                                                     double* __restrict__ part) {
+// Backward of the neighbourhood gather and of the SiLU before it: dH[b, j,
+// k][c] = sum of dA over every (row, tap) that gathered (j, k) (dA stored
+// [row][tap * C + c]), dZ = dH SiLU'(Z) in BF16, and the column sums of dZ
+// over the block's rows.  Blocks of CI_ROWS rows x 64 channels, 4 row phases.
+constexpr int CI_ROWS = 32;
+__global__ void __launch_bounds__(256) k_col2im_back(const float* __restrict__ da,
+                                                     const float* __restrict__ z,
+                                                     uint16_t* __restrict__ dzb,
+                                                     double* __restrict__ col, int M, Conv cv) {
   __shared__ double sh[4][64];
-  const int n = blockIdx.x * 64 + (threadIdx.x & 63), ph = threadIdx.x >> 6;
-  const int rows = (M + CS_SLABS - 1) / CS_SLABS;
-  const int m0 = blockIdx.y * rows, m1 = m0 + rows < M ? m0 + rows : M;
+  const int nt = cv.nt, np = cv.np, C = cv.C, nk = cv.nk, taps = 3 * nk;
+  const int c = blockIdx.y * 64 + (threadIdx.x & 63), ph = threadIdx.x >> 6;
+  const int r0 = blockIdx.x * CI_ROWS, r1 = r0 + CI_ROWS < M ? r0 + CI_ROWS : M;
   double acc = 0.0;
-  if (n < N)
-    for (int m = m0 + ph; m < m1; m += 4) {
-      const long long i = (long long)m * N + n;
-      acc += DIFF ? (double)(a[i] - b[i]) : (double)a[i];
+  if (c < C)
+    for (int m = r0 + ph; m < r1; m += 4) {
+      const ConvRow r = conv_row(cv, m);
+      float s = 0.f;
+      for (int dj = -1; dj <= 1; ++dj) {
+        // source rows jsrc whose clamp(jsrc + dj) == j
+        int js[2], ns = 0;
+        const int j0 = r.j - dj;
+        if (j0 >= 0 && j0 < nt) js[ns++] = j0;
+        if (dj == -1 && r.j == 0) js[ns++] = 0;            // clamp(0 - 1) = 0
+        if (dj == 1 && r.j == nt - 1) js[ns++] = nt - 1;  // clamp(nt - 1 + 1) = nt - 1
+        for (int q = 0; q < ns; ++q)
+          for (int t = 0; t < nk; ++t) {
+            int ks = (r.k - (t + cv.dk0)) % np;
+            if (ks < 0) ks += np;
+            const int tap = (dj + 1) * nk + t;
+            s += da[((((long long)r.b * nt + js[q]) * np + ks) * taps + tap) * C + c];
+          }
+      }
+      const long long o = (long long)m * C + c;
+      const float d = silu_back(s, z[o]);
+      dzb[o] = f2bf(d);
+      acc += (double)d;
     }
   sh[ph][threadIdx.x & 63] = acc;
   __syncthreads();
-  if (ph == 0 && n < N)
-    part[(long long)blockIdx.y * N + n] = ((sh[0][threadIdx.x] + sh[1][threadIdx.x]) +
-                                           sh[2][threadIdx.x]) + sh[3][threadIdx.x];
+  if (ph == 0 && c < C)
+    col[(long long)blockIdx.x * C + c] =
+        ((sh[0][threadIdx.x] + sh[1][threadIdx.x]) + sh[2][threadIdx.x]) + sh[3][threadIdx.x];
 }
 
-__global__ void k_colsum_fin(const double* __restrict__ part, int N, double scale,
-                             float* __restrict__ db) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= N) return;
+// Bias gradients of the four layers in one launch: db[n] = scale times the
+// column sums added over the row tiles, 16 row phases combined in order.
+struct ColJob {
+  const double* part;
+  float* db;
+  int rows, N, blk0;  // first block of this job
+  double scale;
+};
+struct ColJobs {
+  ColJob j[4];
+};
+__global__ void __launch_bounds__(1024) k_colsum_fin(ColJobs jobs) {
+  __shared__ double sh[16][64];
+  int q = 0;
+  while (q < 3 && (int)blockIdx.x >= jobs.j[q + 1].blk0) ++q;
+  const ColJob& J = jobs.j[q];
+  const int n = (blockIdx.x - J.blk0) * 64 + (threadIdx.x & 63), ph = threadIdx.x >> 6;
   double acc = 0.0;
-  for (int z = 0; z < CS_SLABS; ++z) acc += part[(long long)z * N + n];
-  db[n] = (float)(acc * scale);
-}
-
-// db = scale * column sums of A (or of A - B when b != nullptr)
-void colsum(const float* a, const float* b, int M, int N, double scale, float* db,
-            double* scratch, hipStream_t s) {
-  const dim3 grid((N + 63) / 64, CS_SLABS);
-  if (b)
-    hipLaunchKernelGGL(k_colsum_part<true>, grid, dim3(256), 0, s, a, b, M, N, scratch);
-  else
-    hipLaunchKernelGGL(k_colsum_part<false>, grid, dim3(256), 0, s, a, b, M, N, scratch);
-  hipLaunchKernelGGL(k_colsum_fin, dim3((N + 255) / 256), dim3(256), 0, s, scratch, N, scale, db);
-}
-
-// dY = 2 (Y - T) / count (BF16 for the products), loss partial sums per block
-__global__ void k_mse(const float* __restrict__ y, const float* __restrict__ t,
-                      uint16_t* __restrict__ dy, double* __restrict__ part, long long n,
-                      float scale) {
-  __shared__ double sh[256];
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  double e = 0.0;
-  if (i < n) {
-    const float d = y[i] - t[i];
-    dy[i] = f2bf(2.f * d * scale);
-    e = (double)d * d;
+  if (n < J.N) {
+#pragma unroll 8
+    for (int r = ph; r < J.rows; r += 16) acc += J.part[(long long)r * J.N + n];
   }
-  sh[threadIdx.x] = e;
+  sh[ph][threadIdx.x & 63] = acc;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-    __syncthreads();
+  if (ph == 0 && n < J.N) {
+    double s = 0.0;
+#pragma unroll
+    for (int p = 0; p < 16; ++p) s += sh[p][threadIdx.x];
+    J.db[n] = (float)(s * J.scale);
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
 }
 
-// out = sum of part[0..n): one block of 256, strided partial sums, then a
+// out = sum of part[0..n): one block of 1024, strided partial sums, then a
 // fixed tree
-__global__ void __launch_bounds__(256) k_sum(const double* __restrict__ part, int n,
-                                             double* __restrict__ out) {
-  __shared__ double sh[256];
+__global__ void __launch_bounds__(1024) k_sum(const double* __restrict__ part, int n,
+                                              double* __restrict__ out) {
+  __shared__ double sh[1024];
   double acc = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) acc += part[i];
+  for (int i = threadIdx.x; i < n; i += 1024) acc += part[i];
   sh[threadIdx.x] = acc;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
+  for (int o = 512; o > 0; o >>= 1) {
     if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
     __syncthreads();
   }
@@ -549,14 +823,13 @@ struct icr_nn {
   uint16_t* pb;
   long long step;
   // activations (batch_max rows)
-  float *x;                                // [M][8] features
-  uint16_t *xb, *a1, *h1, *a2, *h2, *h3;   // bf16 operands
+  uint16_t *xb, *h1, *h2, *h3;             // bf16 operands
   float *z1, *z2, *z3, *y;                 // pre-activations and output
   uint16_t *dyb, *dz3b, *dz2b, *dz1b;
-  float *dh3, *dz3, *dh2, *dz2, *da2, *dh1, *dz1;
+  float* da2;
   double *part, *loss;
-  float* split;    // split-K partial products of the weight gradients
-  double* cpart;   // column-sum partials [CS_SLABS][widest layer]
+  float* split;     // split-K partial products of the weight gradients
+  double* cpart[4]; // column-sum partials of each layer [row tiles][width]
   // parameter views
   float *W1, *b1, *W2, *b2, *W3, *b3, *W4, *b4;
   uint16_t *W1b, *W2b, *W3b, *W4b;
@@ -580,53 +853,45 @@ size_t layout(const icr_nn_shape& s, icr_nn* n) {
   float* m = (float*)take(4 * P);
   float* v = (float*)take(4 * P);
   uint16_t* pb = (uint16_t*)take(2 * P);
-  float* x = (float*)take(4 * M * z.cin);
   uint16_t* xb = (uint16_t*)take(2 * M * z.cin);
-  uint16_t* a1 = (uint16_t*)take(2 * M * z.k1);
   float* z1 = (float*)take(4 * M * z.c1);
   uint16_t* h1 = (uint16_t*)take(2 * M * z.c1);
-  uint16_t* a2 = (uint16_t*)take(2 * M * z.k2);
   float* z2 = (float*)take(4 * M * z.c2);
   uint16_t* h2 = (uint16_t*)take(2 * M * z.c2);
   float* z3 = (float*)take(4 * M * z.h);
   uint16_t* h3 = (uint16_t*)take(2 * M * z.h);
   float* y = (float*)take(4 * M * z.no);
   uint16_t* dyb = (uint16_t*)take(2 * M * z.no);
-  float* dh3 = (float*)take(4 * M * z.h);
-  float* dz3 = (float*)take(4 * M * z.h);
   uint16_t* dz3b = (uint16_t*)take(2 * M * z.h);
-  float* dh2 = (float*)take(4 * M * z.c2);
-  float* dz2 = (float*)take(4 * M * z.c2);
   uint16_t* dz2b = (uint16_t*)take(2 * M * z.c2);
   float* da2 = (float*)take(4 * M * z.k2);
-  float* dh1 = (float*)take(4 * M * z.c1);
-  float* dz1 = (float*)take(4 * M * z.c1);
   uint16_t* dz1b = (uint16_t*)take(2 * M * z.c1);
-  const long long nblk = (M * z.no + 255) / 256;
-  double* part = (double*)take(8 * nblk);
+  // one loss partial per tile of the output layer, column sums per row tile
+  // (sized for the smaller tile)
+  double* part = (double*)take(8 * tiles(TSMALL, (int)M, z.no));
   double* loss = (double*)take(8);
+  // (a smaller batch may be split differently, but never into more slabs)
   long long nsplit = 1;
   {
     const int dims[4][2] = {{z.h, z.no}, {z.c2, z.h}, {z.k2, z.c2}, {z.k1, z.c1}};
     for (const auto& d : dims) {
-      const Split sp = ksplit(d[0], d[1], (int)M);
-      if (sp.slabs > 1 && (long long)sp.slabs * d[0] * d[1] > nsplit)
-        nsplit = (long long)sp.slabs * d[0] * d[1];
+      const long long most = split_most(d[0], d[1]);
+      if (most > 1 && most * d[0] * d[1] > nsplit) nsplit = most * d[0] * d[1];
     }
   }
   float* split = (float*)take(4 * nsplit);
-  int wmax = z.no > z.h ? z.no : z.h;
-  wmax = wmax > z.c2 ? wmax : z.c2;
-  wmax = wmax > z.c1 ? wmax : z.c1;
-  double* cpart = (double*)take(8LL * CS_SLABS * wmax);
+  const long long rt = (M + TSMALL - 1) / TSMALL;
+  const int width[4] = {z.c1, z.c2, z.h, z.no};
+  double* cpart[4];
+  for (int q = 0; q < 4; ++q)
+    cpart[q] = (double*)take(8 * width[q] * (q == 0 ? (M + CI_ROWS - 1) / CI_ROWS : rt));
   if (n) {
     n->z = z;
     n->p = p; n->g = g; n->m = m; n->v = v; n->pb = pb;
-    n->x = x; n->xb = xb; n->a1 = a1; n->z1 = z1; n->h1 = h1; n->a2 = a2; n->z2 = z2;
-    n->h2 = h2; n->z3 = z3; n->h3 = h3; n->y = y; n->dyb = dyb; n->dh3 = dh3; n->dz3 = dz3;
-    n->dz3b = dz3b; n->dh2 = dh2; n->dz2 = dz2; n->dz2b = dz2b; n->da2 = da2; n->dh1 = dh1;
-    n->dz1 = dz1; n->dz1b = dz1b; n->part = part; n->loss = loss; n->split = split;
-    n->cpart = cpart;
+    n->xb = xb; n->z1 = z1; n->h1 = h1; n->z2 = z2; n->h2 = h2; n->z3 = z3; n->h3 = h3;
+    n->y = y; n->dyb = dyb; n->dz3b = dz3b; n->dz2b = dz2b; n->da2 = da2; n->dz1b = dz1b;
+    n->part = part; n->loss = loss; n->split = split;
+    for (int q = 0; q < 4; ++q) n->cpart[q] = cpart[q];
     long long o = 0;
     auto view = [&](long long cnt, float*& fp, float*& gp, uint16_t** bp) {
       fp = p + o;
@@ -648,55 +913,104 @@ size_t layout(const icr_nn_shape& s, icr_nn* n) {
 
 inline dim3 g1(long long n) { return dim3((unsigned)((n + 255) / 256)); }
 
-void forward(icr_nn* n, int B, const float* x_dev) {
-  const Sizes& z = n->z;
-  const int nt = n->s.n_theta, np = n->s.n_phi;
-  const long long M = (long long)B * z.ncol;
-  hipStream_t s = n->stream;
-  hipLaunchKernelGGL(k_to_bf16, g1(M * z.cin), dim3(256), 0, s, x_dev, n->xb, M * z.cin);
-  hipLaunchKernelGGL(k_im2col, g1(M * z.k1), dim3(256), 0, s, n->xb, n->a1, B, nt, np, z.cin,
-                     n->s.phi_lo, n->s.phi_hi - n->s.phi_lo + 1);
-  gemm(0, 0, n->a1, n->W1b, n->z1, n->b1, (int)M, z.c1, z.k1, z.k1, z.c1, z.c1, s);
-  hipLaunchKernelGGL(k_silu, g1(M * z.c1), dim3(256), 0, s, n->z1, n->h1, M * z.c1);
-  hipLaunchKernelGGL(k_im2col, g1(M * z.k2), dim3(256), 0, s, n->h1, n->a2, B, nt, np, z.c1,
-                     -1, 3);
-  gemm(0, 0, n->a2, n->W2b, n->z2, n->b2, (int)M, z.c2, z.k2, z.k2, z.c2, z.c2, s);
-  hipLaunchKernelGGL(k_silu, g1(M * z.c2), dim3(256), 0, s, n->z2, n->h2, M * z.c2);
-  gemm(0, 0, n->h2, n->W3b, n->z3, n->b3, (int)M, z.h, z.c2, z.c2, z.h, z.h, s);
-  hipLaunchKernelGGL(k_silu, g1(M * z.h), dim3(256), 0, s, n->z3, n->h3, M * z.h);
-  gemm(0, 0, n->h3, n->W4b, n->y, n->b4, (int)M, z.no, z.h, z.h, z.no, z.no, s);
+Conv conv1(const icr_nn* n) {
+  return Conv{n->s.n_theta, n->s.n_phi, n->z.cin, n->s.phi_lo, n->s.phi_hi - n->s.phi_lo + 1};
+}
+Conv conv2(const icr_nn* n) { return Conv{n->s.n_theta, n->s.n_phi, n->z.c1, -1, 3}; }
+
+Epi silu_epi(float* z, const float* bias, uint16_t* h) {
+  Epi e{};
+  e.c = z;
+  e.bias = bias;
+  e.h = h;
+  return e;
 }
 
-void backward(icr_nn* n, int B, const float* t_dev) {
+// The layers before the output layer; the pre-activations are kept for a
+// backward pass only.
+void encode(icr_nn* n, int B, const float* x_dev, bool keep) {
   const Sizes& z = n->z;
-  const int nt = n->s.n_theta, np = n->s.n_phi;
-  const long long M = (long long)B * z.ncol;
+  const int M = (int)((long long)B * z.ncol);
   hipStream_t s = n->stream;
-  const long long ny = M * z.no;
-  const int nblk = (int)((ny + 255) / 256);
-  hipLaunchKernelGGL(k_mse, dim3(nblk), dim3(256), 0, s, n->y, t_dev, n->dyb, n->part, ny,
-                     1.f / (float)ny);
-  hipLaunchKernelGGL(k_sum, dim3(1), dim3(256), 0, s, n->part, nblk, n->loss);
+  hipLaunchKernelGGL(k_to_bf16, g1((long long)M * z.cin), dim3(256), 0, s, x_dev, n->xb,
+                     (long long)M * z.cin);
+  gemm<0, 0, 1, EP_SILU>(conv_operand(n->xb, conv1(n)), operand(n->W1b, z.c1),
+                         silu_epi(keep ? n->z1 : nullptr, n->b1, n->h1), M, z.c1, z.k1, s);
+  gemm<0, 0, 1, EP_SILU>(conv_operand(n->h1, conv2(n)), operand(n->W2b, z.c2),
+                         silu_epi(keep ? n->z2 : nullptr, n->b2, n->h2), M, z.c2, z.k2, s);
+  gemm<0, 0, 0, EP_SILU>(operand(n->h2, z.c2), operand(n->W3b, z.h),
+                         silu_epi(keep ? n->z3 : nullptr, n->b3, n->h3), M, z.h, z.c2, s);
+}
+
+void forward(icr_nn* n, int B, const float* x_dev, float* y) {
+  const Sizes& z = n->z;
+  encode(n, B, x_dev, false);
+  Epi e{};
+  e.c = y;
+  e.ldc = z.no;
+  e.bias = n->b4;
+  gemm<0, 0, 0, EP_OUT>(operand(n->h3, z.h), operand(n->W4b, z.no), e, (int)(B * z.ncol), z.no,
+                        z.h, n->stream);
+}
+
+Epi back_epi(const float* z, uint16_t* dzb, double* col) {
+  Epi e{};
+  e.t = z;
+  e.h = dzb;
+  e.col = col;
+  return e;
+}
+
+// Loss and gradients.  The output layer's tiles go straight to dY and the
+// loss; Y itself is not stored.
+void loss_grad(icr_nn* n, int B, const float* x_dev, const float* t_dev) {
+  const Sizes& z = n->z;
+  const int M = (int)((long long)B * z.ncol);
+  const long long ny = (long long)M * z.no;
+  hipStream_t s = n->stream;
+  auto row_tiles = [&](int N) {
+    const int t = tile_for(M, N, 1);
+    return (M + t - 1) / t;
+  };
+  encode(n, B, x_dev, true);
+  Epi e{};
+  e.bias = n->b4;
+  e.t = t_dev;
+  e.h = n->dyb;
+  e.loss = n->part;
+  e.col = n->cpart[3];
+  e.scale = 1.f / (float)ny;
+  gemm<0, 0, 0, EP_MSE>(operand(n->h3, z.h), operand(n->W4b, z.no), e, M, z.no, z.h, s);
+  hipLaunchKernelGGL(k_sum, dim3(1), dim3(1024), 0, s, n->part,
+                     (int)tiles(tile_for(M, z.no, 1), M, z.no), n->loss);
   // decoder layer 2: Y = H3 W4 + b4
-  gemm_wgrad(1, 0, n->h3, n->dyb, n->gW4, z.h, z.no, (int)M, z.h, z.no, n->split, s);
-  // db4 = colsum(dY) needs dY in FP32: recompute as 2(Y - T)/ny inside a colsum of Y - T
-  gemm(0, 1, n->dyb, n->W4b, n->dh3, nullptr, (int)M, z.h, z.no, z.no, z.no, z.h, s);
-  hipLaunchKernelGGL(k_silu_back, g1(M * z.h), dim3(256), 0, s, n->dh3, n->z3, n->dz3, n->dz3b,
-                     M * z.h);
-  gemm_wgrad(1, 0, n->h2, n->dz3b, n->gW3, z.c2, z.h, (int)M, z.c2, z.h, n->split, s);
-  colsum(n->dz3, nullptr, (int)M, z.h, 1.0, n->gb3, n->cpart, s);
-  gemm(0, 1, n->dz3b, n->W3b, n->dh2, nullptr, (int)M, z.c2, z.h, z.h, z.h, z.c2, s);
-  hipLaunchKernelGGL(k_silu_back, g1(M * z.c2), dim3(256), 0, s, n->dh2, n->z2, n->dz2, n->dz2b,
-                     M * z.c2);
-  gemm_wgrad(1, 0, n->a2, n->dz2b, n->gW2, z.k2, z.c2, (int)M, z.k2, z.c2, n->split, s);
-  colsum(n->dz2, nullptr, (int)M, z.c2, 1.0, n->gb2, n->cpart, s);
-  gemm(0, 1, n->dz2b, n->W2b, n->da2, nullptr, (int)M, z.k2, z.c2, z.c2, z.c2, z.k2, s);
-  hipLaunchKernelGGL(k_col2im, g1(M * z.c1), dim3(256), 0, s, n->da2, n->dh1, B, nt, np, z.c1,
-                     -1, 3);
-  hipLaunchKernelGGL(k_silu_back, g1(M * z.c1), dim3(256), 0, s, n->dh1, n->z1, n->dz1, n->dz1b,
-                     M * z.c1);
-  gemm_wgrad(1, 0, n->a1, n->dz1b, n->gW1, z.k1, z.c1, (int)M, z.k1, z.c1, n->split, s);
-  colsum(n->dz1, nullptr, (int)M, z.c1, 1.0, n->gb1, n->cpart, s);
+  gemm_wgrad<0>(operand(n->h3, z.h), operand(n->dyb, z.no), n->gW4, z.h, z.no, M, n->split, s);
+  gemm<0, 1, 0, EP_BACK>(operand(n->dyb, z.no), operand(n->W4b, z.no),
+                         back_epi(n->z3, n->dz3b, n->cpart[2]), M, z.h, z.no, s);
+  gemm_wgrad<0>(operand(n->h2, z.c2), operand(n->dz3b, z.h), n->gW3, z.c2, z.h, M, n->split, s);
+  gemm<0, 1, 0, EP_BACK>(operand(n->dz3b, z.h), operand(n->W3b, z.h),
+                         back_epi(n->z2, n->dz2b, n->cpart[1]), M, z.c2, z.h, s);
+  gemm_wgrad<1>(conv_operand(n->h1, conv2(n)), operand(n->dz2b, z.c2), n->gW2, z.k2, z.c2, M,
+                n->split, s);
+  Epi da{};
+  da.c = n->da2;
+  da.ldc = z.k2;
+  gemm<0, 1, 0, EP_OUT>(operand(n->dz2b, z.c2), operand(n->W2b, z.c2), da, M, z.k2, z.c2, s);
+  const int ci = (M + CI_ROWS - 1) / CI_ROWS;
+  hipLaunchKernelGGL(k_col2im_back, dim3(ci, (z.c1 + 63) / 64), dim3(256), 0, s, n->da2, n->z1,
+                     n->dz1b, n->cpart[0], M, conv2(n));
+  gemm_wgrad<1>(conv_operand(n->xb, conv1(n)), operand(n->dz1b, z.c1), n->gW1, z.k1, z.c1, M,
+                n->split, s);
+  ColJobs jobs;
+  float* db[4] = {n->gb1, n->gb2, n->gb3, n->gb4};
+  const int width[4] = {z.c1, z.c2, z.h, z.no};
+  int blk = 0;
+  for (int q = 0; q < 4; ++q) {
+    jobs.j[q] = ColJob{n->cpart[q], db[q], q == 0 ? ci : row_tiles(width[q]), width[q], blk,
+                       q == 3 ? 2.0 / (double)ny : 1.0};
+    blk += (width[q] + 63) / 64;
+  }
+  hipLaunchKernelGGL(k_colsum_fin, dim3(blk), dim3(1024), 0, s, jobs);
 }
 
 }  // namespace
@@ -763,11 +1077,7 @@ int icr_nn_get_params(icr_nn* n, float* host) {
 int icr_nn_forward(icr_nn* n, int batch, const float* x_dev, float* y_dev) {
   if (!n || !x_dev) return nfail(ICR_NN_ERR_ARG, "NULL argument");
   if (batch < 1 || batch > n->s.batch_max) return nfail(ICR_NN_ERR_ARG, "batch outside [1, %d]", n->s.batch_max);
-  forward(n, batch, x_dev);
-  if (y_dev) {
-    const long long ny = (long long)batch * n->z.ncol * n->z.no;
-    NN_TRY(hipMemcpyAsync(y_dev, n->y, 4 * ny, hipMemcpyDeviceToDevice, n->stream));
-  }
+  forward(n, batch, x_dev, y_dev ? y_dev : n->y);
   NN_TRY(hipGetLastError());
   return ICR_NN_OK;
 }
@@ -776,11 +1086,8 @@ int icr_nn_loss_grad(icr_nn* n, int batch, const float* x_dev, const float* t_de
                      float* grad_host) {
   if (!n || !x_dev || !t_dev) return nfail(ICR_NN_ERR_ARG, "NULL argument");
   if (batch < 1 || batch > n->s.batch_max) return nfail(ICR_NN_ERR_ARG, "batch outside [1, %d]", n->s.batch_max);
-  forward(n, batch, x_dev);
-  backward(n, batch, t_dev);
-  const long long M = (long long)batch * n->z.ncol;
-  const long long ny = M * n->z.no;
-  colsum(n->y, t_dev, (int)M, n->z.no, 2.0 / (double)ny, n->gb4, n->cpart, n->stream);
+  loss_grad(n, batch, x_dev, t_dev);
+  const long long ny = (long long)batch * n->z.ncol * n->z.no;
   NN_TRY(hipGetLastError());
   double l = 0.0;
   NN_TRY(hipMemcpyAsync(&l, n->loss, 8, hipMemcpyDeviceToHost, n->stream));
@@ -840,8 +1147,16 @@ int icr_nn_decode_state(icr_nn* n, const double* map_dev, const float* y_dev, co
 int icr_nn_gemm_bf16(int trans_a, int trans_b, int M, int N, int K, const void* A, int lda,
                      const void* B, int ldb, float* C, int ldc, const float* bias, void* stream) {
   if (M < 1 || N < 1 || K < 1 || !A || !B || !C) return nfail(ICR_NN_ERR_ARG, "invalid GEMM");
-  gemm(trans_a, trans_b, (const uint16_t*)A, (const uint16_t*)B, C, bias, M, N, K, lda, ldb, ldc,
-       (hipStream_t)stream);
+  const Operand a = operand((const uint16_t*)A, lda), b = operand((const uint16_t*)B, ldb);
+  Epi e{};
+  e.c = C;
+  e.ldc = ldc;
+  e.bias = bias;
+  hipStream_t s = (hipStream_t)stream;
+  if (!trans_a && !trans_b) gemm<0, 0, 0, EP_OUT>(a, b, e, M, N, K, s);
+  else if (!trans_a) gemm<0, 1, 0, EP_OUT>(a, b, e, M, N, K, s);
+  else if (!trans_b) gemm<1, 0, 0, EP_OUT>(a, b, e, M, N, K, s);
+  else gemm<1, 1, 0, EP_OUT>(a, b, e, M, N, K, s);
   NN_TRY(hipGetLastError());
   return ICR_NN_OK;
 }

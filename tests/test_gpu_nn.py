@@ -142,3 +142,38 @@ def test_transforms_match_oracle(torch):
     assert np.allclose(st, ref, rtol=1e-12, atol=1e-30)
     t = net.encode_target(dm[0], torch.from_numpy(ref).cuda(), drc, dth, om, rin).cpu().numpy()
     assert np.allclose(t, no.encode_target(m, ref, rc, th, om, rin, 1.5), rtol=1e-5, atol=1e-6)
+
+
+# Tile edges and the forms of the operand loads: odd channel counts (element
+# loads), counts off the 8-channel loads, rows off the 64- and 128-row tiles,
+# and an output layer wide and tall enough for the 128 x 128 tiles and for
+# several reduction slabs (n_theta, n_phi, n_r, c1, c2, hidden, batch, window,
+# coord).  Same bounds as above: both sides round the operands to bfloat16.
+EDGE_SHAPES = [(5, 9, 3, 5, 7, 11, 1, (-1, 2), 0), (7, 11, 4, 6, 12, 20, 3, (0, 4), 1),
+               (8, 16, 9, 64, 128, 72, 1, (-2, 6), 1), (13, 30, 7, 16, 65, 129, 2, (-2, 9), 0),
+               (33, 60, 150, 8, 16, 48, 4, (-1, 1), 0)]
+
+
+@pytest.mark.parametrize("shape", EDGE_SHAPES)
+def test_network_tile_edges(torch, shape):
+    from paper_2501_15923_amd.nn import WarmStartNet, init_params
+    nt, nph, nr, c1, c2, h, batch, window, coord = shape
+    net = WarmStartNet(nt, nph, nr, c1, c2, h, batch_max=batch + 1, phi_lo=window[0],
+                       phi_hi=window[1], coord=coord)
+    p = init_params(*net.dims, seed=3)
+    p[-8 * nr - h * 8 * nr:] *= 10
+    net.set_params(p)
+    sh = no.Shape(*net.dims)
+    p64 = p.astype(np.float32).astype(np.float64)
+    rng = np.random.default_rng(11)
+    x = rng.normal(size=(batch, nt, nph, sh.cin)).astype(np.float32)
+    t = rng.normal(size=(batch * nt * nph, 8 * nr)).astype(np.float32)
+    y = net.forward(torch.from_numpy(x).cuda()).cpu().numpy()
+    ref, _ = no.forward(sh, p64, x)
+    assert np.linalg.norm(y - ref) / np.linalg.norm(ref) < 5e-3
+    loss, g = net.loss_grad(torch.from_numpy(x).cuda(), torch.from_numpy(t).cuda(),
+                            want_grad=True)
+    lo, go = no.loss_grad(sh, p64, x, t)
+    assert abs(loss - lo) <= 5e-3 * abs(lo)
+    assert g @ go / (np.linalg.norm(g) * np.linalg.norm(go)) >= 0.9999
+    assert np.linalg.norm(g - go) / np.linalg.norm(go) <= 1e-2
