@@ -44,8 +44,7 @@ __device__ __forceinline__ void lds_face(const R* base, int stride, R gam, R igm
   for (int v = 0; v < NV; ++v) {
     const R* q = base + v * vstride;
     const R p0 = q[0], p1 = q[stride], p2 = q[2 * stride], p3 = q[3 * stride];
-    wl[v] = p1 + R(0.5) * limiter<R, LIM, true>(p1 - p0, p2 - p1);
-    wr[v] = p2 - R(0.5) * limiter<R, LIM, true>(p2 - p1, p3 - p2);
+    face_states<R, LIM, true>(p0, p1, p2, p3, wl[v], wr[v]);
   }
   face_flux<R, N, FLUX, true>(wl, wr, gam, igm1, f);
 }
@@ -71,7 +70,9 @@ struct alignas(16) StageF {
   R sFt[NV][TT + 1][TR];
   // the metric factors of the tile's cells, loaded once per block: per-r
   // arrays at each lane's cell, per-theta arrays at each row's cell (the
-  // update then reads them from LDS instead of loading them every plane)
+  // update then reads them from LDS instead of loading them every plane).
+  // The face areas (r+-^2, sin t+-) are stored divided by the cell's 1-D
+  // volume (times 1/V_r, 1/C_t), as the divergence uses them
   R mr[MR_N][TR];
   R mt[MT_N][TT];
 };
@@ -193,12 +194,20 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R>& a, int kplanes, i
     const int icl = ii < 0 ? (a.asymm ? (-1 - ii < nr ? -1 - ii : nr - 1) : 0)
                            : (ii < nr ? ii : nr - 1);
 #pragma unroll
-    for (int arr = 0; arr < MR_N; ++arr) smf.mr[arr][l] = ldg(metric_r(a.m, arr), (unsigned)icl);
+    for (int arr = 0; arr < MR_N; ++arr) {
+      R x = ldg(metric_r(a.m, arr), (unsigned)icl);
+      if (arr == MR_RM2 || arr == MR_RP2) x *= ldg(a.m.ivr, (unsigned)icl);
+      smf.mr[arr][l] = x;
+    }
   }
   for (int row = tid; row < TT; row += NT) {
     const int jr = j0 + row < nt ? j0 + row : nt - 1;
 #pragma unroll
-    for (int arr = 0; arr < MT_N; ++arr) smf.mt[arr][row] = ldg(metric_t(a.m, arr), (unsigned)jr);
+    for (int arr = 0; arr < MT_N; ++arr) {
+      R x = ldg(metric_t(a.m, arr), (unsigned)jr);
+      if (arr == MT_SM || arr == MT_SP) x *= ldg(a.m.ict, (unsigned)jr);
+      smf.mt[arr][row] = x;
+    }
   }
   const LdsCellMetric<R, TR, TT> cm{smf, ti, tj, a.m.ilth};
   // the stage's dt, read once: a global load inside the update would make
@@ -446,17 +455,15 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R>& a, int kplanes, i
         if (dma_on && k + 1 < kend) dma_halo(k + 1);  // in flight during this update
       }
       if (valid) {
-        const R rm2 = cm.r(MR_RM2), rp2 = cm.r(MR_RP2), ivr = cm.r(MR_IVR);
-        const R hr = cm.r(MR_HR);
-        const R sm = cm.t(MT_SM), sp = cm.t(MT_SP), ict = cm.t(MT_ICT);
+        const R r0 = cm.r(MR_RM2), r1 = cm.r(MR_RP2), hr = cm.r(MR_HR);
+        const R t0 = hr * cm.t(MT_SM), t1 = hr * cm.t(MT_SP);
         const R fph = hr * cm.t(MT_PHF);
         R L[NV];
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-          L[v] = R(0);
-          L[v] -= (rp2 * sFr[v][tj][ti + 1] - rm2 * sFr[v][tj][ti]) * ivr;
-          L[v] -= hr * (sp * sFt[v][tj + 1][ti] - sm * sFt[v][tj][ti]) * ict;
-          L[v] -= fph * (fhi[v] - fcar[v]);
+          const R dr = fma_(r0, sFr[v][tj][ti], -r1 * sFr[v][tj][ti + 1]);
+          const R dth = fma_(t0, sFt[v][tj][ti], -t1 * sFt[v][tj + 1][ti]);
+          L[v] = fma_(fph, fcar[v] - fhi[v], dr + dth);
         }
         add_sources_cm<R>(wa, cm, a.omega, a.gravity, a.corot, L);
         // the stage's own conserved state, rebuilt from the ring's primitives
