@@ -311,7 +311,7 @@ int icr_boundary_at(icr_solver *s, double t_s, double *out);
  * tracer keeps 64 for variant 2; a WENO5 solver's variant 2 is its own
  * 64-lane tile of 58 cells along r, and with the tracer it runs variant 1);
  * 256 threads per block.  planes: phi planes per block of
- * variant 2 (1..n_phi, 0 = 8).  use_graphs: 1 replays steps from captured
+ * variant 2 (1..n_phi, 0 = chosen from the grid's size, also the default).  use_graphs: 1 replays steps from captured
  * HIP graphs.  All tiles and plane counts of one variant give bit-identical
  * results; the two variants agree to rounding. */
 int icr_set_launch(icr_solver *s, int variant, int tile_r, int planes,
@@ -366,8 +366,8 @@ void icr_ens_destroy(icr_ensemble *e);
  * icr_get_state and icr_get_clock.  Do not destroy it. */
 int icr_ens_run(icr_ensemble *e, int r, icr_solver **out);
 
-/* Phi planes per tile for run r (1..n_phi); the autotuner's knob.  The
- * result does not depend on it. */
+/* Phi planes per tile for run r (1..n_phi; chosen from the sizes of all runs
+ * until set); the autotuner's knob.  The result does not depend on it. */
 int icr_ens_set_planes(icr_ensemble *e, int r, int planes);
 
 /* persistent: 1 (default) one launch for many steps, 0 one launch per phase;

@@ -81,6 +81,48 @@ constexpr long long STAGE_CELLS = 65536;
 
 size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
+// Phi planes per stage block where the caller leaves the choice.  A block
+// marches over p planes after a prologue worth C of a plane (ring loads and
+// one phi face), and `slots` blocks run at once (256 CUs x 2 blocks in FP64,
+// 3 in FP32), so B(p) blocks take (p + C) R(B / slots) plane times.  R was
+// read off sweeps of p = 1 .. 120 over grids from 64x16x32 to 600x60x120:
+// one round at one block per CU or fewer costs 0.7 of a full round (a block
+// alone on a CU runs faster), a last round that is at most half full about
+// 0.4 + 0.3 f of one, a fuller one 0.6 + 0.4 f.  Measured, FP64 minmod +
+// TVDLF, stage 1 + 2, against the 8 planes of every grid before: 64x16x32
+// (p = 1) 109 -> 30 us, 150x30x60 (p = 3) 99 -> 74 us, 331x47x91 with HLLD
+// (p = 4) 356 -> 325 us, 600x60x120 (p = 12) 618 -> 610 us.  Longer marches
+// than 16 planes gained nothing on any of them.  Grids of more than 16 rounds
+// at 8 planes keep 8: the choice is worth less than 2 % there, and the block
+// counts that icr_step_noalloc accepts stay what they were.
+constexpr double PLANE_PROLOGUE = 0.45;
+constexpr int PLANES_FIXED = 8, PLANES_MOST = 16;
+
+double stage_rounds(double r) {
+  const double full = std::floor(r), f = r - full;
+  if (f == 0.0) return full;
+  if (full == 0.0) return f <= 0.5 ? 0.7 : 1.0;
+  return full + (f <= 0.5 ? 0.4 + 0.3 * f : 0.6 + 0.4 * f);
+}
+
+inline int stage_slots(bool f32) { return 256 * (f32 ? 3 : 2); }
+
+// blocks(p): stage blocks at p planes
+template <typename F>
+int choose_planes(int np_max, int slots, F blocks) {
+  if (blocks(PLANES_FIXED) > 16LL * slots) return PLANES_FIXED;
+  int best = 1;
+  double best_cost = 0.0;
+  for (int p = 1; p <= PLANES_MOST && p <= np_max; ++p) {
+    const double cost = (p + PLANE_PROLOGUE) * stage_rounds((double)blocks(p) / slots);
+    if (p == 1 || cost < best_cost) {
+      best = p;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
 struct Layout {
   size_t u[3], g[2], m64, mr, maps, tau, cme, traj, plog, pout, clock, partials, stage, total;
   long long stage_cells;  // cells per host-transfer chunk
@@ -236,7 +278,8 @@ struct icr_solver {
   std::vector<double> tau_h;  // map times (code units) held on the device, ascending
   double cadence;
   double r_in, omega, gm, dph;
-  int tile_r, variant, use_graphs, planes;
+  int tile_r, variant, use_graphs;
+  int planes;              // phi planes per stage block, 0: by the rule of choose_planes
   hipGraphExec_t g_steps[NGRAPH][2];
   bool graphs_ok;
   int dev;                  // HIP device the solver was created on
@@ -260,13 +303,20 @@ struct icr_solver {
     const int tr = v1_tile(), tt = 256 / tr;
     return dim3((g.n_r + tr - 1) / tr, (g.n_theta + tt - 1) / tt, g.n_phi);
   }
+  long long tile_blocks(int pl) const {
+    if (p.limiter == ICR_LIM_WENO5) return stage_w5_blocks(g.n_r, g.n_theta, g.n_phi, pl);
+    return stage_lds_blocks(g.n_r, g.n_theta, g.n_phi, tile_r, pl);
+  }
+  int stage_planes() const {
+    if (planes > 0) return planes;
+    return choose_planes(g.n_phi, stage_slots(f32), [&](int pl) { return tile_blocks(pl); });
+  }
   int stage_blocks() const {
     if (variant == 1) {
       const dim3 gr = grid();
       return (int)(gr.x * gr.y * gr.z);
     }
-    if (p.limiter == ICR_LIM_WENO5) return (int)stage_w5_blocks(g.n_r, g.n_theta, g.n_phi, planes);
-    return (int)stage_lds_blocks(g.n_r, g.n_theta, g.n_phi, tile_r, planes);
+    return (int)tile_blocks(stage_planes());
   }
 
   BndArgs bnd() {
@@ -359,20 +409,21 @@ struct icr_solver {
   void enqueue_stages(int from, int to, hipStream_t st, hipEvent_t* ev) {
     const StageArgs<R> a1 = stage_args<R>(from, from, 2, 0);
     const StageArgs<R> a2 = stage_args<R>(2, from, to, 1);
+    const int pl = stage_planes();
     if (variant == 1)
       launch_stage<R>(a1, 1, p.flux, p.limiter, grid(), block(), st);
     else if (p.limiter == ICR_LIM_WENO5)
-      launch_stage_w5<R>(a1, 1, p.flux, planes, st);
+      launch_stage_w5<R>(a1, 1, p.flux, pl, st);
     else
-      launch_stage_lds<R>(a1, 1, p.flux, p.limiter, tile_r, planes, st);
+      launch_stage_lds<R>(a1, 1, p.flux, p.limiter, tile_r, pl, st);
     if (trc()) launch_tracer<R>(tracer_args<R>(from, from, from, 2, 0), 1, st);
     if (ev) (void)hipEventRecord(ev[2], st);
     if (variant == 1)
       launch_stage<R>(a2, 2, p.flux, p.limiter, grid(), block(), st);
     else if (p.limiter == ICR_LIM_WENO5)
-      launch_stage_w5<R>(a2, 2, p.flux, planes, st);
+      launch_stage_w5<R>(a2, 2, p.flux, pl, st);
     else
-      launch_stage_lds<R>(a2, 2, p.flux, p.limiter, tile_r, planes, st);
+      launch_stage_lds<R>(a2, 2, p.flux, p.limiter, tile_r, pl, st);
     if (trc()) launch_tracer<R>(tracer_args<R>(2, 2, from, to, 1), 2, st);
     if (ev) (void)hipEventRecord(ev[3], st);
     launch_finalize<R>(clock(), partials(), stage_blocks(), p.cfl, 1, logging() ? 1 : 0,
@@ -517,7 +568,7 @@ int icr_create(const icr_grid* g, const icr_phys* p, void* ws, size_t ws_bytes, 
   // WENO5 with the tracer: the thread-per-cell kernel (the WENO5 face-once
   // tile keeps no face mass fluxes)
   s->variant = (p->limiter == ICR_LIM_WENO5 && p->tracer) ? 1 : 2;
-  s->planes = 8;
+  s->planes = 0;
   s->use_graphs = 1;
   s->graphs_ok = false;
   s->part_override = nullptr;
@@ -1189,9 +1240,10 @@ int icr_set_launch(icr_solver* s, int variant, int tile_r, int planes, int use_g
     return fail(ICR_ERR_ARG, "variant 1 tile_r must be 64, 128 or 256 (got %d)", tile_r);
   if (variant == 2 && tile_r != 32 && tile_r != 64)
     return fail(ICR_ERR_ARG, "variant 2 tile_r must be 32 or 64 (got %d)", tile_r);
-  if (planes == 0) planes = 8;
-  if (planes < 1 || planes > s->g.n_phi)
-    return fail(ICR_ERR_ARG, "planes must be in [1, n_phi] (got %d)", planes);
+  // (0 is refused below 8 planes, as the 8 it once stood for)
+  const int least = planes == 0 ? PLANES_FIXED : planes;
+  if (least < 1 || least > s->g.n_phi)
+    return fail(ICR_ERR_ARG, "planes must be in [1, n_phi] (got %d)", least);
   if (variant == 2 && s->trc()) tile_r = 64;  // the tracer's flux stores exist for 64 x 4
   s->variant = variant;
   s->tile_r = tile_r;
@@ -1214,7 +1266,7 @@ struct icr_ensemble {
   char* ws;
   size_t table_bytes;
   std::vector<icr_solver*> runs;
-  std::vector<int> planes;
+  std::vector<int> planes;  // per run, 0: by the rule over all runs' tiles
   // device tables
   void* d_runs;
   int* d_tile_off;
@@ -1280,15 +1332,27 @@ RunDesc<R> make_desc(icr_solver* s, int planes) {
 int ens_upload(icr_ensemble* e) {
   const int n = e->n;
   std::vector<int> toff(n + 1, 0), boff(n + 1, 0), coff(n + 1, 0);
+  int np_max = 1;
+  for (const icr_solver* s : e->runs) np_max = s->g.n_phi > np_max ? s->g.n_phi : np_max;
+  const int slots = e->persistent ? e->grid : stage_slots(e->f32);
+  const int pl = choose_planes(np_max, slots, [&](int p) {
+    long long b = 0;
+    for (const icr_solver* s : e->runs) b += s->tile_blocks(p);
+    return b;
+  });
+  auto planes = [&](int r) {
+    const int want = e->planes[r] > 0 ? e->planes[r] : pl, np = e->runs[r]->g.n_phi;
+    return want < np ? want : np;
+  };
   std::vector<char> host(sizeof(RunDesc<double>) * n);
   for (int r = 0; r < n; ++r) {
     icr_solver* s = e->runs[r];
     if (e->f32) {
-      RunDesc<float> d = make_desc<float>(s, e->planes[r]);
+      RunDesc<float> d = make_desc<float>(s, planes(r));
       std::memcpy(host.data() + sizeof(RunDesc<float>) * r, &d, sizeof d);
       toff[r + 1] = toff[r] + d.nbx * d.nby * d.nbz;
     } else {
-      RunDesc<double> d = make_desc<double>(s, e->planes[r]);
+      RunDesc<double> d = make_desc<double>(s, planes(r));
       std::memcpy(host.data() + sizeof(RunDesc<double>) * r, &d, sizeof d);
       toff[r + 1] = toff[r] + d.nbx * d.nby * d.nbz;
     }
@@ -1390,7 +1454,7 @@ int icr_ens_create(int n, const icr_grid* grids, const icr_phys* phys, void* ws,
   e->graph_ok = false;
   e->graph_n = 0;
   e->spin_limit = 1LL << 28;
-  e->planes.assign(n, 8);
+  e->planes.assign(n, 0);
   if (hipStreamCreateWithFlags(&e->cap_stream, hipStreamNonBlocking) != hipSuccess) {
     delete e;
     return fail(ICR_ERR_HIP, "hipStreamCreate failed");
@@ -1409,7 +1473,6 @@ int icr_ens_create(int n, const icr_grid* grids, const icr_phys* phys, void* ws,
     }
     e->runs.push_back(s);
     clocks[r] = s->clock();
-    if (e->planes[r] > grids[r].n_phi) e->planes[r] = grids[r].n_phi;
     w += b;
   }
   GridBar zero{};
