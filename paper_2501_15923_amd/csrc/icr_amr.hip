@@ -7,12 +7,13 @@
 // layers; a level-(l+1) block is one octant of a level-l block at twice the
 // resolution (radial edges split at the geometric mean).  One global dt,
 // SSP-RK2 on the leaves.  Per stage:
-//   k_amr_ghost   the ghost layers of every leaf, coarse levels first: copies
-//                 from a leaf of the same level, volume-weighted restriction
-//                 of finer leaves, conservative prolongation of the coarser
-//                 leaf (minmod slopes from its padded block, then a constant
-//                 correction so the children's volume-weighted mean is the
-//                 coarse cell), physical edges as in the uniform solver;
+//   k_amr_ghost   the ghost layers of every leaf, one block per leaf face:
+//                 copies from a leaf of the same level, volume-weighted
+//                 restriction of finer leaves, physical edges as in the
+//                 uniform solver; then, coarse levels first, the faces next
+//                 to a coarser leaf: conservative prolongation (minmod slopes
+//                 from its padded block, then a constant correction so the
+//                 children's volume-weighted mean is the coarse cell);
 //   k_amr_stage   reconstruct / flux / divergence / sources / RK combine of
 //                 every leaf cell, the fluxes of the block's six faces kept;
 //   k_amr_reflux  a coarse cell next to finer leaves takes the area-weighted
@@ -57,7 +58,7 @@ struct AmrArgs {
   double* F;   // [slot][6][9][fmax] fluxes of the block faces r-, r+, t-, t+, p-, p+
   const unsigned char* leaf;  // [slot]
   const int* key;             // [slot][4]: level, bi, bj, bk
-  AmrLevel lv[AMR_MAXL + 1];  // index = level (1 ..)
+  const AmrLevel* __restrict__ lv;  // [level], device table
   int nlev, br, bt, bp, pr, pt, pp, fmax;
   long long bvol;  // padded cells per variable of a block
   BndArgs bnd;     // maps and CMEs on the base grid
@@ -66,6 +67,24 @@ struct AmrArgs {
   double gam, gm1, igm1, omega, cfl, r_in;
   int gravity, corot;
 };
+
+// What a block needs to know of its leaf, and of one leaf face: built on the
+// host with the tree and read through scalar loads, one step from the data
+// (walking list -> key -> level map -> leaf flag cost each block that chain
+// of dependent loads).
+struct LeafDesc {
+  int slot, l, bi, bj, bk;
+  int other, finer;  // bit f: another level / finer leaves across face f
+  int src[6];        // ghosts of face f: LEAF_* | slot << 2
+};
+// from the padded block's own ghost layers; the same-level leaf's interior;
+// the leaf's own cells (zero gradient, mirror rows)
+enum { LEAF_POOL, LEAF_COPY, LEAF_SELF };
+struct FaceDesc {
+  int slot, face, kind, ns;  // face = 2 d + side (d = r, theta, phi); FACE_*
+  int l, bi, bj, bk;
+};
+enum { FACE_COPY, FACE_EDGE, FACE_INNER, FACE_FINE, FACE_COARSE };
 
 __device__ __forceinline__ long long pidx(const AmrArgs& a, int slot, int v, int kk, int jj,
                                           int ii) {
@@ -88,7 +107,7 @@ __device__ __forceinline__ int amr_slot(const AmrArgs& a, int l, int i, int j, i
 // Cell volume without the phi width, and the full volume, at level l.
 __device__ __forceinline__ double vol_nophi(const AmrArgs& a, int l, int i, int j) {
   const Metric<double>& m = a.lv[l].m;
-  return 1.0 / (m.ivr[i] * m.ict[j]);
+  return rcp_fast(m.ivr[i] * m.ict[j]);
 }
 
 // Inner-boundary primitive of level-l column (j, k): the map of the base
@@ -123,85 +142,34 @@ __device__ __forceinline__ double mm(double x, double y) {
   return x * y <= 0.0 ? 0.0 : (fabs(x) < fabs(y) ? x : y);
 }
 
-// Children (sub = e*4 + b*2 + c for phi, theta, r halves) of a level-l
-// coarse cell with centre value c0 and face neighbours n[6] (r-, r+, t-,
-// t+, p-, p+), the cell at global (ic, jc): conservative prolongation of one
-// variable; writes all 8 children.
-__device__ void prolong8(const AmrArgs& a, int l, int ic, int jc, double c0,
-                         const double (&n)[6], double (&ch)[8]) {
-  const double sr = mm(c0 - n[0], n[1] - c0);
-  const double st = mm(c0 - n[2], n[3] - c0);
-  const double sp = mm(c0 - n[4], n[5] - c0);
-  double vs = 0.0, ws = 0.0;
-  for (int s = 0; s < 8; ++s) {
-    const int e = s >> 2, b = (s >> 1) & 1, c = s & 1;
-    const double x = c0 + sp * (e ? 0.25 : -0.25) + st * (b ? 0.25 : -0.25) +
-                     sr * (c ? 0.25 : -0.25);
-    ch[s] = x;
-    const double v = vol_nophi(a, l + 1, 2 * ic + c, 2 * jc + b);
-    vs += v;
-    ws += x * v;
-  }
-  const double d = c0 - ws / vs;
-  for (int s = 0; s < 8; ++s) ch[s] += d;
+// Conservative prolongation of a level-l coarse cell (global ic, jc): child
+// (c, b, e) = (r, theta, phi half) is c0 + s_r (+-1/4 - f_r) + s_t (+-1/4 -
+// f_t) + s_p (+-1/4) with minmod slopes s and f_r, f_t the volume-weighted
+// means of the +-1/4 over the 8 children (phi's is zero), so that their
+// volume-weighted mean is c0.  The coefficients depend on the cell only and
+// serve all its variables.
+struct Prolong {
+  double cr, ct, cp;
+};
+__device__ __forceinline__ Prolong prolong_coef(const AmrArgs& a, int l, int ic, int jc, int sub) {
+  const double v00 = vol_nophi(a, l + 1, 2 * ic, 2 * jc);
+  const double v10 = vol_nophi(a, l + 1, 2 * ic + 1, 2 * jc);
+  const double v01 = vol_nophi(a, l + 1, 2 * ic, 2 * jc + 1);
+  const double v11 = vol_nophi(a, l + 1, 2 * ic + 1, 2 * jc + 1);
+  const double iv = 0.25 * rcp_fast((v00 + v10) + (v01 + v11));
+  Prolong p;
+  p.cr = (sub & 1 ? 0.25 : -0.25) - ((v10 + v11) - (v00 + v01)) * iv;
+  p.ct = (sub & 2 ? 0.25 : -0.25) - ((v01 + v11) - (v00 + v10)) * iv;
+  p.cp = sub & 4 ? 0.25 : -0.25;
+  return p;
 }
-
-// The level-l cell (i, j, k) (inside the domain) of buffer `buf` from the
-// leaves: a leaf of level l, the restriction of 8 finer leaf cells, or the
-// prolongation of the coarser leaf's cell (from its padded block).
-__device__ void amr_value(const AmrArgs& a, const double* buf, int l, int i, int j, int k,
-                          double (&u)[NA]) {
-  const int slot = amr_slot(a, l, i, j, k);
-  if (slot >= 0 && a.leaf[slot]) {
-    const int* key = a.key + 4 * slot;
-    const int ii = AG + i - key[1] * a.br, jj = AG + j - key[2] * a.bt, kk = AG + k - key[3] * a.bp;
-    for (int v = 0; v < NA; ++v) u[v] = buf[pidx(a, slot, v, kk, jj, ii)];
-    return;
-  }
-  if (slot >= 0) {  // refined: volume-weighted mean of the 8 children
-    if (l >= a.nlev) {  // cannot happen in a valid tree: poison, do not read
-      for (int v = 0; v < NA; ++v) u[v] = __builtin_nan("");
-      return;
-    }
-    double acc[NA], vs = 0.0;
-    for (int v = 0; v < NA; ++v) acc[v] = 0.0;
-    for (int s = 0; s < 8; ++s) {
-      const int e = s >> 2, b = (s >> 1) & 1, c = s & 1;
-      const int fi = 2 * i + c, fj = 2 * j + b, fk = 2 * k + e;
-      const int fs = amr_slot(a, l + 1, fi, fj, fk);
-      if (fs < 0) {  // cannot happen in a valid tree
-        for (int v = 0; v < NA; ++v) u[v] = __builtin_nan("");
-        return;
-      }
-      const int* key = a.key + 4 * fs;
-      const int ii = AG + fi - key[1] * a.br, jj = AG + fj - key[2] * a.bt,
-                kk = AG + fk - key[3] * a.bp;
-      const double vol = vol_nophi(a, l + 1, fi, fj);
-      vs += vol;
-      for (int v = 0; v < NA; ++v) acc[v] += buf[pidx(a, fs, v, kk, jj, ii)] * vol;
-    }
-    for (int v = 0; v < NA; ++v) u[v] = acc[v] / vs;
-    return;
-  }
-  // covered by the coarser leaf
-  const int ic = i >> 1, jc = j >> 1, kc = k >> 1;
-  const int cs = l > 1 ? amr_slot(a, l - 1, ic, jc, kc) : -1;
-  if (cs < 0) {  // cannot happen in a valid tree (levels differ by one)
-    for (int v = 0; v < NA; ++v) u[v] = __builtin_nan("");
-    return;
-  }
-  const int* key = a.key + 4 * cs;
-  const int ii = AG + ic - key[1] * a.br, jj = AG + jc - key[2] * a.bt, kk = AG + kc - key[3] * a.bp;
-  const int sub = ((k - 2 * kc) << 2) | ((j - 2 * jc) << 1) | (i - 2 * ic);
-  for (int v = 0; v < NA; ++v) {
-    const double c0 = buf[pidx(a, cs, v, kk, jj, ii)];
-    const double n[6] = {buf[pidx(a, cs, v, kk, jj, ii - 1)], buf[pidx(a, cs, v, kk, jj, ii + 1)],
-                         buf[pidx(a, cs, v, kk, jj - 1, ii)], buf[pidx(a, cs, v, kk, jj + 1, ii)],
-                         buf[pidx(a, cs, v, kk - 1, jj, ii)], buf[pidx(a, cs, v, kk + 1, jj, ii)]};
-    double ch[8];
-    prolong8(a, l - 1, ic, jc, c0, n, ch);
-    u[v] = ch[sub];
-  }
+// one variable at q = the coarse cell in a padded block
+__device__ __forceinline__ double prolong1(const double* q, int pr, int prt, const Prolong& p) {
+  const double c0 = q[0];
+  const double sr = mm(c0 - q[-1], q[1] - c0);
+  const double st = mm(c0 - q[-pr], q[pr] - c0);
+  const double sp = mm(c0 - q[-prt], q[prt] - c0);
+  return fma_(sp, p.cp, fma_(st, p.ct, fma_(sr, p.cr, c0)));
 }
 
 __device__ __forceinline__ void prim_to_cons9(const AmrArgs& a, const double (&w)[NV], double tr,
@@ -213,75 +181,144 @@ __device__ __forceinline__ void prim_to_cons9(const AmrArgs& a, const double (&w
 }
 
 // ---------------------------------------------------------------- ghosts --
-// One thread per ghost cell of the listed leaves of level l: r faces
-// (2 sides x 2 layers x bp x bt), theta faces (2 x 2 x bp x br), phi faces
-// (2 x 2 x bt x br).  Inside a step the fill follows the step clock (no work
-// once t_end is reached); a regrid fills whatever the clock says (always).
-__global__ void __launch_bounds__(256) k_amr_ghost(AmrArgs a, int l, const int* __restrict__ list,
-                                                   int n, int use_u1, int t_plus_dt, int always) {
-  const int nr_g = 4 * a.bp * a.bt, nt_g = 4 * a.bp * a.br, np_g = 4 * a.bt * a.br;
-  const int per = nr_g + nt_g + np_g;
-  const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= (long long)per * n || !(always || a.clock->active)) return;
-  const int slot = list[q / per];
-  int r = (int)(q % per);
+// One block per listed leaf face: its two ghost layers.  What lies across a
+// face is the same for all its cells.  Inside a step only the faces the
+// stage kernel does not read from its neighbours itself are filled (at 3800
+// leaves in four levels 4800 of 22900: 65 us a stage, where one thread per
+// ghost cell of every leaf took 195), and the fill follows the step clock (no
+// work once t_end is reached); a regrid fills every face, whatever the clock
+// says.
+__global__ void __launch_bounds__(256) k_amr_ghost(AmrArgs a, const FaceDesc* __restrict__ list,
+                                                   int use_u1, int t_plus_dt, int always) {
+  if (!(always || a.clock->active)) return;
+  const FaceDesc F = list[blockIdx.x];
+  const int slot = F.slot, d = F.face >> 1, side = F.face & 1, ns = F.ns, l = F.l;
   double* buf = use_u1 ? a.U1 : a.U;
-  const int* key = a.key + 4 * slot;
-  const int i0 = key[1] * a.br, j0 = key[2] * a.bt, k0 = key[3] * a.bp;
-  const AmrLevel& L = a.lv[l];
-  int d, side, g, x, y;  // direction, side, layer 1..2, transverse indices
-  if (r < nr_g) {
-    d = 0;
-  } else if (r < nr_g + nt_g) {
-    d = 1;
-    r -= nr_g;
-  } else {
-    d = 2;
-    r -= nr_g + nt_g;
+  const int n1 = d == 0 ? a.bt : a.br, n2 = d == 2 ? a.bt : a.bp;  // transverse extents
+  const int area = n1 * n2, bd = d == 0 ? a.br : (d == 1 ? a.bt : a.bp);
+  const int pr = a.pr, prt = a.pr * a.pt;
+  const int sd = d == 0 ? 1 : (d == 1 ? pr : prt);    // strides of a padded block
+  const int s1 = d == 0 ? pr : 1, s2 = d == 2 ? pr : prt;
+  double* own = buf + (long long)slot * NA * a.bvol;
+  const int o0 = AG * (1 + pr + prt);  // interior cell (0, 0, 0)
+  // ghost layer g = 1, 2 sits at index -g (lower side) or bd - 1 + g along d
+  auto ghost = [&](int g) { return (side ? bd - 1 + g : -g) * sd; };
+  // plain copies: 256 / (2 area) threads share a ghost cell's variables, all
+  // loads before the first store (they could alias it)
+  const int ng = 2 * area < 256 ? 256 / (2 * area) : 1;
+  const int vg = ng > 1 ? threadIdx.x / (2 * area) : 0, tq = threadIdx.x - vg * 2 * area;
+  if (F.kind == FACE_INNER || F.kind == FACE_EDGE) {
+    if (F.kind == FACE_INNER) {  // inner boundary: the same value in both layers
+      const double t = a.clock->t + (t_plus_dt ? a.clock->dt : 0.0);
+      for (int q = threadIdx.x; q < area; q += 256) {
+        const int y = q / n1, x = q - y * n1;
+        double w[NV], u[NA];
+        int inside;
+        amr_inner_prim(a, l, F.bj * a.bt + x, F.bk * a.bp + y, t, w, &inside);
+        prim_to_cons9(a, w, (double)inside, u);
+        const int o = o0 + y * s2 + x * s1;
+        for (int v = 0; v < NA; ++v) {
+          own[v * a.bvol + o + ghost(1)] = u[v];
+          own[v * a.bvol + o + ghost(2)] = u[v];
+        }
+      }
+    } else {  // zero gradient beyond r_out; mirror rows at the colatitude edges
+      for (int q0 = tq; q0 < 2 * area && vg < ng; q0 += 256) {
+        const int g = q0 < area ? 1 : 2, q = q0 - (g - 1) * area;
+        const int y = q / n1, x = q - y * n1;
+        const int o = o0 + y * s2 + x * s1;
+        const int src = d == 0 ? bd - 1 : (side ? bd - g : g - 1);
+        double t[NA];
+#pragma unroll
+        for (int c = 0; c < NA; ++c) {
+          const int v = vg + c * ng;
+          if (v < NA) t[c] = own[v * a.bvol + o + src * sd];
+          if (d == 1 && (v == 2 || v == 6)) t[c] = -t[c];
+        }
+#pragma unroll
+        for (int c = 0; c < NA; ++c) {
+          const int v = vg + c * ng;
+          if (v < NA) own[v * a.bvol + o + ghost(g)] = t[c];
+        }
+      }
+    }
+    return;
   }
-  const int w2 = d == 0 ? a.bt : a.br;  // fastest transverse extent
-  const int area = (d == 2 ? a.bt : a.bp) * w2;
-  side = r / (2 * area);
-  r -= side * 2 * area;
-  g = r / area + 1;
-  r -= (g - 1) * area;
-  y = r / w2;  // slower transverse (phi for r/theta faces, theta for phi faces)
-  x = r - y * w2;
-  // padded and global indices of the ghost cell
-  int ii, jj, kk;
-  if (d == 0) {
-    ii = side ? AG + a.br - 1 + g : AG - g;
-    jj = AG + x;
-    kk = AG + y;
-  } else if (d == 1) {
-    ii = AG + x;
-    jj = side ? AG + a.bt - 1 + g : AG - g;
-    kk = AG + y;
-  } else {
-    ii = AG + x;
-    jj = AG + y;
-    kk = side ? AG + a.bp - 1 + g : AG - g;
+  if (F.kind == FACE_COPY) {  // a leaf of the same level
+    const double* from = buf + (long long)ns * NA * a.bvol;
+    for (int q0 = tq; q0 < 2 * area && vg < ng; q0 += 256) {
+      const int g = q0 < area ? 1 : 2, q = q0 - (g - 1) * area;
+      const int y = q / n1, x = q - y * n1;
+      const int o = o0 + y * s2 + x * s1;
+      const int src = o + (side ? g - 1 : bd - g) * sd;
+      double t[NA];
+#pragma unroll
+      for (int c = 0; c < NA; ++c)
+        if (vg + c * ng < NA) t[c] = from[(vg + c * ng) * a.bvol + src];
+#pragma unroll
+      for (int c = 0; c < NA; ++c)
+        if (vg + c * ng < NA) own[(vg + c * ng) * a.bvol + o + ghost(g)] = t[c];
+    }
+    return;
   }
-  int i = i0 + ii - AG, j = j0 + jj - AG, k = k0 + kk - AG;
-  double u[NA];
-  if (d == 0 && i < 0) {  // inner boundary: the same value in both layers
-    const double t = a.clock->t + (t_plus_dt ? a.clock->dt : 0.0);
-    double w[NV];
-    int inside;
-    amr_inner_prim(a, l, j, k, t, w, &inside);
-    prim_to_cons9(a, w, (double)inside, u);
-  } else if (d == 0 && i >= L.nr) {  // zero gradient beyond r_out
-    for (int v = 0; v < NA; ++v) u[v] = buf[pidx(a, slot, v, kk, jj, AG + a.br - 1)];
-  } else if (d == 1 && (j < 0 || j >= L.nt)) {  // mirror rows at the colatitude edges
-    const int src = side ? AG + a.bt - g : AG + g - 1;
-    for (int v = 0; v < NA; ++v) u[v] = buf[pidx(a, slot, v, kk, src, ii)];
-    u[2] = -u[2];
-    u[6] = -u[6];
-  } else {
-    if (d == 2) k = (k + L.np) % L.np;
-    amr_value(a, buf, l, i, j, k, u);
+  for (int q0 = threadIdx.x; q0 < 2 * area; q0 += 256) {
+    const int g = q0 < area ? 1 : 2, q = q0 - (g - 1) * area;
+    const int y = q / n1, x = q - y * n1;
+    const int dst = o0 + y * s2 + x * s1 + ghost(g);
+    // global level-l indices of the ghost cell
+    const int along = side ? bd - 1 + g : -g;
+    const int i = F.bi * a.br + (d == 0 ? along : x);
+    const int j = F.bj * a.bt + (d == 0 ? x : (d == 1 ? along : y));
+    int k = F.bk * a.bp + (d == 2 ? along : y);
+    if (d == 2) k = k < 0 ? k + a.lv[l].np : (k >= a.lv[l].np ? k - a.lv[l].np : k);
+    if (F.kind == FACE_FINE) {  // refined: volume-weighted mean of the 8 children
+      // (the eight lookups, then the loads, all in flight together)
+      long long at[8];
+      double vol[8], acc[NA], vs = 0.0;
+      bool ok = true;
+      int fs[8];
+#pragma unroll
+      for (int s = 0; s < 8; ++s)
+        fs[s] = l < a.nlev ? amr_slot(a, l + 1, 2 * i + (s & 1), 2 * j + ((s >> 1) & 1),
+                                      2 * k + (s >> 2))
+                           : -1;
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        const int fi = 2 * i + (s & 1), fj = 2 * j + ((s >> 1) & 1), fk = 2 * k + (s >> 2);
+        ok = ok && fs[s] >= 0;
+        const int f0 = fs[s] < 0 ? 0 : fs[s];
+        at[s] = pidx(a, f0, 0, AG + fk % a.bp, AG + fj % a.bt, AG + fi % a.br);
+        vol[s] = vol_nophi(a, l + 1, fi, fj);
+        vs += vol[s];
+      }
+#pragma unroll
+      for (int v = 0; v < NA; ++v) {
+        acc[v] = 0.0;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) acc[v] = fma_(buf[at[s] + v * a.bvol], vol[s], acc[v]);
+      }
+      // a missing child cannot happen in a valid tree: poison
+      const double iv = ok ? rcp_fast(vs) : __builtin_nan("");
+#pragma unroll
+      for (int v = 0; v < NA; ++v) own[v * a.bvol + dst] = acc[v] * iv;
+    } else {  // covered by the coarser leaf
+      const int ic = i >> 1, jc = j >> 1, kc = k >> 1;
+      const int cs = l > 1 ? amr_slot(a, l - 1, ic, jc, kc) : -1;
+      if (cs < 0) {  // cannot happen in a valid tree (levels differ by one)
+        for (int v = 0; v < NA; ++v) own[v * a.bvol + dst] = __builtin_nan("");
+        continue;
+      }
+      const int* ckey = a.key + 4 * cs;
+      const double* c = buf + pidx(a, cs, 0, AG + kc - ckey[3] * a.bp, AG + jc - ckey[2] * a.bt,
+                                   AG + ic - ckey[1] * a.br);
+      const Prolong p = prolong_coef(a, l - 1, ic, jc, ((k & 1) << 2) | ((j & 1) << 1) | (i & 1));
+      double t[NA];
+#pragma unroll
+      for (int v = 0; v < NA; ++v) t[v] = prolong1(c + v * a.bvol, pr, prt, p);
+#pragma unroll
+      for (int v = 0; v < NA; ++v) own[v * a.bvol + dst] = t[v];
+    }
   }
-  for (int v = 0; v < NA; ++v) buf[pidx(a, slot, v, kk, jj, ii)] = u[v];
 }
 
 // ----------------------------------------------------------------- stage --
@@ -297,33 +334,32 @@ __device__ void amr_face(const AmrArgs& a, const double* buf, int slot, int d, i
     double u[NV];
     for (int v = 0; v < NV; ++v)
       u[v] = buf[pidx(a, slot, v, kk + o * dk, jj + o * dj, ii + o * di)];
-    cons2prim<double>(u, w[s], a.gm1);
+    cons2prim<double, true>(u, w[s], a.gm1);
     rho[s] = u[0];
     tr[s] = buf[pidx(a, slot, 8, kk + o * dk, jj + o * dj, ii + o * di)];
   }
   double wl[NV], wr[NV], fl[NV];
-  reconstruct<double, LIM>(w[0], w[1], w[2], w[3], wl, wr);
+  reconstruct<double, LIM, true>(w[0], w[1], w[2], w[3], wl, wr);
   if (d == 0)
-    face_flux<double, 1, FLUX>(wl, wr, a.gam, a.igm1, fl);
+    face_flux<double, 1, FLUX, true>(wl, wr, a.gam, a.igm1, fl);
   else if (d == 1)
-    face_flux<double, 2, FLUX>(wl, wr, a.gam, a.igm1, fl);
+    face_flux<double, 2, FLUX, true>(wl, wr, a.gam, a.igm1, fl);
   else
-    face_flux<double, 3, FLUX>(wl, wr, a.gam, a.igm1, fl);
+    face_flux<double, 3, FLUX, true>(wl, wr, a.gam, a.igm1, fl);
   for (int v = 0; v < NV; ++v) f[v] = fl[v];
   // tracer: mass flux times tau of the upwind cell
-  f[8] = fl[0] * (fl[0] >= 0.0 ? tr[1] / rho[1] : tr[2] / rho[2]);
+  f[8] = fl[0] * (fl[0] >= 0.0 ? tr[1] * rcp_fast(rho[1]) : tr[2] * rcp_fast(rho[2]));
 }
 
 // One thread per cell of the listed leaves (blocks of 256 threads loop over
 // a leaf's cells).  stage 1: U1 = U + dt L(U); stage 2: U = U/2 + (U1 + dt
 // L(U1))/2 in place.
 template <int FLUX, int LIM>
-__global__ void __launch_bounds__(256) k_amr_stage(AmrArgs a, const int* __restrict__ list,
+__global__ void __launch_bounds__(256) k_amr_stage(AmrArgs a, const LeafDesc* __restrict__ list,
                                                    int stage) {
   if (!a.clock->active) return;
-  const int slot = list[blockIdx.x];
-  const int* key = a.key + 4 * slot;
-  const int l = key[0];
+  const LeafDesc& D = list[blockIdx.x];
+  const int slot = D.slot, l = D.l;
   const AmrLevel& LV = a.lv[l];
   const Metric<double>& m = LV.m;
   const double dt = a.clock->dt;
@@ -333,7 +369,7 @@ __global__ void __launch_bounds__(256) k_amr_stage(AmrArgs a, const int* __restr
   for (int c = threadIdx.x; c < ncell; c += blockDim.x) {
     const int ci = c % a.br, cj = (c / a.br) % a.bt, ck = c / (a.br * a.bt);
     const int ii = AG + ci, jj = AG + cj, kk = AG + ck;
-    const int gi = key[1] * a.br + ci, gj = key[2] * a.bt + cj;
+    const int gi = D.bi * a.br + ci, gj = D.bj * a.bt + cj;
     double L[NA];
     for (int v = 0; v < NA; ++v) L[v] = 0.0;
     {  // r
@@ -383,143 +419,325 @@ __global__ void __launch_bounds__(256) k_amr_stage(AmrArgs a, const int* __restr
   }
 }
 
-// Face-once variant for leaves of at most 512 cells (two per thread): the
-// faces of one direction at a time go to LDS (each computed once by
-// amr_face, the same function and inputs as above, so the results are
-// bitwise those of k_amr_stage), then every thread adds them to the
-// right-hand sides of its cells, kept in registers.  Face index along
-// direction d: position p in [0, b_d] (between cells p-1 and p) fastest for
-// r, then the transverse cells.
-constexpr int AMR_FO_CELLS = 512;
-template <int FLUX, int LIM>
-__global__ void __launch_bounds__(256) k_amr_stage_fo(AmrArgs a, const int* __restrict__ list,
-                                                      int stage) {
-  extern __shared__ double sF[];  // [NA][faces of one direction]
+// Face-once variant for leaves whose primitives fit LDS.  The padded cells a
+// face can read (the interior and two layers beyond each side, no corners)
+// are converted once and kept in LDS, one slab of
+//   [bp][bt][br + 4]  interior with its r layers,
+//   [bp][4][br]       theta layers,  [4][bt][br]  phi layers
+// per variable (eight primitives and tau).  Every thread forms up to two
+// faces of each direction in registers; then the fluxes take the slabs' place,
+// five variables and four, and every thread updates up to two cells.
+// 256 threads and 80 KB (two blocks per CU, 10x6x6 cells and below) or 512
+// threads and 160 KB; larger leaves take k_amr_stage.  At a mean of 2900
+// leaves of 10x6x6 a stage takes 125 us, where every face converting its four
+// cells by itself, with IEEE divisions and roots, took 249; it is bound by the
+// latency of its phases (two waves per SIMD) and moves 0.35 GB at 3800 leaves.
+constexpr int AMR_LDS_S = 80 * 1024, AMR_LDS_L = 160 * 1024;
+__host__ __device__ constexpr int amr_slab(int br, int bt, int bp) {
+  return (br + 2 * AG) * bt * bp + 2 * AG * br * bp + 2 * AG * br * bt;
+}
+__host__ __device__ constexpr int amr_faces(int br, int bt, int bp, int d) {
+  return d == 0 ? (br + 1) * bt * bp : (d == 1 ? br * (bt + 1) * bp : br * bt * (bp + 1));
+}
+constexpr int AMR_V0 = 5;  // variables in the first round of fluxes
+// doubles of the slabs or of a round of fluxes, then the metric of the
+// leaf's rows: MR_N arrays along r, MT_N along theta
+__host__ __device__ inline int amr_lds_work(int br, int bt, int bp) {
+  const int nf = amr_faces(br, bt, bp, 0) + amr_faces(br, bt, bp, 1) + amr_faces(br, bt, bp, 2);
+  const int w = NA * amr_slab(br, bt, bp), f = AMR_V0 * nf;
+  return w > f ? w : f;
+}
+// bytes of LDS, and whether NT threads with two items each cover the leaf
+inline int amr_lds_bytes(int br, int bt, int bp) {
+  return (int)sizeof(double) * (amr_lds_work(br, bt, bp) + MR_N * br + MT_N * bt);
+}
+inline bool amr_covers(int nt, int br, int bt, int bp) {
+  for (int d = 0; d < 3; ++d)
+    if (amr_faces(br, bt, bp, d) > 2 * nt) return false;
+  return true;
+}
+
+struct AmrCellMetric {  // a cell's metric factors in LDS
+  const double *mr, *mt;
+  int br, bt;
+  __device__ __forceinline__ double r(int arr) const { return mr[arr * br]; }
+  __device__ __forceinline__ double t(int arr) const { return mt[arr * bt]; }
+};
+
+template <int FLUX, int LIM, int NT, int BYTES>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2)))
+k_amr_stage_lds(AmrArgs a, const LeafDesc* __restrict__ list, int stage) {
+  __shared__ double sm[BYTES / 8];
   if (!a.clock->active) return;
-  const int slot = list[blockIdx.x];
-  const int* key = a.key + 4 * slot;
-  const int l = key[0];
-  const AmrLevel& LV = a.lv[l];
-  const Metric<double>& m = LV.m;
+  const LeafDesc D = list[blockIdx.x];
+  const int slot = D.slot, tid = threadIdx.x;
+  const Metric<double>& m = a.lv[D.l].m;
   const double dt = a.clock->dt;
-  const double* in = stage == 1 ? a.U : a.U1;
-  double* out = stage == 1 ? a.U1 : a.U;
-  const int br = a.br, bt = a.bt, bp = a.bp;
-  const int ncell = br * bt * bp;
-  const int nfmax = (br + 1) * bt * bp > br * (bt + 1) * bp
-                        ? ((br + 1) * bt * bp > br * bt * (bp + 1) ? (br + 1) * bt * bp
-                                                                  : br * bt * (bp + 1))
-                        : (br * (bt + 1) * bp > br * bt * (bp + 1) ? br * (bt + 1) * bp
-                                                                  : br * bt * (bp + 1));
-  double L[2][NA];
-  for (int q = 0; q < 2; ++q)
-    for (int v = 0; v < NA; ++v) L[q][v] = 0.0;
-  for (int d = 0; d < 3; ++d) {
-    const int nf = d == 0 ? (br + 1) * bt * bp : (d == 1 ? br * (bt + 1) * bp : br * bt * (bp + 1));
-    for (int f = threadIdx.x; f < nf; f += blockDim.x) {
-      int p, ci, cj, ck;  // face position along d and the transverse cells
-      if (d == 0) {
-        p = f % (br + 1);
-        cj = (f / (br + 1)) % bt;
-        ck = f / ((br + 1) * bt);
-        ci = p;
-      } else if (d == 1) {
-        ci = f % br;
-        p = (f / br) % (bt + 1);
-        ck = f / (br * (bt + 1));
-        cj = p;
-      } else {
-        ci = f % br;
-        cj = (f / br) % bt;
-        p = f / (br * bt);
-        ck = p;
-      }
-      double fl[NA];
-      amr_face<FLUX, LIM>(a, in, slot, d, AG + ck, AG + cj, AG + ci, fl);
-      for (int v = 0; v < NA; ++v) sF[v * nfmax + f] = fl[v];
-      const int bd = d == 0 ? br : (d == 1 ? bt : bp);
-      if (p == 0 || p == bd) {  // block face: kept for the flux correction
-        const int q = d == 0 ? ck * bt + cj : (d == 1 ? ck * br + ci : cj * br + ci);
-        for (int v = 0; v < NA; ++v) a.F[fidx(a, slot, 2 * d + (p == bd), v, q)] = fl[v];
-      }
+  const int br = a.br, bt = a.bt, bp = a.bp, pr = a.pr, prt = a.pr * a.pt;
+  const double* pool = stage == 1 ? a.U : a.U1;
+  const long long leafsz = NA * a.bvol;
+  double* out = (stage == 1 ? a.U1 : a.U) + slot * leafsz;
+  const int rw = br + 2 * AG, nW = rw * bt * bp, nT = 2 * AG * br * bp;
+  const int S = amr_slab(br, bt, bp), ncell = br * bt * bp;
+  double* mr = sm + amr_lds_work(br, bt, bp);
+  double* mt = mr + MR_N * br;
+  for (int q = tid; q < MR_N * br + MT_N * bt; q += NT) {
+    if (q < MR_N * br) {
+      const int arr = q / br;
+      mr[q] = metric_r(m, arr)[D.bi * br + q - arr * br];
+    } else {
+      const int t = q - MR_N * br, arr = t / bt;
+      mt[t] = metric_t(m, arr)[D.bj * bt + t - arr * bt];
     }
-    __syncthreads();
-    for (int q = 0; q < 2; ++q) {
-      const int c = threadIdx.x + q * blockDim.x;
-      if (c >= ncell) break;
-      const int ci = c % br, cj = (c / br) % bt, ck = c / (br * bt);
-      const int gi = key[1] * br + ci, gj = key[2] * bt + cj;
-      if (d == 0) {
-        const int f0 = (ck * bt + cj) * (br + 1) + ci;
-        for (int v = 0; v < NA; ++v)
-          L[q][v] -= (m.rp2[gi] * sF[v * nfmax + f0 + 1] - m.rm2[gi] * sF[v * nfmax + f0]) *
-                     m.ivr[gi];
-      } else if (d == 1) {
-        const int f0 = (ck * (bt + 1) + cj) * br + ci;
-        for (int v = 0; v < NA; ++v)
-          L[q][v] -= m.hr[gi] *
-                     (m.sp[gj] * sF[v * nfmax + f0 + br] - m.sm[gj] * sF[v * nfmax + f0]) *
-                     m.ict[gj];
-      } else {
-        const int f0 = (ck * bt + cj) * br + ci;
-        const double fph = m.hr[gi] * m.phf[gj];
-        for (int v = 0; v < NA; ++v)
-          L[q][v] -= fph * (sF[v * nfmax + f0 + br * bt] - sF[v * nfmax + f0]);
-      }
-    }
-    __syncthreads();  // the next direction overwrites sF
   }
+  // (four cells a round: 36 loads in flight per thread; a ghost cell comes
+  // straight from the same-level leaf across its face, from the leaf's own
+  // edge cells, or from the padded block where k_amr_ghost formed it)
+  for (int e0 = tid; e0 < S; e0 += 4 * NT) {
+    double raw[4][NA];
+    bool flip[4];
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      const int e = e0 + h * NT;
+      int ii, jj, kk, s, hop;  // source word of the face, cells to its far side
+      if (e < nW) {
+        const int r = e / rw;
+        ii = e - r * rw;
+        jj = AG + r % bt;
+        kk = AG + r / bt;
+        s = ii < AG ? D.src[0] : (ii >= AG + br ? D.src[1] : LEAF_POOL);
+        hop = ii < AG ? br : -br;
+      } else if (e < nW + nT) {
+        const int r = (e - nW) / br;
+        const bool lo = (r & 3) < AG;
+        ii = AG + (e - nW) - r * br;
+        jj = lo ? (r & 3) : bt + (r & 3);
+        kk = AG + (r >> 2);
+        s = lo ? D.src[2] : D.src[3];
+        hop = (lo ? bt : -bt) * pr;
+      } else {
+        const int r = (e - nW - nT) / br, row = r / bt;
+        const bool lo = row < AG;
+        ii = AG + (e - nW - nT) - r * br;
+        jj = AG + r - row * bt;
+        kk = lo ? row : bp + row;
+        s = lo ? D.src[4] : D.src[5];
+        hop = (lo ? bp : -bp) * prt;
+      }
+      long long at = (s & 3) == LEAF_COPY ? (s >> 2) * leafsz + hop : slot * leafsz;
+      flip[h] = false;
+      if ((s & 3) == LEAF_SELF) {
+        if (e < nW) {
+          ii = AG + br - 1;  // zero gradient beyond r_out
+        } else {
+          jj = jj < AG ? 2 * AG - 1 - jj : 2 * (AG + bt) - 1 - jj;  // mirror row
+          flip[h] = true;
+        }
+      }
+      at += kk * prt + jj * pr + ii;
+      if (e < S) {
+#pragma unroll
+        for (int v = 0; v < NA; ++v) raw[h][v] = pool[at + v * a.bvol];
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      const int e = e0 + h * NT;
+      if (e < S) {
+        double u[NV], w[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) u[v] = raw[h][v];
+        cons2prim<double, true>(u, w, a.gm1);
+        if (flip[h]) flip_theta(w);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) sm[v * S + e] = w[v];
+        sm[8 * S + e] = raw[h][8] * rcp_fast(u[0]);
+      }
+    }
+  }
+  __syncthreads();
+  // fluxes: face index along direction d: position p in [0, b_d] (between
+  // cells p-1 and p) in place of that direction's cell index, r fastest
+  double fl[3][2][NA];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const int e0 = d == 0 ? br + 1 : br, e1 = d == 1 ? bt + 1 : bt;
+    const int bd = d == 0 ? br : (d == 1 ? bt : bp);
+    const int nf = amr_faces(br, bt, bp, d);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int f = tid + q * NT;
+      if (f < nf) {
+        const int r = f / e0, ci = f - r * e0, ck = r / e1, cj = r - ck * e1;
+        const int p = d == 0 ? ci : (d == 1 ? cj : ck);
+        int off[4];
+#pragma unroll
+        for (int o = 0; o < 4; ++o) {
+          const int c = p + o - 2;  // cell along d, -2 .. bd + 1
+          if (d == 0) {
+            off[o] = (ck * bt + cj) * rw + c + AG;
+          } else {
+            const bool inside = c >= 0 && c < bd;
+            const int g = c < 0 ? c + AG : c - bd + AG;
+            if (d == 1)
+              off[o] = inside ? (ck * bt + c) * rw + ci + AG : nW + (ck * 2 * AG + g) * br + ci;
+            else
+              off[o] = inside ? (c * bt + cj) * rw + ci + AG : nW + nT + (g * bt + cj) * br + ci;
+          }
+        }
+        double wl[NV], wr[NV], fv[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+          face_states<double, LIM, true>(sm[v * S + off[0]], sm[v * S + off[1]],
+                                         sm[v * S + off[2]], sm[v * S + off[3]], wl[v], wr[v]);
+        if (d == 0)
+          face_flux<double, 1, FLUX, true>(wl, wr, a.gam, a.igm1, fv);
+        else if (d == 1)
+          face_flux<double, 2, FLUX, true>(wl, wr, a.gam, a.igm1, fv);
+        else
+          face_flux<double, 3, FLUX, true>(wl, wr, a.gam, a.igm1, fv);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) fl[d][q][v] = fv[v];
+        // tracer: mass flux times tau of the upwind cell
+        fl[d][q][8] = fv[0] * sm[8 * S + (fv[0] >= 0.0 ? off[1] : off[2])];
+        if (p == 0 || p == bd) {  // block face next to another level: kept
+          const int face = 2 * d + (p == bd);
+          if (D.other >> face & 1) {
+            const int fq = d == 0 ? ck * bt + cj : (d == 1 ? ck * br + ci : cj * br + ci);
+#pragma unroll
+            for (int v = 0; v < NA; ++v) a.F[fidx(a, slot, face, v, fq)] = fl[d][q][v];
+          }
+        }
+      }
+    }
+  }
+  // the cells' own state (from the primitives: the stored values up to
+  // rounding, no reload), sources and metric factors
+  double uc[2][NA], un[2][NA], src[2][NV], cf[2][5];
+#pragma unroll
   for (int q = 0; q < 2; ++q) {
-    const int c = threadIdx.x + q * blockDim.x;
-    if (c >= ncell) break;
-    const int ci = c % br, cj = (c / br) % bt, ck = c / (br * bt);
-    const int ii = AG + ci, jj = AG + cj, kk = AG + ck;
-    const int gi = key[1] * br + ci, gj = key[2] * bt + cj;
-    double u[NV], w[NV];
-    for (int v = 0; v < NV; ++v) u[v] = in[pidx(a, slot, v, kk, jj, ii)];
-    cons2prim<double>(u, w, a.gm1);
-    double Ls[NV];
-    for (int v = 0; v < NV; ++v) Ls[v] = L[q][v];
-    add_sources<double>(w, m, gi, gj, a.omega, a.gravity, a.corot, Ls);
-    for (int v = 0; v < NV; ++v) L[q][v] = Ls[v];
-    for (int v = 0; v < NA; ++v) {
-      const long long o = pidx(a, slot, v, kk, jj, ii);
-      const double uc = in[o];
-      out[o] = stage == 1 ? uc + dt * L[q][v] : 0.5 * out[o] + 0.5 * (uc + dt * L[q][v]);
+    const int c = tid + q * NT;
+    if (c < ncell) {
+      const int r = c / br, ci = c - r * br, ck = r / bt, cj = r - ck * bt;
+      const int o = (AG + ck) * prt + (AG + cj) * pr + AG + ci;
+      if (stage == 2)
+#pragma unroll
+        for (int v = 0; v < NA; ++v) un[q][v] = out[v * a.bvol + o];
+      const int at = (ck * bt + cj) * rw + ci + AG;
+      double w[NV], u8[NV];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        w[v] = sm[v * S + at];
+        src[q][v] = 0.0;
+      }
+      prim2cons<double>(w, u8, a.igm1);
+#pragma unroll
+      for (int v = 0; v < NV; ++v) uc[q][v] = u8[v];
+      uc[q][8] = sm[8 * S + at] * w[0];
+      const AmrCellMetric cm{mr + ci, mt + cj, br, bt};
+      add_sources_cm<double>(w, cm, a.omega, a.gravity, a.corot, src[q]);
+      const double ivr = cm.r(MR_IVR), hr = cm.r(MR_HR), hc = hr * cm.t(MT_ICT);
+      cf[q][0] = cm.r(MR_RM2) * ivr;
+      cf[q][1] = cm.r(MR_RP2) * ivr;
+      cf[q][2] = hc * cm.t(MT_SM);
+      cf[q][3] = hc * cm.t(MT_SP);
+      cf[q][4] = hr * cm.t(MT_PHF);
+    }
+  }
+  const int nf0 = amr_faces(br, bt, bp, 0), nf1 = amr_faces(br, bt, bp, 1);
+  const int nfs = nf0 + nf1 + amr_faces(br, bt, bp, 2);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    constexpr int VB[3] = {0, AMR_V0, NA};
+    __syncthreads();  // the slabs (or the first fluxes) have been read
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int f = tid + q * NT;
+        if (f < amr_faces(br, bt, bp, d)) {
+          const int at = (d == 0 ? 0 : (d == 1 ? nf0 : nf0 + nf1)) + f;
+#pragma unroll
+          for (int v = VB[h]; v < VB[h + 1]; ++v) sm[(v - VB[h]) * nfs + at] = fl[d][q][v];
+        }
+      }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int c = tid + q * NT;
+      if (c < ncell) {
+        const int r = c / br, ci = c - r * br, ck = r / bt, cj = r - ck * bt;
+        const int o = (AG + ck) * prt + (AG + cj) * pr + AG + ci;
+        const int fr = r * (br + 1) + ci, ft = nf0 + (ck * (bt + 1) + cj) * br + ci;
+        const int fp = nf0 + nf1 + c;
+#pragma unroll
+        for (int v = VB[h]; v < VB[h + 1]; ++v) {
+          const double* F = sm + (v - VB[h]) * nfs;
+          const double dr = fma_(cf[q][0], F[fr], -cf[q][1] * F[fr + 1]);
+          const double dth = fma_(cf[q][2], F[ft], -cf[q][3] * F[ft + br]);
+          double L = fma_(cf[q][4], F[fp] - F[fp + br * bt], dr + dth);
+          if (v < NV) L += src[q][v < NV ? v : 0];
+          const double u1 = fma_(dt, L, uc[q][v]);
+          out[v * a.bvol + o] = stage == 1 ? u1 : 0.5 * un[q][v] + 0.5 * u1;
+        }
+      }
     }
   }
 }
 
 // --------------------------------------------------------- flux correction --
-// One thread per (listed face of direction d, face cell): the list holds
-// 2 slot + side of the coarse leaf faces whose neighbour region holds finer
-// leaves; the coarse face's A F is replaced by the sum of the fine faces'
-// A F.  coef: 1 after stage 1 (U1), 1/2 after stage 2 (U).  An edge or
-// corner cell of a block lies on faces of several directions: one launch
-// per direction keeps each cell's updates ordered (blocks have >= 4 cells a
-// side, so the two faces of one direction never share a cell).
-__global__ void __launch_bounds__(256) k_amr_reflux(AmrArgs a, const int* __restrict__ list,
-                                                    int n, int stage, int d) {
-  const int area = face_cells(a, d);
-  const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= (long long)area * n || !a.clock->active) return;
-  const int ent = list[q / area];
-  const int slot = ent >> 1, side = ent & 1;
-  const int fq = (int)(q % area);
-  const int* key = a.key + 4 * slot;
-  const int l = key[0];
-  if (l >= a.nlev) return;
+// One block per listed leaf (those with finer leaves across some face): the
+// coarse face's A F is replaced by the sum of the fine faces' A F.  coef: 1
+// after stage 1 (U1), 1/2 after stage 2 (U).  An edge or corner cell of a
+// block lies on faces of several directions: the directions follow each
+// other behind a barrier, so each cell's updates stay ordered (blocks have
+// >= 4 cells a side, so the two faces of one direction never share a cell).
+__device__ __forceinline__ long long amr_reflux_cell(const AmrArgs& a, const LeafDesc& D, int d,
+                                                     int side, int fq, int stage,
+                                                     double (&dU)[NA]);
+
+__global__ void __launch_bounds__(128) k_amr_reflux(AmrArgs a, const LeafDesc* __restrict__ list,
+                                                    int stage) {
+  if (!a.clock->active) return;
+  const LeafDesc D = list[blockIdx.x];
+  double* tgt = stage == 1 ? a.U1 : a.U;
+  const int most = 2 * max(face_cells(a, 0), max(face_cells(a, 1), face_cells(a, 2)));
+  for (int q0 = 0; q0 < most; q0 += 128) {
+    // the corrections of all three directions (the loads overlap), then
+    // their application in order
+    double dU[3][NA];
+    long long at[3];
+    const int q = q0 + threadIdx.x;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const int area = face_cells(a, d), side = q >= area;
+      at[d] = -1;
+      if (q < 2 * area && (D.finer >> (2 * d + side) & 1))
+        at[d] = amr_reflux_cell(a, D, d, side, q - side * area, stage, dU[d]);
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      __syncthreads();
+      if (at[d] >= 0) {
+        double t[NA];
+#pragma unroll
+        for (int v = 0; v < NA; ++v) t[v] = tgt[at[d] + v * a.bvol];
+#pragma unroll
+        for (int v = 0; v < NA; ++v) tgt[at[d] + v * a.bvol] = t[v] + dU[d][v];
+      }
+    }
+  }
+}
+
+// the correction dt dL of one coarse cell's variables, and its index in the
+// padded block of variable 0
+__device__ __forceinline__ long long amr_reflux_cell(const AmrArgs& a, const LeafDesc& D, int d,
+                                                     int side, int fq, int stage,
+                                                     double (&dU)[NA]) {
+  const int slot = D.slot, l = D.l;
   const int w2 = d == 0 ? a.bt : a.br;
   const int y = fq / w2, x = fq - y * w2;
-  // the neighbour block of the same level across this face
-  int nb[3] = {key[1], key[2], key[3]};
-  nb[d] += side ? 1 : -1;
   const AmrLevel& L = a.lv[l];
-  if (d == 2) nb[2] = (nb[2] + L.nbp) % L.nbp;
-  if (d == 0 && (nb[0] < 0 || nb[0] >= L.nbr)) return;
-  if (d == 1 && (nb[1] < 0 || nb[1] >= L.nbt)) return;
-  const int ns = L.map[((long long)nb[2] * L.nbt + nb[1]) * L.nbr + nb[0]];
-  if (ns < 0 || a.leaf[ns]) return;
   // coarse cell next to the face (block-local), its global indices
   int ci, cj, ck;
   if (d == 0) {
@@ -535,7 +753,7 @@ __global__ void __launch_bounds__(256) k_amr_reflux(AmrArgs a, const int* __rest
     cj = y;
     ck = side ? a.bp - 1 : 0;
   }
-  const int gi = key[1] * a.br + ci, gj = key[2] * a.bt + cj;
+  const int gi = D.bi * a.br + ci, gj = D.bj * a.bt + cj;
   const Metric<double>& m = L.m;
   const Metric<double>& mf = a.lv[l + 1].m;
   // coarse face area, and the fine faces (2 x 2) of the finer leaves
@@ -549,13 +767,13 @@ __global__ void __launch_bounds__(256) k_amr_reflux(AmrArgs a, const int* __rest
   const double V = vol_nophi(a, l, gi, gj) * L.dph;
   const int face = 2 * d + side, fface = 2 * d + (1 - side);
   const double dt = a.clock->dt * (stage == 1 ? 1.0 : 0.5);
-  double* tgt = stage == 1 ? a.U1 : a.U;
-  const int gk = key[3] * a.bp + ck;
+  const int gk = D.bk * a.bp + ck;
   // the 2 x 2 fine faces: slot, face cell and area (s = 2 s2 + s1)
   const AmrLevel& LF = a.lv[l + 1];
   int fsl[4], fqf[4];
   double Af[4];
   bool ok = true;
+#pragma unroll
   for (int s = 0; s < 4; ++s) {
     const int s2 = s >> 1, s1 = s & 1;
     // fine cell indices (global, level l+1) on the fine side of the face
@@ -573,44 +791,39 @@ __global__ void __launch_bounds__(256) k_amr_reflux(AmrArgs a, const int* __rest
       fi += s1;
       fj += s2;
     }
-    if (d == 2) fk = (fk + LF.np) % LF.np;
-    const int fs = amr_slot(a, l + 1, fi, fj, fk);
-    fsl[s] = fs;
-    fqf[s] = 0;
-    Af[s] = 0.0;
-    if (fs < 0) {  // cannot happen in a valid tree: poison the cell
-      ok = false;
-      continue;
-    }
-    const int* fkey = a.key + 4 * fs;
-    const int li = fi - fkey[1] * a.br, lj = fj - fkey[2] * a.bt, lk = fk - fkey[3] * a.bp;
+    if (d == 2) fk = fk < 0 ? fk + LF.np : (fk >= LF.np ? fk - LF.np : fk);
+    fsl[s] = amr_slot(a, l + 1, fi, fj, fk);
+    if (fsl[s] < 0) ok = false;  // cannot happen in a valid tree: poison the cell
+    const int li = fi % a.br, lj = fj % a.bt, lk = fk % a.bp;
     if (d == 0) {
       fqf[s] = lk * a.bt + lj;
-      Af[s] = (side ? mf.rm2[fi] : mf.rp2[fi]) / mf.ict[fj] * LF.dph;
+      Af[s] = (side ? mf.rm2[fi] : mf.rp2[fi]) * rcp_fast(mf.ict[fj]) * LF.dph;
     } else if (d == 1) {
       fqf[s] = lk * a.br + li;
-      Af[s] = (side ? mf.sm[fj] : mf.sp[fj]) * mf.hr[fi] / mf.ivr[fi] * LF.dph;
+      Af[s] = (side ? mf.sm[fj] : mf.sp[fj]) * mf.hr[fi] * rcp_fast(mf.ivr[fi]) * LF.dph;
     } else {
       fqf[s] = lj * a.br + li;
-      Af[s] = mf.hr[fi] / mf.ivr[fi] * LF.dth;
+      Af[s] = mf.hr[fi] * rcp_fast(mf.ivr[fi]) * LF.dth;
     }
   }
+  const double iV = rcp_fast(V);
+#pragma unroll
   for (int v = 0; v < NA; ++v) {
     double sumf = 0.0;
+#pragma unroll
     for (int s = 0; s < 4; ++s)
-      if (fsl[s] >= 0) sumf += Af[s] * a.F[fidx(a, fsl[s], fface, v, fqf[s])];
+      if (fsl[s] >= 0) sumf = fma_(Af[s], a.F[fidx(a, fsl[s], fface, v, fqf[s])], sumf);
     if (!ok) sumf = __builtin_nan("");
     const double delta = sumf - Ac * a.F[fidx(a, slot, face, v, fq)];
-    const double dL = (side ? -delta : delta) / V;
-    tgt[pidx(a, slot, v, AG + ck, AG + cj, AG + ci)] += dt * dL;
+    dU[v] = dt * ((side ? -delta : delta) * iV);
   }
+  return pidx(a, slot, 0, AG + ck, AG + cj, AG + ci);
 }
 
 // ------------------------------------------------------------------- CFL --
-__global__ void __launch_bounds__(256) k_amr_cfl(AmrArgs a, const int* __restrict__ list) {
-  const int slot = list[blockIdx.x];
-  const int* key = a.key + 4 * slot;
-  const int l = key[0];
+__global__ void __launch_bounds__(256) k_amr_cfl(AmrArgs a, const LeafDesc* __restrict__ list) {
+  const LeafDesc& D = list[blockIdx.x];
+  const int slot = D.slot, l = D.l;
   const Metric<double>& m = a.lv[l].m;
   double lam = 0.0;
   int bad = BAD_NONE;
@@ -619,9 +832,9 @@ __global__ void __launch_bounds__(256) k_amr_cfl(AmrArgs a, const int* __restric
     const int ci = c % a.br, cj = (c / a.br) % a.bt, ck = c / (a.br * a.bt);
     double u[NV], w[NV];
     for (int v = 0; v < NV; ++v) u[v] = a.U[pidx(a, slot, v, AG + ck, AG + cj, AG + ci)];
-    cons2prim<double>(u, w, a.gm1);
-    const int gi = key[1] * a.br + ci, gj = key[2] * a.bt + cj;
-    const double rate = cell_rate<double>(w, m, gi, gj, a.gam);
+    cons2prim<double, true>(u, w, a.gm1);
+    const int gi = D.bi * a.br + ci, gj = D.bj * a.bt + cj;
+    const double rate = cell_rate<double, true>(w, m, gi, gj, a.gam);
     lam = fmax(lam, rate);
     if (bad == BAD_NONE && !cell_valid<double>(u, w)) bad = slot * ncell + c;
   }
@@ -630,19 +843,19 @@ __global__ void __launch_bounds__(256) k_amr_cfl(AmrArgs a, const int* __restric
 
 // ------------------------------------------------------------ indicators --
 // Per listed leaf: max tau and max of -div(V) r / (2 |v_r|) (ghosts filled).
-__global__ void __launch_bounds__(256) k_amr_indicators(AmrArgs a, const int* __restrict__ list,
+__global__ void __launch_bounds__(256) k_amr_indicators(AmrArgs a,
+                                                        const LeafDesc* __restrict__ list,
                                                         double* __restrict__ out) {
   __shared__ double sh[2][4];
-  const int slot = list[blockIdx.x];
-  const int* key = a.key + 4 * slot;
-  const int l = key[0];
+  const LeafDesc& D = list[blockIdx.x];
+  const int slot = D.slot, l = D.l;
   const Metric<double>& m = a.lv[l].m;
   double tmax = -1e300, cmax = -1e300;
   const int ncell = a.br * a.bt * a.bp;
   for (int c = threadIdx.x; c < ncell; c += blockDim.x) {
     const int ci = c % a.br, cj = (c / a.br) % a.bt, ck = c / (a.br * a.bt);
     const int ii = AG + ci, jj = AG + cj, kk = AG + ck;
-    const int gi = key[1] * a.br + ci, gj = key[2] * a.bt + cj;
+    const int gi = D.bi * a.br + ci, gj = D.bj * a.bt + cj;
     auto vel = [&](int k2, int j2, int i2, int comp) {
       return a.U[pidx(a, slot, comp, k2, j2, i2)] / a.U[pidx(a, slot, 0, k2, j2, i2)];
     };
@@ -693,16 +906,14 @@ __global__ void __launch_bounds__(256) k_amr_prolong(AmrArgs a, const int* __res
     const int fi = ck[1] * a.br + ci, fj = ck[2] * a.bt + cj, fk = ck[3] * a.bp + cq;
     const int gi = fi >> 1, gj = fj >> 1, gk = fk >> 1;
     const int ii = AG + gi - pk[1] * a.br, jj = AG + gj - pk[2] * a.bt, kk = AG + gk - pk[3] * a.bp;
-    const int sub = ((fk - 2 * gk) << 2) | ((fj - 2 * gj) << 1) | (fi - 2 * gi);
-    for (int v = 0; v < NA; ++v) {
-      const double c0 = a.U[pidx(a, ps, v, kk, jj, ii)];
-      const double n[6] = {a.U[pidx(a, ps, v, kk, jj, ii - 1)], a.U[pidx(a, ps, v, kk, jj, ii + 1)],
-                           a.U[pidx(a, ps, v, kk, jj - 1, ii)], a.U[pidx(a, ps, v, kk, jj + 1, ii)],
-                           a.U[pidx(a, ps, v, kk - 1, jj, ii)], a.U[pidx(a, ps, v, kk + 1, jj, ii)]};
-      double ch[8];
-      prolong8(a, l, gi, gj, c0, n, ch);
-      a.U[pidx(a, cs, v, AG + cq, AG + cj, AG + ci)] = ch[sub];
-    }
+    const Prolong p = prolong_coef(a, l, gi, gj,
+                                   ((fk & 1) << 2) | ((fj & 1) << 1) | (fi & 1));
+    const double* c0 = a.U + pidx(a, ps, 0, kk, jj, ii);
+    double t[NA];
+#pragma unroll
+    for (int v = 0; v < NA; ++v) t[v] = prolong1(c0 + v * a.bvol, a.pr, a.pr * a.pt, p);
+#pragma unroll
+    for (int v = 0; v < NA; ++v) a.U[pidx(a, cs, v, AG + cq, AG + cj, AG + ci)] = t[v];
   }
 }
 
@@ -737,16 +948,16 @@ __global__ void __launch_bounds__(256) k_amr_restrict(AmrArgs a, const int* __re
 }
 
 // Level-1 leaves from the radial expansion of the first map (Sect. 2.1).
-__global__ void __launch_bounds__(256) k_amr_init(AmrArgs a, const int* __restrict__ list,
+__global__ void __launch_bounds__(256) k_amr_init(AmrArgs a, const LeafDesc* __restrict__ list,
                                                   double gam) {
-  const int slot = list[blockIdx.x];
-  const int* key = a.key + 4 * slot;
+  const LeafDesc& D = list[blockIdx.x];
+  const int slot = D.slot;
   const AmrLevel& L = a.lv[1];
   const long long plane = (long long)a.bnd.nt * a.bnd.np;
   const int ncell = a.br * a.bt * a.bp;
   for (int c = threadIdx.x; c < ncell; c += blockDim.x) {
     const int ci = c % a.br, cj = (c / a.br) % a.bt, cq = c / (a.br * a.bt);
-    const int i = key[1] * a.br + ci, j = key[2] * a.bt + cj, k = key[3] * a.bp + cq;
+    const int i = D.bi * a.br + ci, j = D.bj * a.bt + cj, k = D.bk * a.bp + cq;
     const double rc = L.m.rc[i];
     const double x = a.r_in / rc;
     const double sth = sin(L.m64[OFF_TC64(L.nr, L.nt) + j]);
@@ -815,8 +1026,8 @@ int err(int code, const std::string& m) { return set_error(code, m.c_str()); }
   } while (0)
 
 struct AmrLayout {
-  size_t U, U1, F, leaf, key, maps[AMR_MAXL + 1], m64[AMR_MAXL + 1], mr[AMR_MAXL + 1],
-      bmaps, tau, cme, clock, partials, ind, lists, rlist, stage, total;
+  size_t U, U1, F, leaf, key, lv, maps[AMR_MAXL + 1], m64[AMR_MAXL + 1], mr[AMR_MAXL + 1],
+      bmaps, tau, cme, clock, partials, ind, lists, leaves, rlist, glist, total;
 };
 
 }  // namespace
@@ -845,17 +1056,14 @@ struct icr_amr {
 
   char* at(size_t off) { return ws + off; }
   DevClock* clock() { return (DevClock*)at(L.clock); }
+  double* pin = nullptr;  // pinned host buffer of one leaf, written by the device
 
-  AmrArgs args() {
-    AmrArgs a;
-    std::memset(&a, 0, sizeof a);
-    a.U = (double*)at(L.U);
-    a.U1 = (double*)at(L.U1);
-    a.F = (double*)at(L.F);
-    a.leaf = (const unsigned char*)at(L.leaf);
-    a.key = (const int*)at(L.key);
+  // the level table on the device (constant after creation)
+  int upload_levels() {
+    std::vector<AmrLevel> t(AMR_MAXL + 1);
+    std::memset(t.data(), 0, t.size() * sizeof(AmrLevel));
     for (int l = 1; l <= nlev; ++l) {
-      AmrLevel& v = a.lv[l];
+      AmrLevel& v = t[l];
       v.nr = nb[l][0] * q.block_r;
       v.nt = nb[l][1] * q.block_theta;
       v.np = nb[l][2] * q.block_phi;
@@ -868,6 +1076,21 @@ struct icr_amr {
       v.m64 = (const double*)at(L.m64[l]);
       v.map = (const int*)at(L.maps[l]);
     }
+    AMR_TRY(hipMemcpyAsync(at(L.lv), t.data(), t.size() * sizeof(AmrLevel), hipMemcpyHostToDevice,
+                           stream));
+    AMR_TRY(hipStreamSynchronize(stream));
+    return ICR_OK;
+  }
+
+  AmrArgs args() {
+    AmrArgs a;
+    std::memset(&a, 0, sizeof a);
+    a.U = (double*)at(L.U);
+    a.U1 = (double*)at(L.U1);
+    a.F = (double*)at(L.F);
+    a.leaf = (const unsigned char*)at(L.leaf);
+    a.key = (const int*)at(L.key);
+    a.lv = (const AmrLevel*)at(L.lv);
     a.nlev = nlev;
     a.br = q.block_r;
     a.bt = q.block_theta;
@@ -981,53 +1204,77 @@ struct icr_amr {
     return ICR_OK;
   }
 
-  // device lists of slots: the leaves (all, and per level) are rebuilt after
-  // every change of the tree; temporary lists go after them
-  int n_all = 0, lvl_off[AMR_MAXL + 1] = {}, lvl_n[AMR_MAXL + 1] = {};
-  int* list_at(size_t at_int) { return (int*)at(L.lists) + at_int; }
+  // device lists: the leaves, their ghost faces and the flux-corrected ones,
+  // rebuilt after every change of the tree
+  int n_all = 0, n_rl = 0;
+  // ghost faces inside a step (0) and of a regrid (1): [0] without
+  // prolongation, [l] prolonged to level l
+  int g_off[2][AMR_MAXL + 2] = {};
+  const LeafDesc* leaf_list() { return (const LeafDesc*)at(L.leaves); }
   int* upload_temp(const std::vector<int>& v) {
-    int* d = list_at(2 * (size_t)q.max_blocks);
+    int* d = (int*)at(L.lists);
     if (!v.empty())
       (void)hipMemcpy(d, v.data(), v.size() * sizeof(int), hipMemcpyHostToDevice);
     return d;
   }
   int rebuild_lists() {
-    std::vector<int> all = slots(leaves());
-    n_all = (int)all.size();
-    std::vector<int> per;
-    for (int l = 1; l <= nlev; ++l) {
-      std::vector<int> s = slots(leaves(l));
-      lvl_off[l] = (int)per.size();
-      lvl_n[l] = (int)s.size();
-      per.insert(per.end(), s.begin(), s.end());
-    }
-    if (!all.empty())
-      AMR_TRY(hipMemcpy(list_at(0), all.data(), all.size() * sizeof(int), hipMemcpyHostToDevice));
-    if (!per.empty())
-      AMR_TRY(hipMemcpy(list_at(q.max_blocks), per.data(), per.size() * sizeof(int),
-                        hipMemcpyHostToDevice));
-    // faces of leaves below the top level whose same-level neighbour is
-    // refined (its children there are leaves, by the one-level rule)
-    for (int d = 0; d < 3; ++d) {
-      std::vector<int> e;
-      for (const int sl : all) {
-        const Key& k = key_of[sl];
-        if (k.l >= nlev) continue;
-        for (int side = 0; side < 2; ++side) {
-          Key nk;
-          if (!neighbour(k, d, side, &nk)) continue;
+    const std::vector<Key> lv = leaves();
+    std::vector<LeafDesc> all, rl;
+    std::vector<FaceDesc> gl[2][AMR_MAXL + 1];
+    all.reserve(lv.size());
+    const bool reads_neighbours = lds_stage();
+    for (const Key& k : lv) {
+      LeafDesc D{slot(k), k.l, k.i, k.j, k.k, 0, 0, {}};
+      FaceDesc fd[6];
+      for (int f = 0; f < 6; ++f) {
+        const int d = f >> 1, side = f & 1;
+        Key nk;
+        fd[f] = FaceDesc{D.slot, f, FACE_EDGE, -1, k.l, k.i, k.j, k.k};
+        D.src[f] = LEAF_SELF;
+        if (neighbour(k, d, side, &nk)) {
           const int ns = slot(nk);
-          if (ns >= 0 && !leaf[ns]) e.push_back(2 * sl + side);
+          fd[f].ns = ns;
+          fd[f].kind = ns < 0 ? FACE_COARSE : (leaf[ns] ? FACE_COPY : FACE_FINE);
+          D.src[f] = fd[f].kind == FACE_COPY ? LEAF_COPY | ns << 2 : LEAF_POOL;
+          if (fd[f].kind != FACE_COPY) D.other |= 1 << f;
+          // refined neighbours' children are leaves, by the one-level rule
+          if (fd[f].kind == FACE_FINE) D.finer |= 1 << f;
+        } else if (f == 0) {
+          fd[f].kind = FACE_INNER;
+          D.src[f] = LEAF_POOL;
         }
       }
-      n_rl[d] = (int)e.size();
-      if (!e.empty())
-        AMR_TRY(hipMemcpy(rlist_at(d), e.data(), e.size() * sizeof(int), hipMemcpyHostToDevice));
+      all.push_back(D);
+      if (D.finer) rl.push_back(D);
+      // the stage kernel takes copies and edges from their source; in the
+      // padded block they are needed where a finer leaf interpolates from it
+      const bool whole = D.finer || !reads_neighbours;
+      for (int f = 0; f < 6; ++f) {
+        const int to = fd[f].kind == FACE_COARSE ? k.l : 0;
+        if (whole || (fd[f].kind != FACE_COPY && fd[f].kind != FACE_EDGE))
+          gl[0][to].push_back(fd[f]);
+        gl[1][to].push_back(fd[f]);
+      }
     }
+    n_all = (int)all.size();
+    n_rl = (int)rl.size();
+    std::vector<FaceDesc> g;
+    for (int w = 0; w < 2; ++w)
+      for (int l = 0; l <= nlev; ++l) {
+        g_off[w][l] = (int)g.size();
+        g.insert(g.end(), gl[w][l].begin(), gl[w][l].end());
+        g_off[w][l + 1] = (int)g.size();
+      }
+    AMR_TRY(hipMemcpyAsync(at(L.leaves), all.data(), all.size() * sizeof(LeafDesc),
+                           hipMemcpyHostToDevice, stream));
+    AMR_TRY(hipMemcpyAsync(at(L.glist), g.data(), g.size() * sizeof(FaceDesc),
+                           hipMemcpyHostToDevice, stream));
+    if (!rl.empty())
+      AMR_TRY(hipMemcpyAsync(at(L.rlist), rl.data(), rl.size() * sizeof(LeafDesc),
+                             hipMemcpyHostToDevice, stream));
+    AMR_TRY(hipStreamSynchronize(stream));
     return ICR_OK;
   }
-  int n_rl[3] = {0, 0, 0};
-  int* rlist_at(int d) { return (int*)at(L.rlist) + (size_t)d * 2 * q.max_blocks; }
 
   std::vector<int> slots(const std::vector<Key>& ks) const {
     std::vector<int> s;
@@ -1035,18 +1282,27 @@ struct icr_amr {
     return s;
   }
 
-  template <int FLUX, int LIM>
-  void launch_stage_t(const AmrArgs& a, int* d, int n, int stage) {
+  // block size and LDS of the face-once stage kernel: 0 (the leaf does not
+  // fit it), 256 or 512 threads
+  int lds_stage() const {
     const int br = q.block_r, bt = q.block_theta, bp = q.block_phi;
-    const int nf = std::max((br + 1) * bt * bp, std::max(br * (bt + 1) * bp, br * bt * (bp + 1)));
-    const size_t lds = sizeof(double) * NA * (size_t)nf;
-    if (br * bt * bp <= AMR_FO_CELLS && lds <= 48 * 1024)
-      hipLaunchKernelGGL((k_amr_stage_fo<FLUX, LIM>), dim3(n), dim3(256), lds, stream, a, d,
-                         stage);
+    const int lds = amr_lds_bytes(br, bt, bp);
+    if (lds <= AMR_LDS_S && amr_covers(256, br, bt, bp)) return 256;
+    return lds <= AMR_LDS_L && amr_covers(512, br, bt, bp) ? 512 : 0;
+  }
+  template <int FLUX, int LIM>
+  void launch_stage_t(const AmrArgs& a, const LeafDesc* d, int n, int stage) {
+    const int nt = lds_stage();
+    if (nt == 256)
+      hipLaunchKernelGGL((k_amr_stage_lds<FLUX, LIM, 256, AMR_LDS_S>), dim3(n), dim3(256), 0,
+                         stream, a, d, stage);
+    else if (nt == 512)
+      hipLaunchKernelGGL((k_amr_stage_lds<FLUX, LIM, 512, AMR_LDS_L>), dim3(n), dim3(512), 0,
+                         stream, a, d, stage);
     else
       hipLaunchKernelGGL((k_amr_stage<FLUX, LIM>), dim3(n), dim3(256), 0, stream, a, d, stage);
   }
-  void launch_stage(const AmrArgs& a, int* d, int n, int stage) {
+  void launch_stage(const AmrArgs& a, const LeafDesc* d, int n, int stage) {
     const int f = p.flux, lm = p.limiter;
     if (f == ICR_FLUX_TVDLF && lm == ICR_LIM_MINMOD) launch_stage_t<FLUX_TVDLF, LIM_MINMOD>(a, d, n, stage);
     else if (f == ICR_FLUX_TVDLF) launch_stage_t<FLUX_TVDLF, LIM_MC>(a, d, n, stage);
@@ -1059,20 +1315,14 @@ struct icr_amr {
   // stage right-hand sides, updates and flux corrections; CFL of the result
   void enqueue_step() {
     const size_t nl = (size_t)n_all;
-    int* d_all = list_at(0);
-    const long long area[3] = {(long long)q.block_phi * q.block_theta,
-                               (long long)q.block_phi * q.block_r,
-                               (long long)q.block_theta * q.block_r};
+    const LeafDesc* d_all = leaf_list();
     for (int stage = 1; stage <= 2; ++stage) {
       fill_ghosts_at(stage == 2, stage == 2, 0);
       AmrArgs a = args();
       launch_stage(a, d_all, (int)nl, stage);
-      for (int d = 0; d < 3; ++d) {
-        if (n_rl[d] == 0) continue;
-        const long long n = area[d] * (long long)n_rl[d];
-        hipLaunchKernelGGL(k_amr_reflux, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
-                           a, rlist_at(d), n_rl[d], stage, d);
-      }
+      if (n_rl > 0)
+        hipLaunchKernelGGL(k_amr_reflux, dim3((unsigned)n_rl), dim3(128), 0, stream, a,
+                           (const LeafDesc*)at(L.rlist), stage);
     }
     AmrArgs a = args();
     hipLaunchKernelGGL(k_amr_cfl, dim3((unsigned)nl), dim3(256), 0, stream, a, d_all);
@@ -1084,19 +1334,18 @@ struct icr_amr {
 
   void fill_ghosts_at(int use_u1, int plus_dt, int always) {
     AmrArgs a = args();
-    for (int l = 1; l <= nlev; ++l) {
-      if (lvl_n[l] == 0) continue;
-      int* d = list_at((size_t)q.max_blocks + lvl_off[l]);
-      const long long per = 4LL * (q.block_phi * q.block_theta + q.block_phi * q.block_r +
-                                   q.block_theta * q.block_r);
-      const long long n = per * (long long)lvl_n[l];
-      hipLaunchKernelGGL(k_amr_ghost, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, a,
-                         l, d, lvl_n[l], use_u1, plus_dt, always);
+    // the faces without a coarser neighbour first, then the prolonged ones
+    // level by level (their source leaves' ghosts are then complete)
+    for (int l = 0; l <= nlev; ++l) {
+      const int *off = g_off[always ? 1 : 0], n = off[l + 1] - off[l];
+      if (n == 0) continue;
+      hipLaunchKernelGGL(k_amr_ghost, dim3((unsigned)n), dim3(256), 0, stream, a,
+                         (const FaceDesc*)at(L.glist) + off[l], use_u1, plus_dt, always);
     }
   }
 
   int first_dt() {
-    int* d_all = list_at(0);
+    const LeafDesc* d_all = leaf_list();
     AmrArgs a = args();
     hipLaunchKernelGGL(k_amr_cfl, dim3((unsigned)n_all), dim3(256), 0, stream, a, d_all);
     ProbeArgs pa;
@@ -1190,7 +1439,7 @@ struct icr_amr {
     AmrArgs a = args();
     double* ind = (double*)at(L.ind);
     hipLaunchKernelGGL(k_amr_indicators, dim3((unsigned)n_all), dim3(256), 0, stream, a,
-                       list_at(0), ind);
+                       leaf_list(), ind);
     std::vector<double> h(2 * lv.size());
     AMR_TRY(hipMemcpyAsync(h.data(), ind, h.size() * sizeof(double), hipMemcpyDeviceToHost,
                            stream));
@@ -1280,6 +1529,7 @@ AmrLayout amr_layout(const icr_grid& g, const icr_amr_params& q) {
   L.F = take(sizeof(double) * 6 * NA * (size_t)fmax * mb);
   L.leaf = take(mb);
   L.key = take(sizeof(int) * 4 * mb);
+  L.lv = take(sizeof(AmrLevel) * (AMR_MAXL + 1));
   for (int l = 1; l <= q.max_level; ++l) {
     const long long f = 1LL << (l - 1);
     const long long nr = g.n_r * f, nt = g.n_theta * f, np = g.n_phi * f;
@@ -1294,12 +1544,12 @@ AmrLayout amr_layout(const icr_grid& g, const icr_amr_params& q) {
   L.clock = take(sizeof(DevClock));
   L.partials = take(sizeof(double) * 4 * mb);
   L.ind = take(sizeof(double) * 2 * mb);
-  // device lists: all leaves [mb], per-level leaves [mb], temporary [4 mb]
-  L.lists = take(sizeof(int) * 6 * mb);
-  // flux-correction lists: per direction, (slot, side) of the coarse leaf
-  // faces next to finer leaves [2 mb] each
-  L.rlist = take(sizeof(int) * 6 * mb);
-  L.stage = take(sizeof(double) * NA * (size_t)q.block_r * q.block_theta * q.block_phi);
+  // temporary slot lists of a regrid [4 mb]; the leaves; those next to finer
+  // leaves; the faces to fill inside a step, then those of a regrid
+  L.lists = take(sizeof(int) * 4 * mb);
+  L.leaves = take(sizeof(LeafDesc) * mb);
+  L.rlist = take(sizeof(LeafDesc) * mb);
+  L.glist = take(sizeof(FaceDesc) * 12 * mb);
   L.total = off;
   return L;
 }
@@ -1381,8 +1631,15 @@ int icr_amr_create(const icr_grid* g, const icr_phys* p, const icr_amr_params* q
   c.t_end = -1.0;
   c.last_sample = -1;
   rc = a->write_clock(&c);
+  if (!rc) rc = a->upload_levels();
   if (!rc) rc = a->upload_tree();
   if (!rc) rc = a->rebuild_lists();
+  if (!rc) {
+    const size_t bytes = sizeof(double) * NA * (size_t)q->block_r * q->block_theta * q->block_phi;
+    const hipError_t e = hipHostMalloc((void**)&a->pin, bytes, hipHostMallocDefault);
+    if (e != hipSuccess)
+      rc = err(ICR_ERR_HIP, std::string("hipHostMalloc failed: ") + hipGetErrorString(e));
+  }
   if (rc) {
     delete a;
     return rc;
@@ -1394,6 +1651,7 @@ int icr_amr_create(const icr_grid* g, const icr_phys* p, const icr_amr_params* q
 void icr_amr_destroy(icr_amr* a) {
   if (!a) return;
   (void)hipStreamSynchronize(a->stream);
+  (void)hipHostFree(a->pin);
   delete a;
 }
 
@@ -1468,7 +1726,7 @@ int icr_amr_init_radial(icr_amr* a) {
   if (rc) return rc;
   AmrArgs args = a->args();
   hipLaunchKernelGGL(k_amr_init, dim3((unsigned)a->n_all), dim3(256), 0, a->stream, args,
-                     a->list_at(0), a->p.gamma);
+                     a->leaf_list(), a->p.gamma);
   AMR_TRY(hipGetLastError());
   DevClock c;
   rc = a->read_clock(&c);
@@ -1552,12 +1810,13 @@ int icr_amr_get_block(icr_amr* a, const int* key, double* out) {
   const Key k{key[0], key[1], key[2], key[3]};
   if (!a->is_leaf(k)) return err(ICR_ERR_ARG, "no such leaf");
   const int ncell = a->q.block_r * a->q.block_theta * a->q.block_phi;
-  double* st = (double*)a->at(a->L.stage);
+  // the kernel writes the pinned buffer itself: a device-to-host copy of one
+  // leaf into pageable memory cost more than the rest of the call (27 us)
   AmrArgs args = a->args();
-  hipLaunchKernelGGL(k_amr_copy_out, dim3(16), dim3(256), 0, a->stream, args, a->slot_of.at(k),
-                     st);
-  AMR_TRY(hipMemcpyAsync(out, st, sizeof(double) * NA * ncell, hipMemcpyDeviceToHost, a->stream));
+  hipLaunchKernelGGL(k_amr_copy_out, dim3(16), dim3(256), 0, a->stream, args, a->slot(k), a->pin);
+  AMR_TRY(hipGetLastError());
   AMR_TRY(hipStreamSynchronize(a->stream));
+  std::memcpy(out, a->pin, sizeof(double) * NA * ncell);
   return ICR_OK;
 }
 
