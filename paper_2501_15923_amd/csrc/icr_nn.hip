@@ -83,20 +83,38 @@ struct ConvRow {  // one row of the neighbourhood matrix
 };
 __device__ __forceinline__ ConvRow conv_row(const Conv& cv, int m) {
   ConvRow r;
-  r.k = m % cv.np;
   const int q = m / cv.np;
-  r.j = q % cv.nt;
+  r.k = m - q * cv.np;
   r.b = q / cv.nt;
+  r.j = q - r.b * cv.nt;
   return r;
 }
-// element offset of channel 0 of the row's neighbour at `tap`
-__device__ __forceinline__ long long conv_at(const Conv& cv, const ConvRow& r, int tap) {
-  const int d = tap / cv.nk;
-  int j = r.j + d - 1, k = r.k + tap - d * cv.nk + cv.dk0;
+__device__ __forceinline__ void conv_next(const Conv& cv, ConvRow& r) {  // row m + 1
+  if (++r.k == cv.np) {
+    r.k = 0;
+    if (++r.j == cv.nt) {
+      r.j = 0;
+      ++r.b;
+    }
+  }
+}
+struct ConvCol {  // one column: neighbour offsets and channel
+  int dj, dk, c;
+};
+__device__ __forceinline__ ConvCol conv_col(const Conv& cv, int col) {
+  const int tap = col / cv.C, d = tap / cv.nk;
+  return ConvCol{d - 1, tap - d * cv.nk + cv.dk0, col - tap * cv.C};
+}
+__device__ __forceinline__ long long conv_at(const Conv& cv, const ConvRow& r, const ConvCol& q) {
+  int j = r.j + q.dj, k = r.k + q.dk;
   j = j < 0 ? 0 : (j >= cv.nt ? cv.nt - 1 : j);
   k = k < 0 ? k + cv.np : (k >= cv.np ? k - cv.np : k);  // |dk| < np
-  return ((long long)(r.b * cv.nt + j) * cv.np + k) * cv.C;
+  return ((long long)(r.b * cv.nt + j) * cv.np + k) * cv.C + q.c;
 }
+// How eight columns of the neighbourhood matrix are read: 16 bytes at once
+// where 8 channels never straddle two taps, else by channel pairs (even C),
+// else one by one.
+enum { CONV_NONE, CONV_VEC, CONV_PAIR, CONV_ONE };
 
 // 8 consecutive elements (r, c .. c+7) of a matrix with rows of ld elements,
 // zero outside R x C.
@@ -112,112 +130,116 @@ __device__ __forceinline__ uint4 fetch8(const Operand& o, int r, int c, int R, i
   return q;
 }
 
-// The same of the neighbourhood matrix: 16 bytes at once where 8 channels
-// never straddle two taps, else by channel pairs (even C), else one by one.
-__device__ __forceinline__ uint4 fetch8_conv(const Operand& o, const ConvRow& row, int c, int K) {
+// The same of the neighbourhood matrix: columns c .. c+7 of K, whose offsets
+// (for every first, second or single column, by CM) are in `col`.
+template <int CM, int NC>
+__device__ __forceinline__ uint4 fetch8_conv(const Operand& o, const ConvRow& row,
+                                             const ConvCol (&col)[NC], int c, int K) {
   uint4 q = make_uint4(0, 0, 0, 0);
   if (c >= K) return q;
-  const Conv& cv = o.cv;
-  if (o.vec) {
-    const int tap = c / cv.C;
-    return *reinterpret_cast<const uint4*>(o.p + conv_at(cv, row, tap) + (c - tap * cv.C));
-  }
-  uint16_t v[8];
-  if ((cv.C & 1) == 0) {
-#pragma unroll
-    for (int i = 0; i < 8; i += 2) {
-      uint32_t w = 0;
-      if (c + i < K) {
-        const int tap = (c + i) / cv.C;
-        w = *reinterpret_cast<const uint32_t*>(o.p + conv_at(cv, row, tap) +
-                                               (c + i - tap * cv.C));
-      }
-      memcpy(v + i, &w, 4);
-    }
+  if constexpr (CM == CONV_VEC) {
+    q = *reinterpret_cast<const uint4*>(o.p + conv_at(o.cv, row, col[0]));
   } else {
+    constexpr int W = 8 / NC;
+    uint16_t v[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      v[i] = 0;
-      if (c + i < K) {
-        const int tap = (c + i) / cv.C;
-        v[i] = o.p[conv_at(cv, row, tap) + (c + i - tap * cv.C)];
+    for (int i = 0; i < NC; ++i) {
+      uint32_t w = 0;
+      if (c + W * i < K) {
+        const uint16_t* g = o.p + conv_at(o.cv, row, col[i]);
+        if (W == 2) w = *reinterpret_cast<const uint32_t*>(g); else w = *g;
       }
+      memcpy(v + W * i, &w, 2 * W);
     }
+    memcpy(&q, v, 16);
   }
-  memcpy(&q, v, 16);
   return q;
 }
 
-// One operand's k-tile, T rows x 64 k: T / 32 16-byte pieces per thread.
+// One operand's k-tile, T rows x 64 k, in registers.
 // KR = 0: stored k-contiguous; piece q is chunk tid % 8 of row tid / 8 + 32 q.
-// KR = 1: stored row-contiguous; a 4 (k) x 8 (row) patch per 4 pieces.
-template <int T, int KR, int CONV>
+// KR = 1: stored row-contiguous; a 4 (k) x 8 (row) patch, 8 k-groups and 8
+// row-groups per wave (64 rows: two waves hold all the patches).
+template <int T, int KR>
+struct Piece {
+  uint4 v[KR ? 4 : T / 32];
+};
+// A convolution's rows and columns that a thread keeps for the whole product:
+// its rows (KR = 0) or its columns (KR = 1); the other index moves with k.
+template <int T, int KR, int CM>
 struct Tile {
-  static constexpr int NP = T / 32;
-  uint4 v[NP];
-  ConvRow row[CONV && !KR ? NP : 1];
+  static constexpr int NP = KR ? 4 : T / 32;
+  static constexpr int NC = CM == CONV_PAIR ? 4 : (CM == CONV_ONE ? 8 : 1);
+  ConvRow row[CM && !KR ? NP : 1];
+  ConvCol col[CM && KR ? NC : 1];
+
+  __device__ __forceinline__ static int patch_k() {
+    return 4 * ((threadIdx.x & 7) + 8 * ((threadIdx.x >> 6) & 1));
+  }
+  __device__ __forceinline__ static int patch_r() {
+    return 8 * (((threadIdx.x & 63) >> 3) + 8 * (threadIdx.x >> 7));
+  }
+  __device__ __forceinline__ static bool idle() { return KR && T < 128 && threadIdx.x >= 128; }
 
   __device__ __forceinline__ void init(const Operand& o, int r0, int R) {
-    if constexpr (CONV && !KR)
+    if constexpr (CM && !KR) {
 #pragma unroll
       for (int q = 0; q < NP; ++q) {
         const int r = r0 + (threadIdx.x >> 3) + 32 * q;
         row[q] = conv_row(o.cv, r < R ? r : R - 1);
       }
-  }
-  // patch of this thread: 8 k-groups and 8 row-groups per wave
-  __device__ __forceinline__ static int patch_k(int w, int l) {
-    return 4 * ((l & 7) + 8 * (w & 1));
-  }
-  __device__ __forceinline__ static int patch_r(int w, int l) {
-    return 8 * ((l >> 3) + 8 * (w >> 1));
+    } else if constexpr (CM) {
+#pragma unroll
+      for (int i = 0; i < NC; ++i) col[i] = conv_col(o.cv, r0 + patch_r() + (8 / NC) * i);
+    }
   }
   // rows r0 .. of R, k0 .. of K
-  __device__ __forceinline__ void load(const Operand& o, int r0, int k0, int R, int K) {
+  __device__ __forceinline__ void load(Piece<T, KR>& p, const Operand& o, int r0, int k0, int R,
+                                       int K) const {
     const int tid = threadIdx.x;
     if constexpr (!KR) {
+      const int k = k0 + (tid & 7) * 8;
+      if constexpr (CM) {
+        ConvCol cc[NC];
 #pragma unroll
-      for (int q = 0; q < NP; ++q) {
-        const int r = r0 + (tid >> 3) + 32 * q, k = k0 + (tid & 7) * 8;
-        if constexpr (CONV)
-          v[q] = r < R ? fetch8_conv(o, row[q], k, K) : make_uint4(0, 0, 0, 0);
-        else
-          v[q] = fetch8(o, r, k, R, K);
+        for (int i = 0; i < NC; ++i) cc[i] = conv_col(o.cv, k + (8 / NC) * i);
+#pragma unroll
+        for (int q = 0; q < NP; ++q)
+          p.v[q] = r0 + (tid >> 3) + 32 * q < R ? fetch8_conv<CM>(o, row[q], cc, k, K)
+                                                : make_uint4(0, 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int q = 0; q < NP; ++q) p.v[q] = fetch8(o, r0 + (tid >> 3) + 32 * q, k, R, K);
       }
     } else {
-      const int w = tid >> 6, l = tid & 63;
-      if (T < 128 && w >= 2) return;  // 64 rows: two waves hold all the patches
-      const int r = r0 + patch_r(w, l), k = k0 + patch_k(w, l);
+      if (idle()) return;
+      const int r = r0 + patch_r(), k = k0 + patch_k();
+      if constexpr (CM) {
+        ConvRow rw = conv_row(o.cv, k);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if constexpr (CONV)
-          set(q, k + q < K && r < R ? fetch8_conv(o, conv_row(o.cv, k + q), r, R)
-                                    : make_uint4(0, 0, 0, 0));
-        else
-          set(q, fetch8(o, k + q, r, K, R));
+        for (int q = 0; q < 4; ++q) {
+          p.v[q] = k + q < K ? fetch8_conv<CM>(o, rw, col, r, R) : make_uint4(0, 0, 0, 0);
+          conv_next(o.cv, rw);
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) p.v[q] = fetch8(o, k + q, r, K, R);
       }
     }
   }
-  uint4 x[KR && T < 128 ? 2 : 1];  // a patch is 4 pieces also where NP is 2
-  __device__ __forceinline__ void set(int q, uint4 a) {
-    if (q < NP) v[q < NP ? q : 0] = a; else x[q >= NP ? (q - NP) % (KR && T < 128 ? 2 : 1) : 0] = a;
-  }
-  __device__ __forceinline__ uint4 get(int q) const {
-    return q < NP ? v[q < NP ? q : 0] : x[q >= NP ? (q - NP) % (KR && T < 128 ? 2 : 1) : 0];
-  }
-  __device__ __forceinline__ void store(uint16_t* s) const {
+  __device__ __forceinline__ static void store(const Piece<T, KR>& p, uint16_t* s) {
     const int tid = threadIdx.x;
     if constexpr (!KR) {
 #pragma unroll
       for (int q = 0; q < NP; ++q)
-        *reinterpret_cast<uint4*>(s + lds_chunk((tid >> 3) + 32 * q, tid & 7)) = v[q];
+        *reinterpret_cast<uint4*>(s + lds_chunk((tid >> 3) + 32 * q, tid & 7)) = p.v[q];
     } else {
-      const int w = tid >> 6, l = tid & 63;
-      if (T < 128 && w >= 2) return;
-      const int r = patch_r(w, l), k = patch_k(w, l);
-      const uint4 p0 = get(0), p1 = get(1), p2 = get(2), p3 = get(3);
-      const uint32_t a0[4] = {p0.x, p0.y, p0.z, p0.w}, a1[4] = {p1.x, p1.y, p1.z, p1.w};
-      const uint32_t a2[4] = {p2.x, p2.y, p2.z, p2.w}, a3[4] = {p3.x, p3.y, p3.z, p3.w};
+      if (idle()) return;
+      const int r = patch_r(), k = patch_k();
+      const uint32_t a0[4] = {p.v[0].x, p.v[0].y, p.v[0].z, p.v[0].w};
+      const uint32_t a1[4] = {p.v[1].x, p.v[1].y, p.v[1].z, p.v[1].w};
+      const uint32_t a2[4] = {p.v[2].x, p.v[2].y, p.v[2].z, p.v[2].w};
+      const uint32_t a3[4] = {p.v[3].x, p.v[3].y, p.v[3].z, p.v[3].w};
 #pragma unroll
       for (int i = 0; i < 8; ++i) {  // row r + i: its four k values
         const uint32_t sel = i & 1 ? 0x07060302u : 0x05040100u;
@@ -291,35 +313,52 @@ __global__ void __launch_bounds__(256) k_gemm(Operand A, Operand B, Epi ep, int 
     for (int b = 0; b < FN; ++b)
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[a][b][q] = 0.f;
+  // PF k-tiles in flight in registers: a small product has few blocks and
+  // little to do per k-tile, so that only the depth hides the load latency
+  // (1800 rows: the first layers' products 19.7 -> 15.7 us).  A second k-tile
+  // of the large shape costs a block per CU and more than it gains (57600 x
+  // 4800 x 384 with the loss: 634 -> 759 us).
+  constexpr int PF = TM == 64 ? 3 : 1;
   Tile<TM, TA, CONV> ta;
-  Tile<TN, !TB, 0> tb;
+  Tile<TN, !TB, CONV_NONE> tb;
+  Piece<TM, TA> pa[PF];
+  Piece<TN, !TB> pb[PF];
   ta.init(A, m0, M);
-  ta.load(A, m0, kbeg, M, K);
-  tb.load(B, n0, kbeg, N, K);
-  for (int k0 = kbeg; k0 < K; k0 += BK) {
-    __syncthreads();  // the previous k-tile has been read
-    ta.store(sA);
-    tb.store(sB);
-    __syncthreads();
-    if (k0 + BK < K) {
-      ta.load(A, m0, k0 + BK, M, K);
-      tb.load(B, n0, k0 + BK, N, K);
+#pragma unroll
+  for (int s = 0; s < PF; ++s)
+    if (kbeg + s * BK < K) {
+      ta.load(pa[s], A, m0, kbeg + s * BK, M, K);
+      tb.load(pb[s], B, n0, kbeg + s * BK, N, K);
     }
+  for (int kg = kbeg; kg < K; kg += PF * BK) {
 #pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      const int ch = 2 * ks + (lane >> 5);
-      bf16x8 fa[FM], fb[FN];
+    for (int s = 0; s < PF; ++s) {
+      const int k0 = kg + s * BK;
+      if (k0 >= K) break;
+      __syncthreads();  // the previous k-tile has been read
+      ta.store(pa[s], sA);
+      tb.store(pb[s], sB);
+      __syncthreads();
+      if (k0 + PF * BK < K) {
+        ta.load(pa[s], A, m0, k0 + PF * BK, M, K);
+        tb.load(pb[s], B, n0, k0 + PF * BK, N, K);
+      }
 #pragma unroll
-      for (int t = 0; t < FM; ++t)
-        memcpy(&fa[t], sA + lds_chunk(wm + t * 32 + (lane & 31), ch), 16);
+      for (int ks = 0; ks < BK / 16; ++ks) {
+        const int ch = 2 * ks + (lane >> 5);
+        bf16x8 fa[FM], fb[FN];
 #pragma unroll
-      for (int t = 0; t < FN; ++t)
-        memcpy(&fb[t], sB + lds_chunk(wn + t * 32 + (lane & 31), ch), 16);
+        for (int t = 0; t < FM; ++t)
+          memcpy(&fa[t], sA + lds_chunk(wm + t * 32 + (lane & 31), ch), 16);
 #pragma unroll
-      for (int a = 0; a < FM; ++a)
+        for (int t = 0; t < FN; ++t)
+          memcpy(&fb[t], sB + lds_chunk(wn + t * 32 + (lane & 31), ch), 16);
 #pragma unroll
-        for (int b = 0; b < FN; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
+        for (int a = 0; a < FM; ++a)
+#pragma unroll
+          for (int b = 0; b < FN; ++b)
+            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
+      }
     }
   }
   // The finished tile goes through LDS, 64 rows at a time, so that each
@@ -469,8 +508,8 @@ Operand conv_operand(const uint16_t* p, const Conv& cv) {
 }
 
 template <int TA, int TB, int CONV, int EP>
-void gemm_launch(const Operand& A, const Operand& B, Epi ep, int M, int N, int K, int splits,
-                 int kchunk, hipStream_t s) {
+void gemm_launch_as(const Operand& A, const Operand& B, Epi ep, int M, int N, int K, int splits,
+                    int kchunk, hipStream_t s) {
   ep.wide = ((((uintptr_t)ep.c | (uintptr_t)ep.t) & 15) | ((uintptr_t)ep.h & 7)) == 0;
   const int t = tile_for(M, N, splits);
   const dim3 grid((unsigned)tiles(t, M, N), splits), blk(256);
@@ -480,6 +519,20 @@ void gemm_launch(const Operand& A, const Operand& B, Epi ep, int M, int N, int K
   else
     hipLaunchKernelGGL((k_gemm<TSMALL, TSMALL, TA, TB, CONV, EP>), grid, blk, 0, s, A, B, ep, M,
                        N, K, kchunk);
+}
+
+// CONV = 1: A is a neighbourhood matrix, read as its channel count allows
+template <int TA, int TB, int CONV, int EP>
+void gemm_launch(const Operand& A, const Operand& B, const Epi& ep, int M, int N, int K,
+                 int splits, int kchunk, hipStream_t s) {
+  if constexpr (!CONV)
+    gemm_launch_as<TA, TB, CONV_NONE, EP>(A, B, ep, M, N, K, splits, kchunk, s);
+  else if (A.vec)
+    gemm_launch_as<TA, TB, CONV_VEC, EP>(A, B, ep, M, N, K, splits, kchunk, s);
+  else if ((A.cv.C & 1) == 0)
+    gemm_launch_as<TA, TB, CONV_PAIR, EP>(A, B, ep, M, N, K, splits, kchunk, s);
+  else
+    gemm_launch_as<TA, TB, CONV_ONE, EP>(A, B, ep, M, N, K, splits, kchunk, s);
 }
 
 template <int TA, int TB, int CONV, int EP>
