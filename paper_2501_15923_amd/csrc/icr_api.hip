@@ -78,6 +78,7 @@ constexpr int GRAPH_STEPS[NGRAPH] = {16, 8, 4, 2, 1};
 // staging region of the workspace in chunks of this many cells (8 doubles
 // each): no call after creation allocates device memory.
 constexpr long long STAGE_CELLS = 65536;
+static_assert(STAGE_CELLS % INIT_CELLS == 0, "chunks hold whole blocks of CFL partials");
 
 size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -169,7 +170,8 @@ Layout make_layout(const icr_grid& g, const icr_phys& p) {
   L.plog = take(sizeof(double) * 12 * (size_t)(g.max_probes > 0 ? g.max_probes : 1) *
                 (size_t)(g.probe_log_rows > 0 ? g.probe_log_rows : 1));
   L.pout = take(sizeof(double) * 12 * (size_t)(g.max_probes > 0 ? g.max_probes : 1));
-  L.clock = take(sizeof(DevClock));
+  // the clock, and its copy as the current step found it
+  L.clock = take(2 * sizeof(DevClock));
   L.partials = take(sizeof(double) * 4 * (size_t)L.max_blocks);
   // staging: the boundary / shell outputs ([8][nt][np] doubles at most) and
   // host-transfer chunks of stage_cells cells x 8 doubles
@@ -280,8 +282,7 @@ struct icr_solver {
   double r_in, omega, gm, dph;
   int tile_r, variant, use_graphs;
   int planes;              // phi planes per stage block, 0: by the rule of choose_planes
-  hipGraphExec_t g_steps[NGRAPH][2];
-  bool graphs_ok;
+  hipGraphExec_t g_steps[NGRAPH][2];  // null until captured
   int dev;                  // HIP device the solver was created on
   double* part_override;    // non-null: stage-2 partials go here (icr_step_noalloc)
 
@@ -405,6 +406,8 @@ struct icr_solver {
     return a;
   }
 
+  // Both stages and the end of a step: in one launch with the next step's
+  // boundary, or (ev set) the clock alone.
   template <typename R>
   void enqueue_stages(int from, int to, hipStream_t st, hipEvent_t* ev) {
     const StageArgs<R> a1 = stage_args<R>(from, from, 2, 0);
@@ -426,18 +429,32 @@ struct icr_solver {
       launch_stage_lds<R>(a2, 2, p.flux, p.limiter, tile_r, pl, st);
     if (trc()) launch_tracer<R>(tracer_args<R>(2, 2, from, to, 1), 2, st);
     if (ev) (void)hipEventRecord(ev[3], st);
-    launch_finalize<R>(clock(), partials(), stage_blocks(), p.cfl, 1, logging() ? 1 : 0,
-                       probe_args(), u(to), (double*)(ws + L.plog), st);
+    if (ev)
+      launch_finalize<R>(clock(), partials(), stage_blocks(), p.cfl, 1, logging() ? 1 : 0,
+                         probe_args(), u(to), (double*)(ws + L.plog), st);
+    else
+      launch_step_end<R>(clock(), partials(), stage_blocks(), p.cfl, logging() ? 1 : 0,
+                         probe_args(), u(to), (double*)(ws + L.plog), bnd(), ghost(0), ghost(1),
+                         tg(0), tg(1), st);
   }
 
-  // One RK2 step from state buffer `from` into `from ^ 1`: boundary driver,
-  // stage 1, stage 2, finalize (clock, dt, probe record).  ev (optional):
-  // 5 events around the four kernels.
+  // Start of a call: clock and first boundary (enqueue_step expects the
+  // boundary of its step and leaves that of the next one).
+  void enqueue_begin(double t_end) {
+    launch_begin(bnd(), clock(), t_end, ghost(0), ghost(1), tg(0), tg(1), f32, stream);
+  }
+
+  // One RK2 step from state buffer `from` into `from ^ 1`: stage 1, stage 2,
+  // end of the step (clock, dt, probe record, next boundary).  ev (timing): 5
+  // events around the boundary driver, the two stages and the finalize
+  // kernel, each launched by itself.
   void enqueue_step(int from, hipStream_t st, hipEvent_t* ev = nullptr) {
     const int to = from ^ 1;
-    if (ev) (void)hipEventRecord(ev[0], st);
-    launch_boundary(bnd(), clock(), ghost(0), ghost(1), tg(0), tg(1), f32, st);
-    if (ev) (void)hipEventRecord(ev[1], st);
+    if (ev) {
+      (void)hipEventRecord(ev[0], st);
+      launch_boundary(bnd(), clock(), ghost(0), ghost(1), tg(0), tg(1), f32, st);
+      (void)hipEventRecord(ev[1], st);
+    }
     if (f32)
       enqueue_stages<float>(from, to, st, ev);
     else
@@ -447,24 +464,27 @@ struct icr_solver {
 
   bool logging() const { return n_probes > 0 && cadence >= 0.0 && g.probe_log_rows > 0; }
 
-  void enqueue_cfl(hipStream_t st) {
-    const dim3 gr(((unsigned)g.n_r + 63) / 64, ((unsigned)g.n_theta + 3) / 4, g.n_phi);
-    const int nb = (int)(gr.x * gr.y * gr.z);
-    const double* part = partials();
-    if (f32) {
-      launch_cfl<float>(stage_args<float>(cur, cur, cur, 0), gr, dim3(64, 4), st);
-      launch_finalize<float>(clock(), part, nb, p.cfl, 0, 0, probe_args(), u(cur), nullptr, st);
-    } else {
-      launch_cfl<double>(stage_args<double>(cur, cur, cur, 0), gr, dim3(64, 4), st);
-      launch_finalize<double>(clock(), part, nb, p.cfl, 0, 0, probe_args(), u(cur), nullptr, st);
-    }
+  // A new state's first dt from the partials its kernel left, the clock
+  // cleared as `reset` says; waits for it.
+  int finish_state(int reset) {
+    const int nb = (int)((ncell() + INIT_CELLS - 1) / INIT_CELLS);
+    if (f32)
+      launch_finalize<float>(clock(), partials(), nb, p.cfl, 0, 0, probe_args(), u(cur), nullptr,
+                             stream, reset);
+    else
+      launch_finalize<double>(clock(), partials(), nb, p.cfl, 0, 0, probe_args(), u(cur), nullptr,
+                              stream, reset);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(stream));
+    return ICR_OK;
   }
 
   void drop_graphs() {
-    if (!graphs_ok) return;
     for (int p = 0; p < NGRAPH; ++p)
-      for (int q = 0; q < 2; ++q) (void)hipGraphExecDestroy(g_steps[p][q]);
-    graphs_ok = false;
+      for (int q = 0; q < 2; ++q) {
+        if (g_steps[p][q]) (void)hipGraphExecDestroy(g_steps[p][q]);
+        g_steps[p][q] = nullptr;
+      }
   }
 
   int capture(int from, int nsteps, hipGraphExec_t* out) {
@@ -487,19 +507,17 @@ struct icr_solver {
     return ICR_OK;
   }
 
-  int build_graphs() {
-    if (graphs_ok) return ICR_OK;
-    for (int p = 0; p < NGRAPH; ++p)
-      for (int q = 0; q < 2; ++q) {
-        const int rc = capture(q, GRAPH_STEPS[p], &g_steps[p][q]);
-        if (rc) {  // release the graphs captured so far
-          for (int pp = 0; pp <= p; ++pp)
-            for (int qq = 0; qq < 2; ++qq)
-              if (pp < p || qq < q) (void)hipGraphExecDestroy(g_steps[pp][qq]);
-          return rc;
-        }
+  // the graph of GRAPH_STEPS[p] steps from buffer q, captured when a call
+  // first needs it (all ten took 8 ms of a solver's first call)
+  int graph(int p, int q, hipGraphExec_t* out) {
+    if (!g_steps[p][q]) {
+      const int rc = capture(q, GRAPH_STEPS[p], &g_steps[p][q]);
+      if (rc) {
+        g_steps[p][q] = nullptr;
+        return rc;
       }
-    graphs_ok = true;
+    }
+    *out = g_steps[p][q];
     return ICR_OK;
   }
 
@@ -570,7 +588,7 @@ int icr_create(const icr_grid* g, const icr_phys* p, void* ws, size_t ws_bytes, 
   s->variant = (p->limiter == ICR_LIM_WENO5 && p->tracer) ? 1 : 2;
   s->planes = 0;
   s->use_graphs = 1;
-  s->graphs_ok = false;
+  for (auto& g2 : s->g_steps) g2[0] = g2[1] = nullptr;
   s->part_override = nullptr;
   hipError_t e = hipGetDevice(&s->dev);
   if (e != hipSuccess) {
@@ -776,37 +794,23 @@ int icr_set_cmes(icr_solver* s, int n, const double* rows) {
   return ICR_OK;
 }
 
-static int refresh_dt(icr_solver* s) {
-  s->enqueue_cfl(s->stream);
-  HIP_TRY(hipGetLastError());
-  HIP_TRY(hipStreamSynchronize(s->stream));
-  return ICR_OK;
-}
-
 int icr_init_radial(icr_solver* s) {
   if (!s) return fail(ICR_ERR_ARG, "solver is NULL");
   if (!s->have_maps) return fail(ICR_ERR_STATE, "set boundary maps first");
+  const int c = s->cur;
   if (s->f32)
-    launch_init_radial<float>(s->bnd(), s->m64(), s->u(s->cur), s->g.n_r, s->p.gamma, s->stream);
+    launch_init_radial<float>(s->stage_args<float>(c, c, c, 0), s->bnd(), s->m64(), s->p.gamma,
+                              s->stream);
   else
-    launch_init_radial<double>(s->bnd(), s->m64(), s->u(s->cur), s->g.n_r, s->p.gamma,
+    launch_init_radial<double>(s->stage_args<double>(c, c, c, 0), s->bnd(), s->m64(), s->p.gamma,
                                s->stream);
   HIP_TRY(hipGetLastError());
   if (s->trc())
     HIP_TRY(hipMemsetAsync(s->tr(s->cur), 0, (s->f32 ? 4 : 8) * (size_t)s->ncell(), s->stream));
-  DevClock c;
-  int rc = s->read_clock(&c);
-  if (rc) return rc;
-  c.t = 0.0;
-  c.step = 0;
-  c.bad = BAD_NONE;
-  c.counter = 0;
-  c.last_dt = 0.0;
-  c.resid = 0.0;
-  rc = s->write_clock(&c);
+  const int rc = s->finish_state(RESET_RUN);
   if (rc) return rc;
   s->have_state = true;
-  return refresh_dt(s);
+  return ICR_OK;
 }
 
 int icr_set_state(icr_solver* s, const double* data, int kind, int on_device) {
@@ -816,13 +820,18 @@ int icr_set_state(icr_solver* s, const double* data, int kind, int on_device) {
     return fail(ICR_ERR_ARG, "unknown state kind %d", kind);
   const long long n = s->ncell();
   const Scale sc = s->un.scale();
-  void* u = s->u(s->cur);
-  if (on_device) {
+  const int q = s->cur;
+  auto import = [&](const double* in, long long ld, long long c0, long long m) {
     if (s->f32)
-      launch_import<float>(data, n, u, n, 0, n, kind, sc, s->p.gamma, s->stream);
+      launch_import<float>(s->stage_args<float>(q, q, q, 0), in, ld, c0, m, kind, sc, s->p.gamma,
+                           s->stream);
     else
-      launch_import<double>(data, n, u, n, 0, n, kind, sc, s->p.gamma, s->stream);
-    HIP_TRY(hipGetLastError());
+      launch_import<double>(s->stage_args<double>(q, q, q, 0), in, ld, c0, m, kind, sc,
+                            s->p.gamma, s->stream);
+    return hipGetLastError();
+  };
+  if (on_device) {
+    HIP_TRY(import(data, n, 0, n));
   } else {
     // host data: chunks of stage_cells cells through the staging region
     double* st = (double*)(s->ws + s->L.stage);
@@ -831,25 +840,14 @@ int icr_set_state(icr_solver* s, const double* data, int kind, int on_device) {
       const long long m = n - c0 < cm ? n - c0 : cm;
       HIP_TRY(hipMemcpy2DAsync(st, sizeof(double) * m, data + c0, sizeof(double) * n,
                                sizeof(double) * m, NV, hipMemcpyHostToDevice, s->stream));
-      if (s->f32)
-        launch_import<float>(st, m, u, n, c0, m, kind, sc, s->p.gamma, s->stream);
-      else
-        launch_import<double>(st, m, u, n, c0, m, kind, sc, s->p.gamma, s->stream);
-      HIP_TRY(hipGetLastError());
+      HIP_TRY(import(st, m, c0, m));
     }
   }
   if (s->trc()) HIP_TRY(hipMemsetAsync(s->tr(s->cur), 0, (s->f32 ? 4 : 8) * (size_t)n, s->stream));
-  hipError_t e = hipStreamSynchronize(s->stream);
-  if (e != hipSuccess) return fail(ICR_ERR_HIP, "state import failed: %s", hipGetErrorString(e));
-  DevClock c;
-  int rc = s->read_clock(&c);
-  if (rc) return rc;
-  c.bad = BAD_NONE;
-  c.counter = 0;
-  rc = s->write_clock(&c);
+  const int rc = s->finish_state(RESET_BAD);
   if (rc) return rc;
   s->have_state = true;
-  return refresh_dt(s);
+  return ICR_OK;
 }
 
 int icr_get_state(icr_solver* s, double* out, int kind, int on_device) {
@@ -960,7 +958,7 @@ int icr_step_noalloc(icr_solver* s, int n, double t_end_s, icr_step_info* info) 
   int rc = scratch_for_device(s->dev, &sp);  // looked up at creation: no lookup here
   if (rc) return rc;
   const double tend = t_end_s > 0.0 ? t_end_s / s->un.t : -1.0;
-  launch_clock_begin(s->clock(), tend, s->stream);
+  s->enqueue_begin(tend);
   // direct launches (no graph instantiation), partials in the fixed array;
   // every stage-2 block writes its slot before the finalize kernel reads it,
   // so nothing needs clearing between calls
@@ -979,14 +977,15 @@ int icr_step(icr_solver* s, int n, double t_end_s, icr_step_info* info) {
   if (!s->have_maps) return fail(ICR_ERR_STATE, "set boundary maps first");
   if (!s->have_state) return fail(ICR_ERR_STATE, "initialise the state first");
   const double tend = t_end_s > 0.0 ? t_end_s / s->un.t : -1.0;
-  launch_clock_begin(s->clock(), tend, s->stream);
+  s->enqueue_begin(tend);
   if (s->use_graphs && n > 0) {
-    int rc = s->build_graphs();
-    if (rc) return rc;
     int left = n;
     for (int p = 0; p < NGRAPH; ++p)
       while (left >= GRAPH_STEPS[p] && (p == 0 || (left & GRAPH_STEPS[p]))) {
-        HIP_TRY(hipGraphLaunch(s->g_steps[p][s->cur], s->stream));
+        hipGraphExec_t g;
+        const int rc = s->graph(p, s->cur, &g);
+        if (rc) return rc;
+        HIP_TRY(hipGraphLaunch(g, s->stream));
         s->cur ^= GRAPH_STEPS[p] & 1;  // an even number of steps keeps the buffer
         left -= GRAPH_STEPS[p];
       }

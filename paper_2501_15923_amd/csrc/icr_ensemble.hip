@@ -70,20 +70,9 @@ __device__ __forceinline__ void bnd_item(const RunDesc<R>* runs, const EnsTables
   const int r = find_run(e.bnd_off, e.n_runs, item);
   const RunDesc<R>& rd = runs[r];
   const int tid = threadIdx.y * blockDim.x + threadIdx.x;
-  const int q = (item - e.bnd_off[r]) * 256 + tid;
-  const int plane = rd.bnd.nt * rd.bnd.np;
-  if (q >= plane || !rd.clock->active) return;
-  const int j = q % rd.bnd.nt, k = q / rd.bnd.nt;
-  double w[NV];
-  int in0, in1;
-  boundary_prim(rd.bnd, rd.clock->t, j, k, w, &in0);
-  for (int v = 0; v < NV; ++v) rd.ghost0[(long long)v * plane + q] = (R)w[v];
-  boundary_prim(rd.bnd, rd.clock->t + rd.clock->dt, j, k, w, &in1);
-  for (int v = 0; v < NV; ++v) rd.ghost1[(long long)v * plane + q] = (R)w[v];
-  if (rd.tghost0) {  // tracer of the inner ghost cells: inside an inserted cone
-    rd.tghost0[q] = (R)in0;
-    rd.tghost1[q] = (R)in1;
-  }
+  if (!rd.clock->active) return;
+  boundary_column<R>(rd.bnd, rd.clock->t, rd.clock->dt, (item - e.bnd_off[r]) * 256 + tid,
+                     rd.ghost0, rd.ghost1, rd.tghost0, rd.tghost1);
 }
 
 // Tracer item: 256 cells of one run, after that run's stage tiles.

@@ -11,7 +11,6 @@
 //                   neighbour converted on the fly (reference variant; the
 //                   default face-once variant is in icr_stage_lds.hip);
 //                   stage 2 also writes per-block CFL / residual partials
-//   k_cfl           CFL partials of the current state (after init / set_state)
 //   k_probe_sample  trajectory interpolation, frame change and trilinear
 //                   sampling on the stretched grid (Sect. 2)
 //
@@ -95,21 +94,40 @@ void launch_metric(const MetricArgs& a, void* mr, bool f32, hipStream_t s) {
 template <typename R>
 __global__ void k_boundary(BndArgs a, const DevClock* __restrict__ ck, R* __restrict__ g1,
                            R* __restrict__ g2, R* __restrict__ tg1, R* __restrict__ tg2) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  const int plane = a.nt * a.np;
-  if (q >= plane || !ck->active) return;
-  const int j = q % a.nt, k = q / a.nt;
-  double w[NV];
-  int in1, in2;
-  boundary_prim(a, ck->t, j, k, w, &in1);
-  for (int v = 0; v < NV; ++v) g1[(long long)v * plane + q] = (R)w[v];
-  boundary_prim(a, ck->t + ck->dt, j, k, w, &in2);
-  for (int v = 0; v < NV; ++v) g2[(long long)v * plane + q] = (R)w[v];
-  // tracer of the inner ghost cells: CME material inside an inserted cone
-  if (tg1) {
-    tg1[q] = (R)in1;
-    tg2[q] = (R)in2;
+  if (!ck->active) return;
+  boundary_column<R>(a, ck->t, ck->dt, blockIdx.x * blockDim.x + threadIdx.x, g1, g2, tg1, tg2);
+}
+
+// The clock of a new call: its end time and step count, the next dt.  Fields
+// that other threads of the launch read (t, dt_cfl, bad) keep their values.
+__device__ __forceinline__ void begin_clock(DevClock& c, double t_end) {
+  c.t_end = t_end;
+  c.taken = 0;
+  c.active = c.bad == BAD_NONE ? 1 : 0;
+  set_next_dt(&c, c.dt_cfl);
+  if (c.bad != BAD_NONE) c.active = 0;
+}
+
+// Start of a call: the clock (written by block 0, formed by every block for
+// itself) and the first step's boundary.
+template <typename R>
+__global__ void __launch_bounds__(256) k_begin(BndArgs a, DevClock* ck, double t_end,
+                                               R* __restrict__ g1, R* __restrict__ g2,
+                                               R* __restrict__ tg1, R* __restrict__ tg2) {
+  DevClock c;
+  c.t = ck->t;
+  c.dt_cfl = ck->dt_cfl;
+  c.bad = ck->bad;
+  begin_clock(c, t_end);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ck->t_end = c.t_end;
+    ck->taken = c.taken;
+    ck->active = c.active;
+    ck->dt = c.dt;
+    ck->clip = c.clip;
   }
+  if (c.active)
+    boundary_column<R>(a, c.t, c.dt, blockIdx.x * blockDim.x + threadIdx.x, g1, g2, tg1, tg2);
 }
 
 // Boundary at an arbitrary time into a [8][nt][np] double buffer (SI).
@@ -135,6 +153,17 @@ void launch_boundary(const BndArgs& a, const DevClock* ck, void* g1, void* g2, v
                        (double*)tg1, (double*)tg2);
 }
 
+void launch_begin(const BndArgs& a, DevClock* ck, double t_end, void* g1, void* g2, void* tg1,
+                  void* tg2, bool f32, hipStream_t s) {
+  const dim3 grid((a.nt * a.np + 255) / 256), blk(256);
+  if (f32)
+    hipLaunchKernelGGL(k_begin<float>, grid, blk, 0, s, a, ck, t_end, (float*)g1, (float*)g2,
+                       (float*)tg1, (float*)tg2);
+  else
+    hipLaunchKernelGGL(k_begin<double>, grid, blk, 0, s, a, ck, t_end, (double*)g1, (double*)g2,
+                       (double*)tg1, (double*)tg2);
+}
+
 void launch_boundary_at(const BndArgs& a, double t, double* out, const Scale& sc, hipStream_t s) {
   const int plane = a.nt * a.np;
   hipLaunchKernelGGL(k_boundary_at, dim3((plane + 255) / 256), dim3(256), 0, s, a, t, out, sc);
@@ -142,11 +171,7 @@ void launch_boundary_at(const BndArgs& a, double t, double* out, const Scale& sc
 
 __global__ void k_clock_begin(DevClock* ck, double t_end) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  ck->t_end = t_end;
-  ck->taken = 0;
-  ck->active = ck->bad == BAD_NONE ? 1 : 0;
-  set_next_dt(ck, ck->dt_cfl);
-  if (ck->bad != BAD_NONE) ck->active = 0;
+  begin_clock(*ck, t_end);
 }
 
 void launch_clock_begin(DevClock* ck, double t_end, hipStream_t s) {
@@ -191,6 +216,8 @@ __global__ void __launch_bounds__(256) k_stage_v1(StageArgs<R> a) {
   const bool valid = i < a.nr && j < a.nt;
   const int active = a.clock->active;
   const R dt = (R)a.clock->dt;
+  // the clock this step began with, for the kernel that ends it
+  if (STAGE == 1 && i == 0 && j == 0 && k == 0) a.clock[1] = a.clock[0];
   double lam = 0.0, s1 = 0.0, s0 = 0.0;
   int bad = BAD_NONE;
   if (valid) {
@@ -329,27 +356,6 @@ __global__ void __launch_bounds__(256) k_stage_v1(StageArgs<R> a) {
                    lam, s1, s0, bad);
 }
 
-// CFL dt of the current state; no time advance.
-template <typename R>
-__global__ void __launch_bounds__(256) k_cfl(StageArgs<R> a) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int j = blockIdx.y * blockDim.y + threadIdx.y;
-  const int k = blockIdx.z;
-  double lam = 0.0;
-  int bad = BAD_NONE;
-  if (i < a.nr && j < a.nt) {
-    const long long c = ((long long)k * a.nt + j) * a.nr + i;
-    R u[NV], w[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) u[v] = a.uin[v * a.ncell + c];
-    cons2prim<R>(u, w, a.gm1);
-    lam = cell_rate<R>(w, a.m, i, j, a.gam);
-  }
-  // invalid cells are reported by the next step, not here
-  write_partials(a.partials, (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x,
-                 lam, 0.0, 0.0, bad);
-}
-
 template <typename R, int FLUX, int LIM>
 static void launch_stage_t(const StageArgs<R>& a, int stage, dim3 grid, dim3 blk, hipStream_t s) {
   if (stage == 1)
@@ -380,74 +386,97 @@ template void launch_stage<double>(const StageArgs<double>&, int, int, int, dim3
 template void launch_stage<float>(const StageArgs<float>&, int, int, int, dim3, dim3,
                                   hipStream_t);
 
-template <typename R>
-void launch_cfl(const StageArgs<R>& a, dim3 grid, dim3 blk, hipStream_t s) {
-  hipLaunchKernelGGL(k_cfl<R>, grid, blk, 0, s, a);
-}
-template void launch_cfl<double>(const StageArgs<double>&, dim3, dim3, hipStream_t);
-template void launch_cfl<float>(const StageArgs<float>&, dim3, dim3, hipStream_t);
-
 // ------------------------------------------------- init and conversions --
-// Radial expansion of map 0 from r_in (Sect. 2.1).
+// The CFL rate of a cell from the state just stored in it (the values the
+// stage kernels will read), so that a new state's first dt needs no second
+// pass over it.
 template <typename R>
-__global__ void k_init_radial(BndArgs b, const double* __restrict__ m64, R* __restrict__ u,
-                              int nr, double gam) {
-  const long long n = (long long)nr * b.nt * b.np;
-  const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= n) return;
-  const int i = (int)(c % nr);
-  const int j = (int)((c / nr) % b.nt);
-  const int k = (int)(c / ((long long)nr * b.nt));
-  const long long plane = (long long)b.nt * b.np;
-  const long long q = (long long)j * b.np + k;
-  const double rc = m64[8 * nr + i];
-  const double x = b.r_in / rc;
-  const double sth = sin(b.tc[j]);
-  double w[NV];
-  w[0] = b.maps[0 * plane + q] * x * x;
-  w[1] = b.maps[1 * plane + q];
-  w[2] = 0.0;
-  w[3] = -b.omega * rc * sth;
-  w[4] = b.maps[4 * plane + q] * pow(x, 2.0 * gam);
-  w[5] = b.maps[5 * plane + q] * x * x;
-  w[6] = 0.0;
-  w[7] = b.maps[7 * plane + q] * x;
-  double uu[NV];
-  prim2cons<double>(w, uu, 1.0 / (gam - 1.0));
-  for (int v = 0; v < NV; ++v) u[v * n + c] = (R)uu[v];
+__device__ __forceinline__ double stored_rate(const StageArgs<R>& a, long long c,
+                                              const double (&uu)[NV]) {
+  R u[NV], w[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) u[v] = (R)uu[v];
+  cons2prim<R>(u, w, a.gm1);
+  return cell_rate<R>(w, a.m, (int)(c % a.nr), (int)((c / a.nr) % a.nt), a.gam);
+}
+
+// Radial expansion of map 0 from r_in (Sect. 2.1).  Invalid cells of a new
+// state are reported by its first step, not here.
+template <typename R>
+__global__ void __launch_bounds__(256) k_init_radial(StageArgs<R> a, BndArgs b,
+                                                     const double* __restrict__ m64, double gam) {
+  const int nr = a.nr;
+  R* u = const_cast<R*>(a.uin);
+  double lam = 0.0;
+  for (int h = 0; h < INIT_CELLS / 256; ++h) {
+    const long long c = (long long)blockIdx.x * INIT_CELLS + h * 256 + threadIdx.x;
+    if (c >= a.ncell) break;
+    const int i = (int)(c % nr);
+    const int j = (int)((c / nr) % b.nt);
+    const int k = (int)(c / ((long long)nr * b.nt));
+    const long long plane = (long long)b.nt * b.np;
+    const long long q = (long long)j * b.np + k;
+    const double rc = m64[8 * nr + i];
+    const double x = b.r_in / rc;
+    const double sth = sin(b.tc[j]);
+    double w[NV];
+    w[0] = b.maps[0 * plane + q] * x * x;
+    w[1] = b.maps[1 * plane + q];
+    w[2] = 0.0;
+    w[3] = -b.omega * rc * sth;
+    w[4] = b.maps[4 * plane + q] * pow(x, 2.0 * gam);
+    w[5] = b.maps[5 * plane + q] * x * x;
+    w[6] = 0.0;
+    w[7] = b.maps[7 * plane + q] * x;
+    double uu[NV];
+    prim2cons<double>(w, uu, 1.0 / (gam - 1.0));
+    for (int v = 0; v < NV; ++v) u[v * a.ncell + c] = (R)uu[v];
+    lam = fmax(lam, stored_rate<R>(a, c, uu));
+  }
+  write_partials(a.partials, blockIdx.x, lam, 0.0, 0.0, BAD_NONE);
 }
 
 template <typename R>
-void launch_init_radial(const BndArgs& b, const double* m64, void* u, int nr, double gam,
+void launch_init_radial(const StageArgs<R>& a, const BndArgs& b, const double* m64, double gam,
                         hipStream_t s) {
-  const long long n = (long long)nr * b.nt * b.np;
-  hipLaunchKernelGGL(k_init_radial<R>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, b,
-                     m64, (R*)u, nr, gam);
+  hipLaunchKernelGGL(k_init_radial<R>, dim3((unsigned)((a.ncell + INIT_CELLS - 1) / INIT_CELLS)),
+                     dim3(256), 0, s, a, b, m64, gam);
 }
-template void launch_init_radial<double>(const BndArgs&, const double*, void*, int, double,
-                                         hipStream_t);
-template void launch_init_radial<float>(const BndArgs&, const double*, void*, int, double,
-                                        hipStream_t);
+template void launch_init_radial<double>(const StageArgs<double>&, const BndArgs&, const double*,
+                                         double, hipStream_t);
+template void launch_init_radial<float>(const StageArgs<float>&, const BndArgs&, const double*,
+                                        double, hipStream_t);
 
 // kind 0: primitive SI <-> state; kind 1: conservative code units <-> state.
 // Cells c0 .. c0+m-1 of the state (variable stride ncell); the buffer holds
 // those m cells with variable stride ld (ld = ncell, c0 = 0 for a whole
-// state in place, ld = m for a staging chunk).
+// state in place, ld = m for a staging chunk).  The import also forms the CFL
+// partials (a pass of its own over the state took 70 us at 600 x 60 x 120).
 template <typename R>
-__global__ void k_import(const double* __restrict__ in, long long ld, R* __restrict__ u,
-                         long long ncell, long long c0, long long m, int kind, Scale sc,
-                         double gam) {
-  const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= m) return;
-  double a[NV], uu[NV];
-  for (int v = 0; v < NV; ++v) a[v] = in[v * ld + c];
-  if (kind == 0) {
-    for (int v = 0; v < NV; ++v) a[v] /= sc.s[v];
-    prim2cons<double>(a, uu, 1.0 / (gam - 1.0));
-  } else {
-    for (int v = 0; v < NV; ++v) uu[v] = a[v];
+__global__ void __launch_bounds__(256) k_import(StageArgs<R> a, const double* __restrict__ in,
+                                                long long ld, long long c0, long long m, int kind,
+                                                Scale sc, double gam) {
+  R* u = const_cast<R*>(a.uin);
+  double lam = 0.0;
+  for (int h = 0; h < INIT_CELLS / 256; ++h) {
+    const long long c = (long long)blockIdx.x * INIT_CELLS + h * 256 + threadIdx.x;
+    if (c >= m) break;
+    double x[NV], uu[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) x[v] = in[v * ld + c];
+    if (kind == 0) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) x[v] /= sc.s[v];
+      prim2cons<double>(x, uu, 1.0 / (gam - 1.0));
+    } else {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) uu[v] = x[v];
+    }
+#pragma unroll
+    for (int v = 0; v < NV; ++v) u[v * a.ncell + c0 + c] = (R)uu[v];
+    lam = fmax(lam, stored_rate<R>(a, c0 + c, uu));
   }
-  for (int v = 0; v < NV; ++v) u[v * ncell + c0 + c] = (R)uu[v];
+  write_partials(a.partials, (int)(c0 / INIT_CELLS) + blockIdx.x, lam, 0.0, 0.0, BAD_NONE);
 }
 
 template <typename R>
@@ -466,10 +495,10 @@ __global__ void k_export(const R* __restrict__ u, long long ncell, long long c0,
 }
 
 template <typename R>
-void launch_import(const double* in, long long ld, void* u, long long ncell, long long c0,
+void launch_import(const StageArgs<R>& a, const double* in, long long ld, long long c0,
                    long long m, int kind, const Scale& sc, double gam, hipStream_t s) {
-  hipLaunchKernelGGL(k_import<R>, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, in, ld,
-                     (R*)u, ncell, c0, m, kind, sc, gam);
+  hipLaunchKernelGGL(k_import<R>, dim3((unsigned)((m + INIT_CELLS - 1) / INIT_CELLS)), dim3(256),
+                     0, s, a, in, ld, c0, m, kind, sc, gam);
 }
 template <typename R>
 void launch_export(const void* u, long long ncell, long long c0, long long m, double* out,
@@ -477,9 +506,9 @@ void launch_export(const void* u, long long ncell, long long c0, long long m, do
   hipLaunchKernelGGL(k_export<R>, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s,
                      (const R*)u, ncell, c0, m, out, ld, kind, sc, gam);
 }
-template void launch_import<double>(const double*, long long, void*, long long, long long,
+template void launch_import<double>(const StageArgs<double>&, const double*, long long, long long,
                                     long long, int, const Scale&, double, hipStream_t);
-template void launch_import<float>(const double*, long long, void*, long long, long long,
+template void launch_import<float>(const StageArgs<float>&, const double*, long long, long long,
                                    long long, int, const Scale&, double, hipStream_t);
 template void launch_export<double>(const void*, long long, long long, long long, double*,
                                     long long, int, const Scale&, double, hipStream_t);

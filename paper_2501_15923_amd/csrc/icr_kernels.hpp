@@ -30,6 +30,13 @@ struct Scale {
   double len;    // metres per code length unit
 };
 
+// What k_finalize clears when a new state has been put in: nothing, the
+// record of an invalid cell, or that and the clock.
+enum : int { RESET_NONE = 0, RESET_BAD = 1, RESET_RUN = 2 };
+// Cells per block of the kernels that put a state in and form its CFL
+// partials (4 per thread): fewer partials for the one-block reduction.
+constexpr int INIT_CELLS = 1024;
+
 struct MetricArgs {
   int nr, nt;
   double r_in, r_out, q;     // code units, q = (r_out/r_in)^(1/nr)
@@ -365,6 +372,28 @@ __device__ inline void boundary_prim(const BndArgs& a, double t, int j, int k, d
   }
 }
 
+// Inner-boundary primitives of column q (= k * nt + j) at the two stage times
+// t and t + dt; tg1 / tg2 (with the tracer): 1 inside an inserted cone.
+template <typename R>
+__device__ __forceinline__ void boundary_column(const BndArgs& a, double t, double dt, int q,
+                                                R* __restrict__ g1, R* __restrict__ g2,
+                                                R* __restrict__ tg1, R* __restrict__ tg2) {
+  const int plane = a.nt * a.np;
+  if (q >= plane) return;
+  const int j = q % a.nt, k = q / a.nt;
+  double w[NV];
+  int in1, in2;
+  boundary_prim(a, t, j, k, w, &in1);
+  for (int v = 0; v < NV; ++v) g1[(long long)v * plane + q] = (R)w[v];
+  boundary_prim(a, t + dt, j, k, w, &in2);
+  for (int v = 0; v < NV; ++v) g2[(long long)v * plane + q] = (R)w[v];
+  // tracer of the inner ghost cells: CME material inside an inserted cone
+  if (tg1) {
+    tg1[q] = (R)in1;
+    tg2[q] = (R)in2;
+  }
+}
+
 template <typename R>
 Metric<R> metric_view(const R* base, int nr, int nt, double dth);
 
@@ -372,20 +401,28 @@ void launch_metric(const MetricArgs& a, void* mr, bool f32, hipStream_t s);
 void launch_boundary(const BndArgs& a, const DevClock* ck, void* g1, void* g2, void* tg1,
                      void* tg2, bool f32,
                      hipStream_t s);
+// start of a call: t_end and the step counter of the clock, the first step's
+// dt and boundary
+void launch_begin(const BndArgs& a, DevClock* ck, double t_end, void* g1, void* g2, void* tg1,
+                  void* tg2, bool f32, hipStream_t s);
+template <typename R>
+void launch_step_end(DevClock* ck, const double* part, int nblocks, double cfl, int log_on,
+                     const ProbeArgs& pa, const void* u, double* log, const BndArgs& bnd,
+                     void* g1, void* g2, void* tg1, void* tg2, hipStream_t s);
 void launch_boundary_at(const BndArgs& a, double t, double* out, const Scale& sc, hipStream_t s);
 void launch_clock_begin(DevClock* ck, double t_end, hipStream_t s);
 template <typename R>
 void launch_stage(const StageArgs<R>& a, int stage, int flux, int lim, dim3 grid, dim3 blk,
                   hipStream_t s);
+// a.uin: the state to write; CFL partials per INIT_CELLS cells
 template <typename R>
-void launch_cfl(const StageArgs<R>& a, dim3 grid, dim3 blk, hipStream_t s);
-template <typename R>
-void launch_init_radial(const BndArgs& b, const double* m64, void* u, int nr, double gam,
+void launch_init_radial(const StageArgs<R>& a, const BndArgs& b, const double* m64, double gam,
                         hipStream_t s);
 // cells c0 .. c0+m-1 of a state with ncell cells; the double buffer holds
-// them with variable stride ld
+// them with variable stride ld.  The import writes a.uin and its CFL partials
+// (c0 a multiple of INIT_CELLS)
 template <typename R>
-void launch_import(const double* in, long long ld, void* u, long long ncell, long long c0,
+void launch_import(const StageArgs<R>& a, const double* in, long long ld, long long c0,
                    long long m, int kind, const Scale& sc, double gam, hipStream_t s);
 template <typename R>
 void launch_export(const void* u, long long ncell, long long c0, long long m, double* out,
@@ -424,6 +461,6 @@ void launch_fast_math(const double* x, long long n, double* rcp, double* sq, hip
 template <typename R>
 void launch_finalize(DevClock* ck, const double* part, int nblocks, double cfl, int advance,
                      int log_on, const ProbeArgs& pa, const void* u, double* log,
-                     hipStream_t s);
+                     hipStream_t s, int reset = RESET_NONE);
 
 }  // namespace icr

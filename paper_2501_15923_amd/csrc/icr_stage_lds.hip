@@ -16,6 +16,8 @@ k_stage_lds(StageArgs<R> a, int kplanes) {
   const int nb = nbx * nby * gridDim.z;
   const int b = (blockIdx.z * nby + blockIdx.y) * nbx + blockIdx.x;
   const int tile = xcd_tile(b, nb);
+  // the clock this step began with, for the kernel that ends it
+  if (STAGE == 1 && b == 0 && threadIdx.x == 0 && threadIdx.y == 0) a.clock[1] = a.clock[0];
   __shared__ StageW<R, TR, TT> smw;
   __shared__ StageF<R, TR, TT> smf;
   stage_tile<R, TR, TT, FLUX, LIM, STAGE, FM>(a, kplanes, tile % nbx, (tile / nbx) % nby,
@@ -80,6 +82,8 @@ k_stage_w5(StageArgs<R> a, int kplanes) {
   const int nb = nbx * nby * gridDim.z;
   const int b = (blockIdx.z * nby + blockIdx.y) * nbx + blockIdx.x;
   const int tile = xcd_tile(b, nb);
+  // the clock this step began with, for the kernel that ends it
+  if (STAGE == 1 && b == 0 && threadIdx.x == 0 && threadIdx.y == 0) a.clock[1] = a.clock[0];
   __shared__ StageW5<R> sm;
   stage_tile_w5<R, FLUX, STAGE>(a, kplanes, tile % nbx, (tile / nbx) % nby, tile / (nbx * nby),
                                 tile, sm);
@@ -121,20 +125,47 @@ __global__ void __launch_bounds__(256) k_finalize(DevClock* ck, const double* __
                                                   int nblocks, double cfl, int advance,
                                                   int log_on, ProbeArgs pa,
                                                   const R* __restrict__ u,
-                                                  double* __restrict__ log) {
-  finalize_run<R>(ck, part, nblocks, cfl, advance, log_on, pa, u, log);
+                                                  double* __restrict__ log, int reset) {
+  finalize_run<R>(ck, part, nblocks, cfl, advance, log_on, pa, u, log, reset);
 }
 
 template <typename R>
 void launch_finalize(DevClock* ck, const double* part, int nblocks, double cfl, int advance,
                      int log_on, const ProbeArgs& pa, const void* u, double* log,
-                     hipStream_t s) {
+                     hipStream_t s, int reset) {
   hipLaunchKernelGGL(k_finalize<R>, dim3(1), dim3(256), 0, s, ck, part, nblocks, cfl, advance,
-                     log_on, pa, (const R*)u, log);
+                     log_on, pa, (const R*)u, log, reset);
 }
 template void launch_finalize<double>(DevClock*, const double*, int, double, int, int,
-                                      const ProbeArgs&, const void*, double*, hipStream_t);
+                                      const ProbeArgs&, const void*, double*, hipStream_t, int);
 template void launch_finalize<float>(DevClock*, const double*, int, double, int, int,
-                                     const ProbeArgs&, const void*, double*, hipStream_t);
+                                     const ProbeArgs&, const void*, double*, hipStream_t, int);
+
+// Latency-bound, one launch where the clock (4.7 us, one block) and the next
+// step's boundary (4.8 us) were two: 64x16x32 steps take 24 us instead of 28.
+template <typename R>
+__global__ void __launch_bounds__(256) k_step_end(DevClock* ck, const double* __restrict__ part,
+                                                  int nblocks, double cfl, int log_on,
+                                                  ProbeArgs pa, const R* __restrict__ u,
+                                                  double* __restrict__ log, BndArgs bnd,
+                                                  R* __restrict__ g1, R* __restrict__ g2,
+                                                  R* __restrict__ tg1, R* __restrict__ tg2) {
+  end_step<R>(ck, part, nblocks, cfl, log_on, pa, u, log, bnd, g1, g2, tg1, tg2);
+}
+
+template <typename R>
+void launch_step_end(DevClock* ck, const double* part, int nblocks, double cfl, int log_on,
+                     const ProbeArgs& pa, const void* u, double* log, const BndArgs& bnd,
+                     void* g1, void* g2, void* tg1, void* tg2, hipStream_t s) {
+  const int blocks = (bnd.nt * bnd.np + 255) / 256;
+  hipLaunchKernelGGL(k_step_end<R>, dim3(blocks), dim3(256), 0, s, ck, part, nblocks, cfl, log_on,
+                     pa, (const R*)u, log, bnd, (R*)g1, (R*)g2, (R*)tg1, (R*)tg2);
+}
+template void launch_step_end<double>(DevClock*, const double*, int, double, int,
+                                      const ProbeArgs&, const void*, double*, const BndArgs&,
+                                      void*, void*, void*, void*, hipStream_t);
+template void launch_step_end<float>(DevClock*, const double*, int, double, int, const ProbeArgs&,
+                                     const void*, double*, const BndArgs&, void*, void*, void*,
+                                     void*, hipStream_t);
 
 }  // namespace icr

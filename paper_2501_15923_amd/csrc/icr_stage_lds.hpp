@@ -506,22 +506,15 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R>& a, int kplanes, i
 
 
 // ------------------------------------------------------------ finalize --
-// Reduce the stage-2 (or CFL) block partials in a fixed order, advance the
-// clock, set the next dt; then, if probes are logged, append a record.
-template <typename R>
-__device__ __forceinline__ void finalize_run(DevClock* ck, const double* __restrict__ part,
-                                             int nblocks, double cfl, int advance, int log_on,
-                                             const ProbeArgs& pa, const R* __restrict__ u,
-                                             double* __restrict__ log) {
-  __shared__ double sh[4][4];
-  __shared__ int s_rec;
-  __shared__ long long s_row, s_idx;
-  __shared__ double s_t;
+// Reduce the stage-2 (or CFL) block partials in a fixed order (a block of 256
+// threads; the result is thread 0's).
+__device__ __forceinline__ void reduce_partials(const double* __restrict__ part, int nblocks,
+                                                double& l, double& a1, double& a0, int& b,
+                                                double (*sh)[4]) {
   const int tid = threadIdx.y * blockDim.x + threadIdx.x;
   const int nthr = blockDim.x * blockDim.y;
-  if (!ck->active && advance) return;  // the stage kernels did not run
-  double l = 0.0, a1 = 0.0, a0 = 0.0;
-  int b = BAD_NONE;
+  l = a1 = a0 = 0.0;
+  b = BAD_NONE;
   for (int q = tid; q < nblocks; q += nthr) {
     l = fmax(l, part[4 * q + 0]);
     a1 += part[4 * q + 1];
@@ -530,39 +523,112 @@ __device__ __forceinline__ void finalize_run(DevClock* ck, const double* __restr
     b = qb < b ? qb : b;
   }
   block_reduce(l, a1, a0, b, sh);
+}
+
+// Advance the clock by the step the partials belong to (advance = 1) and set
+// the next dt; *idx is the cadence index of the new time and the result says
+// whether a probe record is due.
+__device__ __forceinline__ bool advance_clock(DevClock& c, double l, double a1, double a0, int b,
+                                              double cfl, int advance, int log_on,
+                                              const ProbeArgs& pa) {
+  if (advance) {
+    c.t = c.clip ? c.t_end : c.t + c.dt;
+    c.step += 1;
+    c.taken += 1;
+    c.last_dt = c.dt;
+    c.resid = sqrt(a1) / sqrt(a0);
+    if (b != BAD_NONE) {
+      if (c.bad == BAD_NONE || b < c.bad) c.bad = b;
+    }
+  }
+  set_next_dt(&c, cfl / l);
+  if (c.bad != BAD_NONE) c.active = 0;
+  // probe cadence decision on the new time
+  bool rec = advance && log_on;
+  long long idx = 0;
+  if (rec && pa.cadence > 0.0) {
+    idx = (long long)floor(c.t * pa.sc.t / pa.cadence);
+    rec = idx > c.last_sample;
+  }
+  if (rec) {
+    c.n_log += 1;
+    if (pa.cadence > 0.0) c.last_sample = idx;
+  }
+  return rec;
+}
+
+// One block: the reduction, the clock and, if probes are logged, a record.
+// reset: what a new state clears first (see RESET_*).
+template <typename R>
+__device__ __forceinline__ void finalize_run(DevClock* ck, const double* __restrict__ part,
+                                             int nblocks, double cfl, int advance, int log_on,
+                                             const ProbeArgs& pa, const R* __restrict__ u,
+                                             double* __restrict__ log, int reset = RESET_NONE) {
+  __shared__ double sh[4][4];
+  __shared__ int s_rec;
+  __shared__ long long s_row;
+  __shared__ double s_t;
+  const int tid = threadIdx.y * blockDim.x + threadIdx.x;
+  if (!ck->active && advance) return;  // the stage kernels did not run
+  double l, a1, a0;
+  int b;
+  reduce_partials(part, nblocks, l, a1, a0, b, sh);
   if (tid == 0) {
-    if (advance) {
-      ck->t = ck->clip ? ck->t_end : ck->t + ck->dt;
-      ck->step += 1;
-      ck->taken += 1;
-      ck->last_dt = ck->dt;
-      ck->resid = sqrt(a1) / sqrt(a0);
-      if (b != BAD_NONE) {
-        if (ck->bad == BAD_NONE || b < ck->bad) ck->bad = b;
-      }
+    DevClock c = *ck;
+    if (reset != RESET_NONE) {
+      c.bad = BAD_NONE;
+      c.counter = 0;
     }
-    set_next_dt(ck, cfl / l);
-    if (ck->bad != BAD_NONE) ck->active = 0;
-    // probe cadence decision on the new time
-    int rec = advance;
-    long long idx = 0;
-    if (rec && pa.cadence > 0.0) {
-      idx = (long long)floor(ck->t * pa.sc.t / pa.cadence);
-      rec = idx > ck->last_sample;
+    if (reset == RESET_RUN) {
+      c.t = 0.0;
+      c.step = 0;
+      c.last_dt = 0.0;
+      c.resid = 0.0;
     }
-    s_rec = log_on && rec;
-    s_row = ck->n_log;
-    s_idx = idx;
-    s_t = ck->t;
-    if (log_on && rec) {
-      ck->n_log += 1;
-      if (pa.cadence > 0.0) ck->last_sample = idx;
-    }
+    s_row = c.n_log;
+    s_rec = advance_clock(c, l, a1, a0, b, cfl, advance, log_on, pa);
+    s_t = c.t;
+    *ck = c;
   }
   __syncthreads();
   if (s_rec && s_row < pa.log_rows && tid < pa.n)
     probe_eval<R>(pa, u, tid, s_t, log + (s_row * pa.max_probes + tid) * 12);
 }
 
+// The end of a step and the boundary of the next one in a launch: every
+// block reduces the partials for itself (the same order, so the same clock)
+// from the clock as it was when the step began (ck[1], written by stage 1),
+// then forms its columns' inner-boundary primitives at the new times; block 0
+// also writes the clock and the probe record.
+template <typename R>
+__device__ __forceinline__ void end_step(DevClock* ck, const double* __restrict__ part, int nblocks,
+                                         double cfl, int log_on, const ProbeArgs& pa,
+                                         const R* __restrict__ u, double* __restrict__ log,
+                                         const BndArgs& bnd, R* __restrict__ g1,
+                                         R* __restrict__ g2, R* __restrict__ tg1,
+                                         R* __restrict__ tg2) {
+  __shared__ double sh[4][4];
+  __shared__ int s_rec, s_active;
+  __shared__ long long s_row;
+  __shared__ double s_t, s_dt;
+  if (!ck[1].active) return;  // the stage kernels did not run
+  double l, a1, a0;
+  int b;
+  reduce_partials(part, nblocks, l, a1, a0, b, sh);
+  if (threadIdx.x == 0) {
+    DevClock c = ck[1];
+    s_row = c.n_log;
+    s_rec = advance_clock(c, l, a1, a0, b, cfl, 1, log_on, pa);
+    s_t = c.t;
+    s_dt = c.dt;
+    s_active = c.active;
+    if (blockIdx.x == 0) ck[0] = c;
+  }
+  __syncthreads();
+  if (s_active)
+    boundary_column<R>(bnd, s_t, s_dt, blockIdx.x * blockDim.x + threadIdx.x, g1, g2, tg1, tg2);
+  if (blockIdx.x == 0 && s_rec && s_row < pa.log_rows && (int)threadIdx.x < pa.n)
+    probe_eval<R>(pa, u, threadIdx.x, s_t, log + (s_row * pa.max_probes + threadIdx.x) * 12);
+}
 
 }  // namespace icr
