@@ -82,3 +82,29 @@ def test_hlld_fp32_close_to_fp64(mods):
     a.close()
     b.close()
 
+
+
+@pytest.mark.parametrize("case", ["no field", "uniform", "slow"])
+def test_hlld_degenerate_waves(mods, case):
+    """The face-once flux where its branches meet: B = 0 (rotational waves on
+    the contact), equal columns (transverse jumps of zero) and a slow inflow
+    (radial faces inside the fan)."""
+    oracle = mods[0]
+    w = configs.tiny_static()
+    maps = np.array(w.maps, dtype=np.float64, copy=True)
+    if case == "no field":
+        maps[:, 5:] = 0.0
+    elif case == "uniform":
+        maps[:] = maps.mean(axis=(2, 3), keepdims=True)
+    else:
+        maps[:, 1] *= 0.05
+    say("HLLD degenerate waves:", case)
+    s, o = pair(mods, w.grid, w.times, maps)
+    s.step(30)
+    o.step(30)
+    a, b = s.get_state(kind=1), o.get_state(kind=oracle.CONS_CODE)
+    if case == "no field":
+        assert not a[5:].any() and not b[5:].any()
+        a[5:] = b[5:] = 1.0
+    parity.assert_parity(a, b)
+    s.close()
