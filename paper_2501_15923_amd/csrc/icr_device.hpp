@@ -216,12 +216,17 @@ __device__ __forceinline__ R limiter(R a, R b) {
 // the difference across it).  minmod(x, y) is the median of x, y and 0, i.e.
 // x clamped to [lo, hi]; MC / 2 = sign min(|x|, |y|, |x + y|/4) is (x + y)/4
 // clamped to the interval between 0 and that minmod.  Branch-free, and the
-// same values as the definitions above.
+// same values as the definitions above.  FP32 has a median instruction for
+// each clamp; FP64, which has none, takes the smaller magnitude with the
+// minmod's sign, two instructions where the second clamp took four (FP64 MC
+// stage 2281 -> 2153 instructions a cell; in FP32 that form costs 5 % more).
 template <typename R, int LIM>
 __device__ __forceinline__ R half_slope(R x, R y, R lo, R hi) {
   const R m = fmax(lo, fmin(x, hi));
   if (LIM == LIM_MINMOD) return R(0.5) * m;
-  return fmax(fmin(m, R(0)), fmin(R(0.25) * (x + y), fmax(m, R(0))));
+  const R c = R(0.25) * (x + y);
+  if constexpr (sizeof(R) == 8) return __builtin_copysign(fmin(fabs(m), fabs(c)), m);
+  return fmax(fmin(m, R(0)), fmin(c, fmax(m, R(0))));
 }
 
 // Face states from four consecutive cells (m-2, m-1, m, m+1) around face
