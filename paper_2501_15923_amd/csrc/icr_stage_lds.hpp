@@ -34,21 +34,6 @@ __device__ __forceinline__ void load_cons_prim(const StageArgs<R>& a, unsigned c
 
 __device__ __forceinline__ int wrap_phi(int k, int np) { return ((k % np) + np) % np; }
 
-// Face states of face m-1/2 from four LDS values per variable (p0..p3 =
-// cells m-2 .. m+1), then the numerical flux.
-template <typename R, int N, int FLUX, int LIM>
-__device__ __forceinline__ void lds_face(const R* base, int stride, R gam, R igm1, R (&f)[NV],
-                                         int vstride) {
-  R wl[NV], wr[NV];
-#pragma unroll
-  for (int v = 0; v < NV; ++v) {
-    const R* q = base + v * vstride;
-    const R p0 = q[0], p1 = q[stride], p2 = q[2 * stride], p3 = q[3 * stride];
-    face_states<R, LIM, true>(p0, p1, p2, p3, wl[v], wr[v]);
-  }
-  face_flux<R, N, FLUX, true>(wl, wr, gam, igm1, f);
-}
-
 // One tile (bx, by, bz) of one run: (TR - 4) x TT columns, planes
 // bz*kplanes ..; stage-2 partials go to slot pslot.  Called by the
 // single-run kernel and by the ensemble kernels, so both execute the same
@@ -60,9 +45,20 @@ __device__ __forceinline__ void lds_face(const R* base, int stride, R gam, R igm
 // to stage_tile: the compiler can then tell that the update's flux reads do
 // not touch the rows the stage-2 LDS-DMA copies are landing in, and does not
 // wait for those copies before them.
+// Rows of G variables lie side by side, G = 16 bytes / sizeof(R) variables
+// when a wave's halo copies are 16 bytes a lane (FP64), else 1: a copy
+// instruction then fills whole rows of the wave's own halo items.
 template <typename R, int TR, int TT>
 struct alignas(16) StageW {
-  R sW[NV][TT + 4][TR];
+  static constexpr int DW = sizeof(R) == 8 ? 16 : 4;  // bytes per lane and halo copy
+  static constexpr int G = DW / (int)sizeof(R);
+  static constexpr int RS = G * TR;  // values from a row to the next
+  R sW[NV / G][TT + 4][G][TR];
+  __device__ __forceinline__ R& at(int v, int row, int l) { return sW[v / G][row][v % G][l]; }
+  // offset of variable v from variable 0
+  static __device__ __forceinline__ constexpr int var(int v) {
+    return (v / G) * (TT + 4) * RS + (v % G) * TR;
+  }
 };
 template <typename R, int TR, int TT>
 struct alignas(16) StageF {
@@ -88,13 +84,20 @@ struct LdsCellMetric {
   __device__ __forceinline__ R ilth() const { return ilth_; }
 };
 
-// Stage-2 theta-halo copies: a halo region is the two rows on one side of
-// the tile (2 TR values of one variable, contiguous in LDS), copied by wave
-// instructions of 64 lanes x dw bytes (16 where a region is a multiple of
-// 1 KiB, else 4); instruction n of a plane covers chunk n % ipr of region
-// (n / ipr) % 2 of variable n / (2 ipr), and wave w issues n = w, w + nw,
-// ...  Each wave keeps the byte offsets of the first ppw of its (region,
-// chunk) pairs; this checks that they repeat with period ppw.
+// Face states of face m-1/2 from four LDS values per variable (p0..p3 =
+// cells m-2 .. m+1), then the numerical flux.
+template <typename R, int N, int FLUX, int LIM, typename W>
+__device__ __forceinline__ void lds_face(const R* base, int stride, R gam, R igm1, R (&f)[NV]) {
+  R wl[NV], wr[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const R* q = base + W::var(v);
+    const R p0 = q[0], p1 = q[stride], p2 = q[2 * stride], p3 = q[3 * stride];
+    face_states<R, LIM, true>(p0, p1, p2, p3, wl[v], wr[v]);
+  }
+  face_flux<R, N, FLUX, true>(wl, wr, gam, igm1, f);
+}
+
 // One LDS-DMA copy: every lane moves BYTES bytes from its own global
 // address to dst + BYTES * lane (dst is the same for the whole wave).
 template <int BYTES>
@@ -108,23 +111,13 @@ __device__ __forceinline__ void lds_dma(const char* src, char* dst) {
     __builtin_amdgcn_global_load_lds(g, l, 4, 0, 0);
 }
 
-constexpr bool dma_pairs_periodic(int nw, int ipr, int per_wave, int ppw) {
-  for (int w = 0; w < nw; ++w)
-    for (int m = 0; m < per_wave; ++m) {
-      const int n = w + nw * m, q = w + nw * (m % ppw);
-      if (n % ipr != q % ipr || (n / ipr) % 2 != (q / ipr) % 2) return false;
-    }
-  return true;
-}
-
 template <typename R, int TR, int TT, int FLUX, int LIM, int STAGE, bool FM = false>
 __device__ __forceinline__ void stage_tile(const StageArgs<R>& a, int kplanes, int bx, int by,
                                            int bz, int pslot, StageW<R, TR, TT>& smw,
                                            StageF<R, TR, TT>& smf) {
   constexpr int NT = TR * TT;
   constexpr int TI = tile_cells_r(TR);
-  constexpr int WT = TT + 4;
-  auto& sW = smw.sW;
+  using W = StageW<R, TR, TT>;
   auto& sFr = smf.sFr;
   auto& sFt = smf.sFt;
 
@@ -266,58 +259,45 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R>& a, int kplanes, i
     }
     if (hflip) flip_theta(w);
 #pragma unroll
-    for (int v = 0; v < NV; ++v) sW[v][hjj + 2][hl] = w[v];
+    for (int v = 0; v < NV; ++v) smw.at(v, hjj + 2, hl) = w[v];
   };
   R hraw[NV];
   if (PF && hv && k0 < kend) halo_raw(k0, hraw);
 
   // (the copies need n_r >= 2: a 16-byte copy takes two neighbouring cells
   // of a row; with fewer cells stage 2 loads its halo after the barrier)
-  constexpr int NW = NT / 64;                              // waves per block
-  constexpr int RB = 2 * TR * (int)sizeof(R);              // bytes of a halo region
-  constexpr int DW = RB % 1024 == 0 ? 16 : 4;              // bytes per lane and copy
-  constexpr int IPR = RB / (64 * DW) > 0 ? RB / (64 * DW) : 1;  // copies per region
-  constexpr int NINS = NV * 2 * IPR;                       // per plane
-  constexpr int PPW = 2 * IPR > NW ? 2 * IPR / NW : 1;     // (region, chunk) pairs per wave
-  constexpr int SPAN = DW / (int)sizeof(R) > 1 ? DW / (int)sizeof(R) : 1;  // cells per copy
-  static_assert(!DMA || (NT % 64 == 0 && RB % (64 * DW) == 0 && NINS % NW == 0 &&
-                         dma_pairs_periodic(NW, IPR, NINS / NW, PPW) && SPAN <= 2 &&
-                         tile_cells_r(TR) % 2 == 0),
+  // A wave copies exactly the cells its own lanes convert: an instruction
+  // moves G variables of the wave's 64 halo cells, whole rows of StageW.  So
+  // the wave's own wait is enough before the conversion, and no barrier.
+  constexpr int DW = W::DW, G = W::G;
+  static_assert(!DMA || (64 * DW == G * 64 * (int)sizeof(R) && 64 % TR == 0 && TR % 2 == 0 &&
+                         tile_cells_r(TR) % 2 == 0 && G <= 2),
                 "theta-halo DMA layout");
   const bool dma_on = DMA && nr >= 2;  // uniform
   const int wv = __builtin_amdgcn_readfirstlane(tid) >> 6;  // wave index (uniform)
-  unsigned doff[PPW];  // byte offset in a plane of this lane's dw bytes, per pair
+  const bool dma_wave = dma_on && wv < 4 * TR / 64;
+  const int drow = wv * (64 / TR) < 2 ? wv * (64 / TR) : TT + wv * (64 / TR);  // its first sW row
+  const char* dsrc = nullptr;  // of plane 0 and the first G variables
   if constexpr (DMA) {
-    const int lane = tid & 63;
-#pragma unroll
-    for (int p = 0; p < PPW; ++p) {
-      const int n = wv + NW * p;
-      const int c = n % IPR, reg = (n / IPR) % 2;
-      const int b = (c * 64 + lane) * DW;
-      const int e = b / (int)sizeof(R);  // first value of this lane's copy
-      const int rr = e / TR, l = e - rr * TR;
-      bool fl;
-      const int gj = mirror_row(j0 + (reg ? TT + rr : rr - 2), nt, fl);
-      // clamped into the row; a two-cell copy keeps both cells in the row
-      int gi = i0 + l - 2;
-      gi = gi < 0 ? 0 : (gi <= nr - SPAN ? gi : nr - SPAN);
-      doff[p] = (unsigned)(gj * nr + gi) * (unsigned)sizeof(R) + (unsigned)(b % (int)sizeof(R));
-    }
+    const int e = (tid & 63) * G;  // first value of this lane's copies
+    const int l = e % TR;
+    bool fl;
+    const int gj = mirror_row(j0 + drow + e / W::RS - 2, nt, fl);
+    // clamped into the row; a two-cell copy keeps both cells in the row
+    int gi = i0 + l - 2;
+    gi = gi < 0 ? 0 : (gi <= nr - G ? gi : nr - G);
+    dsrc = reinterpret_cast<const char*>(a.uin + (size_t)(e / TR % G) * a.ncell) +
+           (size_t)(unsigned)(gj * nr + gi) * sizeof(R);
   }
   auto dma_halo = [&](int k) {
-    const unsigned kb = (unsigned)k * plane_cells * (unsigned)sizeof(R);
+    const char* src = dsrc + (size_t)((unsigned)k * plane_cells) * sizeof(R);
 #pragma unroll
-    for (int m = 0; m < NINS / NW; ++m) {
-      const int n = wv + NW * m;
-      const int c = n % IPR, reg = (n / IPR) % 2, v = n / (2 * IPR);
-      const char* src = reinterpret_cast<const char*>(a.uin + (size_t)v * a.ncell) + kb +
-                        doff[m % PPW];
-      char* dst = reinterpret_cast<char*>(&sW[v][reg ? TT + 2 : 0][0]) + c * 64 * DW;
-      lds_dma<DW>(src, dst);
-    }
+    for (int m = 0; m < NV / G; ++m)
+      lds_dma<DW>(src + (size_t)(m * G) * a.ncell * sizeof(R),
+                  reinterpret_cast<char*>(&smw.at(m * G, drow, 0)));
   };
   if constexpr (DMA) {
-    if (dma_on && k0 < kend) dma_halo(k0);
+    if (dma_wave && k0 < kend) dma_halo(k0);
   }
 
   double lam = 0.0, s1 = 0.0, s0 = 0.0;
@@ -327,12 +307,14 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R>& a, int kplanes, i
     const bool body = k >= k0;  // uniform over the block
     const unsigned kbase = (unsigned)k * plane_cells;
     if (body) {
-      // stage 2: this wave's halo copies have landed (s_waitcnt vmcnt(0));
-      // the barrier then makes every wave's copies visible
+      // No barrier here: sW was last read by the previous plane's faces, all
+      // done before its second barrier, and the fluxes that a slower wave may
+      // still read are written again only after this plane's first barrier.
+      // stage 2: this wave's halo copies have landed (s_waitcnt vmcnt(0))
       if constexpr (DMA) {
         if (dma_on) __builtin_amdgcn_s_waitcnt(0x3f70);
+        asm volatile("" ::: "memory");
       }
-      __syncthreads();  // the previous plane's LDS reads are complete
       if (lghost) {  // inner ghost (primitives) at this lane's row
         R w[NV];
 #pragma unroll
@@ -345,10 +327,10 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R>& a, int kplanes, i
           w[7] = -wb[7];
         }
 #pragma unroll
-        for (int v = 0; v < NV; ++v) sW[v][tj + 2][ti] = w[v];
+        for (int v = 0; v < NV; ++v) smw.at(v, tj + 2, ti) = w[v];
       } else {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) sW[v][tj + 2][ti] = wb[v];
+        for (int v = 0; v < NV; ++v) smw.at(v, tj + 2, ti) = wb[v];
       }
       // theta halo: rows -2, -1, TT, TT + 1 over all TR lanes
       if constexpr (PF) {
@@ -363,18 +345,18 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R>& a, int kplanes, i
           // start being even): at the end of a row of odd length it was
           // shifted back into the row, so the even lane of the last cell got
           // its left neighbour; reload that one cell
-          if (SPAN == 2 && hgi == nr - 1 && (hl & 1) == 0 && hl >= 2 && hl < TR - 2) {
+          if (G == 2 && hgi == nr - 1 && (hl & 1) == 0 && hl >= 2 && hl < TR - 2) {
 #pragma unroll
             for (int v = 0; v < NV; ++v)
               u[v] = ldg(a.uin + v * a.ncell, kbase + (unsigned)(hgj * nr + hgi));
           } else {
 #pragma unroll
-            for (int v = 0; v < NV; ++v) u[v] = sW[v][hjj + 2][hl];
+            for (int v = 0; v < NV; ++v) u[v] = smw.at(v, hjj + 2, hl);
           }
           cons2prim<R, true>(u, w, a.gm1);
           if (hflip) flip_theta(w);
 #pragma unroll
-          for (int v = 0; v < NV; ++v) sW[v][hjj + 2][hl] = w[v];
+          for (int v = 0; v < NV; ++v) smw.at(v, hjj + 2, hl) = w[v];
         }
       } else {
         for (int h = tid; h < 4 * TR; h += NT) {
@@ -393,7 +375,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R>& a, int kplanes, i
           }
           if (flip) flip_theta(w);
 #pragma unroll
-          for (int v = 0; v < NV; ++v) sW[v][jj + 2][l] = w[v];
+          for (int v = 0; v < NV; ++v) smw.at(v, jj + 2, l) = w[v];
         }
       }
       __syncthreads();
@@ -402,23 +384,22 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R>& a, int kplanes, i
       // face, and the theta faces of the inner lanes; the others are never
       // read, and lanes 0, 1 and TR-1 read neighbouring LDS rows for their
       // r face), then the tile's upper theta face of every inner lane
-      constexpr int VS = WT * TR;
       {
         R f[NV];
-        lds_face<R, 1, FLUX, LIM>(&sW[0][tj + 2][ti] - 2, 1, a.gam, a.igm1, f, VS);
+        lds_face<R, 1, FLUX, LIM, W>(&smw.at(0, tj + 2, ti) - 2, 1, a.gam, a.igm1, f);
 #pragma unroll
         for (int v = 0; v < NV; ++v) sFr[v][tj][ti] = f[v];
       }
       {
         R f[NV];
-        lds_face<R, 2, FLUX, LIM>(&sW[0][tj][ti], TR, a.gam, a.igm1, f, VS);
+        lds_face<R, 2, FLUX, LIM, W>(&smw.at(0, tj, ti), W::RS, a.gam, a.igm1, f);
 #pragma unroll
         for (int v = 0; v < NV; ++v) sFt[v][tj][ti] = f[v];
       }
       for (int q = tid - 64; q >= 0 && q < TR; q += NT - 64) {
         if (q >= 2 && q < TR - 2) {
           R f[NV];
-          lds_face<R, 2, FLUX, LIM>(&sW[0][TT][q], TR, a.gam, a.igm1, f, VS);
+          lds_face<R, 2, FLUX, LIM, W>(&smw.at(0, TT, q), W::RS, a.gam, a.igm1, f);
 #pragma unroll
           for (int v = 0; v < NV; ++v) sFt[v][TT][q] = f[v];
         }
@@ -452,7 +433,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R>& a, int kplanes, i
     if (body) {
       __syncthreads();  // r / theta face fluxes are in LDS
       if constexpr (DMA) {
-        if (dma_on && k + 1 < kend) dma_halo(k + 1);  // in flight during this update
+        if (dma_wave && k + 1 < kend) dma_halo(k + 1);  // in flight during this update
       }
       if (valid) {
         const R r0 = cm.r(MR_RM2), r1 = cm.r(MR_RP2), hr = cm.r(MR_HR);

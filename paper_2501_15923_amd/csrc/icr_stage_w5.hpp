@@ -164,7 +164,9 @@ __device__ __forceinline__ void stage_tile_w5(const StageArgs<R>& a, int kplanes
     const bool body = k >= k0;  // uniform over the block
     const unsigned kbase = (unsigned)k * plane_cells;
     if (body) {
-      __syncthreads();  // the previous plane's LDS reads are complete
+      // No barrier here: sW was last read by the previous plane's edge values,
+      // all formed before its second barrier, and the fluxes that a slower
+      // wave may still read are written again only after this plane's first.
       if (lghost) {  // inner ghost (primitives), the same in every layer
         R w[NV];
 #pragma unroll
