@@ -249,6 +249,22 @@ __device__ __forceinline__ void face_states(R a, R b, R c, R d, R& wl, R& wr) {
     wr = c - R(0.5) * limiter<R, LIM>(dc, dd);
   }
 }
+// A cell's states at its lower and upper face from its value w and the
+// differences x (to the cell below) and y (to the cell above): the values
+// face_states gives its two faces.
+template <typename R, int LIM>
+__device__ __forceinline__ void cell_states(R w, R x, R y, R& dn, R& up) {
+  const R lo = fmin(y, R(0)), hi = fmax(y, R(0));
+  if (LIM == LIM_MINMOD) {
+    const R m = fmax(lo, fmin(x, hi));
+    dn = fma_(R(-0.5), m, w);
+    up = fma_(R(0.5), m, w);
+  } else {
+    const R h = half_slope<R, LIM>(x, y, lo, hi);
+    dn = w - h;
+    up = w + h;
+  }
+}
 template <typename R, int LIM, bool FAST = false>
 __device__ __forceinline__ void reconstruct(const R (&a)[NV], const R (&b)[NV],
                                             const R (&c)[NV], const R (&d)[NV],
