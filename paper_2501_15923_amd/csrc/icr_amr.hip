@@ -961,7 +961,7 @@ __global__ void __launch_bounds__(256) k_amr_init(AmrArgs a, const LeafDesc* __r
     const double rc = L.m.rc[i];
     const double x = a.r_in / rc;
     const double sth = sin(L.m64[OFF_TC64(L.nr, L.nt) + j]);
-    const long long q = (long long)j * a.bnd.np + k;
+    const long long q = (long long)k * a.bnd.nt + j;
     double w[NV];
     w[0] = a.bnd.maps[0 * plane + q] * x * x;
     w[1] = a.bnd.maps[1 * plane + q];
@@ -1670,7 +1670,8 @@ int icr_amr_set_boundary_maps(icr_amr* a, int n, const double* t_s, const double
         const double x = maps[((size_t)m * NV + v) * plane + qq];
         if ((v == 0 || v == 4) && !(x > 0.0)) return err(ICR_ERR_ARG, "map rho or p <= 0");
         if (!std::isfinite(x)) return err(ICR_ERR_ARG, "map has a non-finite value");
-        h[((size_t)m * NV + v) * plane + qq] = x / sc[v];
+        h[((size_t)m * NV + v) * plane + qq % a->g.n_phi * a->g.n_theta + qq / a->g.n_phi] =
+            x / sc[v];
       }
   std::vector<double> tau(n);
   for (int m = 0; m < n; ++m) tau[m] = t_s[m] / a->t_unit;

@@ -668,27 +668,29 @@ int icr_grid_edges(const icr_solver* s, double* r, double* t, double* ph) {
 }
 
 namespace {
-// Copy n SI maps [n][8][nt][np] (host or device) into h in code units,
-// checking rho > 0, p > 0 and finiteness.
+// Copy n SI maps [n][8][nt][np] (host or device) into h [n][8][np][nt] in code
+// units, checking rho > 0, p > 0 and finiteness.
 int stage_maps(icr_solver* s, int n, const double* maps, int on_device, std::vector<double>& h) {
   const size_t plane = (size_t)s->g.n_theta * s->g.n_phi;
   h.resize((size_t)n * NV * plane);
+  std::vector<double> copy;
   if (on_device) {
-    HIP_TRY(hipMemcpyAsync(h.data(), maps, h.size() * sizeof(double), hipMemcpyDeviceToHost,
+    copy.resize(h.size());
+    HIP_TRY(hipMemcpyAsync(copy.data(), maps, h.size() * sizeof(double), hipMemcpyDeviceToHost,
                            s->stream));
     HIP_TRY(hipStreamSynchronize(s->stream));
-  } else {
-    std::memcpy(h.data(), maps, h.size() * sizeof(double));
+    maps = copy.data();
   }
+  const size_t nt = s->g.n_theta, np = s->g.n_phi;
   const Scale sc = s->un.scale();
   for (int m = 0; m < n; ++m)
     for (int v = 0; v < NV; ++v)
       for (size_t q = 0; q < plane; ++q) {
-        double& x = h[((size_t)m * NV + v) * plane + q];
+        const double x = maps[((size_t)m * NV + v) * plane + q];
         if ((v == 0 || v == 4) && !(x > 0.0))
           return fail(ICR_ERR_ARG, "map %d has %s <= 0 at point %zu", m, v ? "p" : "rho", q);
         if (!std::isfinite(x)) return fail(ICR_ERR_ARG, "map %d has a non-finite value", m);
-        x /= sc.s[v];
+        h[((size_t)m * NV + v) * plane + q % np * nt + q / np] = x / sc.s[v];
       }
   return ICR_OK;
 }
@@ -1355,7 +1357,7 @@ int ens_upload(icr_ensemble* e) {
       std::memcpy(host.data() + sizeof(RunDesc<double>) * r, &d, sizeof d);
       toff[r + 1] = toff[r] + d.nbx * d.nby * d.nbz;
     }
-    boff[r + 1] = boff[r] + (s->g.n_theta * s->g.n_phi + 255) / 256;
+    boff[r + 1] = boff[r] + boundary_blocks(s->g.n_theta, s->g.n_phi);
     coff[r + 1] = coff[r] + (s->trc() ? (int)((s->ncell() + 255) / 256) : 0);
   }
   e->n_tiles = toff[n];

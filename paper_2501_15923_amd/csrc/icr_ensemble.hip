@@ -71,8 +71,8 @@ __device__ __forceinline__ void bnd_item(const RunDesc<R>* runs, const EnsTables
   const RunDesc<R>& rd = runs[r];
   const int tid = threadIdx.y * blockDim.x + threadIdx.x;
   if (!rd.clock->active) return;
-  boundary_column<R>(rd.bnd, rd.clock->t, rd.clock->dt, (item - e.bnd_off[r]) * 256 + tid,
-                     rd.ghost0, rd.ghost1, rd.tghost0, rd.tghost1);
+  boundary_block<R>(rd.bnd, rd.clock->t, rd.clock->dt, item - e.bnd_off[r], tid, rd.ghost0,
+                    rd.ghost1, rd.tghost0, rd.tghost1);
 }
 
 // Tracer item: 256 cells of one run, after that run's stage tiles.

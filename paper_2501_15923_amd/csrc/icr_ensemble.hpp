@@ -34,7 +34,7 @@ struct RunDesc {
 struct EnsTables {
   int n_runs;
   int n_tiles;          // stage tiles over all runs
-  int n_bitems;         // boundary items of 256 columns over all runs
+  int n_bitems;         // boundary items (256 columns, one time) over all runs
   int n_titems;         // tracer items of 256 cells over all runs (0: tracer off)
   const int* tile_off;  // [n_runs + 1] prefix sums of tiles
   const int* bnd_off;   // [n_runs + 1] prefix sums of boundary items

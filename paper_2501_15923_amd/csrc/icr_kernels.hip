@@ -95,7 +95,7 @@ template <typename R>
 __global__ void k_boundary(BndArgs a, const DevClock* __restrict__ ck, R* __restrict__ g1,
                            R* __restrict__ g2, R* __restrict__ tg1, R* __restrict__ tg2) {
   if (!ck->active) return;
-  boundary_column<R>(a, ck->t, ck->dt, blockIdx.x * blockDim.x + threadIdx.x, g1, g2, tg1, tg2);
+  boundary_block<R>(a, ck->t, ck->dt, blockIdx.x, threadIdx.x, g1, g2, tg1, tg2);
 }
 
 // The clock of a new call: its end time and step count, the next dt.  Fields
@@ -127,7 +127,7 @@ __global__ void __launch_bounds__(256) k_begin(BndArgs a, DevClock* ck, double t
     ck->clip = c.clip;
   }
   if (c.active)
-    boundary_column<R>(a, c.t, c.dt, blockIdx.x * blockDim.x + threadIdx.x, g1, g2, tg1, tg2);
+    boundary_block<R>(a, c.t, c.dt, blockIdx.x, threadIdx.x, g1, g2, tg1, tg2);
 }
 
 // Boundary at an arbitrary time into a [8][nt][np] double buffer (SI).
@@ -143,8 +143,7 @@ __global__ void k_boundary_at(BndArgs a, double t, double* __restrict__ out, Sca
 
 void launch_boundary(const BndArgs& a, const DevClock* ck, void* g1, void* g2, void* tg1,
                      void* tg2, bool f32, hipStream_t s) {
-  const int plane = a.nt * a.np;
-  const dim3 grid((plane + 255) / 256), blk(256);
+  const dim3 grid(boundary_blocks(a.nt, a.np)), blk(256);
   if (f32)
     hipLaunchKernelGGL(k_boundary<float>, grid, blk, 0, s, a, ck, (float*)g1, (float*)g2,
                        (float*)tg1, (float*)tg2);
@@ -155,7 +154,7 @@ void launch_boundary(const BndArgs& a, const DevClock* ck, void* g1, void* g2, v
 
 void launch_begin(const BndArgs& a, DevClock* ck, double t_end, void* g1, void* g2, void* tg1,
                   void* tg2, bool f32, hipStream_t s) {
-  const dim3 grid((a.nt * a.np + 255) / 256), blk(256);
+  const dim3 grid(boundary_blocks(a.nt, a.np)), blk(256);
   if (f32)
     hipLaunchKernelGGL(k_begin<float>, grid, blk, 0, s, a, ck, t_end, (float*)g1, (float*)g2,
                        (float*)tg1, (float*)tg2);
@@ -415,7 +414,7 @@ __global__ void __launch_bounds__(256) k_init_radial(StageArgs<R> a, BndArgs b,
     const int j = (int)((c / nr) % b.nt);
     const int k = (int)(c / ((long long)nr * b.nt));
     const long long plane = (long long)b.nt * b.np;
-    const long long q = (long long)j * b.np + k;
+    const long long q = (long long)k * b.nt + j;
     const double rc = m64[8 * nr + i];
     const double x = b.r_in / rc;
     const double sth = sin(b.tc[j]);

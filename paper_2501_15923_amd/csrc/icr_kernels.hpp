@@ -50,7 +50,7 @@ struct BndArgs {
   int nt, np;
   int n_maps;
   const double* tau;   // [n_maps] code time
-  const double* maps;  // [n_maps][8][nt][np] code primitive
+  const double* maps;  // [n_maps][8][np][nt] code primitive: theta fastest, as the ghosts
   int n_cme;
   const double* cme;   // [n][8]: t0, dur, colat, lon, cos(hw), v, rho, p (code)
   const double* tc;    // [nt] colatitude centres
@@ -333,7 +333,7 @@ __device__ inline void boundary_prim(const BndArgs& a, double t, int j, int k, d
                                      int* inside = nullptr) {
   if (inside) *inside = 0;
   const long long plane = (long long)a.nt * a.np;
-  const long long q = (long long)j * a.np + k;
+  const long long q = (long long)k * a.nt + j;
   const int n = a.n_maps;
   if (n == 1 || t <= a.tau[0]) {
     for (int v = 0; v < NV; ++v) w[v] = a.maps[v * plane + q];
@@ -353,12 +353,12 @@ __device__ inline void boundary_prim(const BndArgs& a, double t, int j, int k, d
     }
   }
   if (a.n_cme > 0) {
-    const double th = a.tc[j];
-    const double ph = (k + 0.5) * a.dph;
-    const double sth = sin(th), cth = cos(th);
     for (int c = 0; c < a.n_cme; ++c) {
       const double* m = a.cme + 8 * c;  // t0, dur, colat, lon, cos(hw), v, rho, p
       if (!(t >= m[0] && t < m[0] + m[1])) continue;
+      const double th = a.tc[j];
+      const double ph = (k + 0.5) * a.dph;
+      const double sth = sin(th), cth = cos(th);
       const double cosd = cth * cos(m[2]) + sth * sin(m[2]) * cos(ph - m[3]);
       if (cosd >= m[4]) {
         if (inside) *inside = 1;
@@ -372,26 +372,33 @@ __device__ inline void boundary_prim(const BndArgs& a, double t, int j, int k, d
   }
 }
 
-// Inner-boundary primitives of column q (= k * nt + j) at the two stage times
-// t and t + dt; tg1 / tg2 (with the tracer): 1 inside an inserted cone.
+// Inner-boundary primitives at the two stage times t and t + dt, one column
+// and time a thread: block b of 256 threads forms the columns of b / 2 at the
+// time of b % 2 (tg1 / tg2, with the tracer: 1 inside an inserted cone).
+// Bound by the latency of the chain time -> map -> values: the columns of a
+// wave lie side by side in the maps, and no thread forms both times.  The end
+// of a step at 600 x 60 x 120 with 10 maps took 16.3 us with maps of phi
+// fastest and both times in one thread, 12.2 us so; 64 x 16 x 32 with one map
+// 5.9 and 4.4 us.  (Comparing 12 map times at once instead of halving the
+// interval gave nothing.)
+constexpr int BND_TIMES = 2;
+__host__ __device__ constexpr int boundary_blocks(int nt, int np) {
+  return BND_TIMES * ((nt * np + 255) / 256);
+}
 template <typename R>
-__device__ __forceinline__ void boundary_column(const BndArgs& a, double t, double dt, int q,
-                                                R* __restrict__ g1, R* __restrict__ g2,
-                                                R* __restrict__ tg1, R* __restrict__ tg2) {
-  const int plane = a.nt * a.np;
+__device__ __forceinline__ void boundary_block(const BndArgs& a, double t, double dt, int b,
+                                               int tid, R* __restrict__ g1, R* __restrict__ g2,
+                                               R* __restrict__ tg1, R* __restrict__ tg2) {
+  const int plane = a.nt * a.np, q = b / BND_TIMES * 256 + tid;
   if (q >= plane) return;
-  const int j = q % a.nt, k = q / a.nt;
+  const bool second = b % BND_TIMES != 0;
   double w[NV];
-  int in1, in2;
-  boundary_prim(a, t, j, k, w, &in1);
-  for (int v = 0; v < NV; ++v) g1[(long long)v * plane + q] = (R)w[v];
-  boundary_prim(a, t + dt, j, k, w, &in2);
-  for (int v = 0; v < NV; ++v) g2[(long long)v * plane + q] = (R)w[v];
+  int in;
+  boundary_prim(a, second ? t + dt : t, q % a.nt, q / a.nt, w, &in);
+  R* g = second ? g2 : g1;
+  for (int v = 0; v < NV; ++v) g[(long long)v * plane + q] = (R)w[v];
   // tracer of the inner ghost cells: CME material inside an inserted cone
-  if (tg1) {
-    tg1[q] = (R)in1;
-    tg2[q] = (R)in2;
-  }
+  if (tg1) (second ? tg2 : tg1)[q] = (R)in;
 }
 
 template <typename R>

@@ -157,7 +157,7 @@ template <typename R>
 void launch_step_end(DevClock* ck, const double* part, int nblocks, double cfl, int log_on,
                      const ProbeArgs& pa, const void* u, double* log, const BndArgs& bnd,
                      void* g1, void* g2, void* tg1, void* tg2, hipStream_t s) {
-  const int blocks = (bnd.nt * bnd.np + 255) / 256;
+  const int blocks = boundary_blocks(bnd.nt, bnd.np);
   hipLaunchKernelGGL(k_step_end<R>, dim3(blocks), dim3(256), 0, s, ck, part, nblocks, cfl, log_on,
                      pa, (const R*)u, log, bnd, (R*)g1, (R*)g2, (R*)tg1, (R*)tg2);
 }

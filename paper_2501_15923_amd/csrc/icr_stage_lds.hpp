@@ -632,7 +632,7 @@ __device__ __forceinline__ void end_step(DevClock* ck, const double* __restrict_
   }
   __syncthreads();
   if (s_active)
-    boundary_column<R>(bnd, s_t, s_dt, blockIdx.x * blockDim.x + threadIdx.x, g1, g2, tg1, tg2);
+    boundary_block<R>(bnd, s_t, s_dt, blockIdx.x, threadIdx.x, g1, g2, tg1, tg2);
   if (blockIdx.x == 0 && s_rec && s_row < pa.log_rows && (int)threadIdx.x < pa.n)
     probe_eval<R>(pa, u, threadIdx.x, s_t, log + (s_row * pa.max_probes + threadIdx.x) * 12);
 }
