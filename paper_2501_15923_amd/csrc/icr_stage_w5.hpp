@@ -203,6 +203,7 @@ __device__ __forceinline__ void stage_tile_w5(const StageArgs<R>& a, int kplanes
 #pragma unroll
         for (int v = 0; v < NV; ++v) sW[v][jj + H][l] = w[v];
       }
+      __builtin_amdgcn_s_setprio(0);
       __syncthreads();
       constexpr int VS = WT * TR;
       {
@@ -331,6 +332,7 @@ __device__ __forceinline__ void stage_tile_w5(const StageArgs<R>& a, int kplanes
     }
     if (body) {
       __syncthreads();  // r / theta face fluxes are in LDS
+      __builtin_amdgcn_s_setprio(2);  // until this block's next rows are in LDS
       if (valid) {
         const R ivr = ldg(a.m.ivr, ic), r0 = ldg(a.m.rm2, ic) * ivr, r1 = ldg(a.m.rp2, ic) * ivr;
         const R hr = ldg(a.m.hr, ic), hc = hr * ldg(a.m.ict, jc);
