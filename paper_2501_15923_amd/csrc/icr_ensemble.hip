@@ -38,17 +38,25 @@ __device__ bool grid_sync(GridBar* gb, unsigned nblocks, long long spin_limit) {
   __syncthreads();
   if (threadIdx.x == 0 && threadIdx.y == 0) {
     ok = 1;
-    const unsigned g = __hip_atomic_load(&gb->gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned grp = blockIdx.x % NXCD, ngrp = nblocks < NXCD ? nblocks : NXCD;
+    const unsigned members = (nblocks - grp + NXCD - 1) / NXCD;
+    GridBar::Line& mine = gb->group[grp];
+    const unsigned g = __hip_atomic_load(&mine.gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // release this block's writes (L2 write-back), then arrive
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    const unsigned arrived = atomicAdd(&gb->count, 1u);
-    if (arrived == nblocks - 1) {
-      __hip_atomic_store(&gb->count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-      atomicAdd(&gb->gen, 1u);
+    bool last = atomicAdd(&mine.count, 1u) == members - 1;
+    if (last) {
+      __hip_atomic_store(&mine.count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "agent");
+      last = atomicAdd(&gb->all.count, 1u) == ngrp - 1;
+    }
+    if (last) {
+      __hip_atomic_store(&gb->all.count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "agent");
+      for (unsigned y = 0; y < ngrp; ++y) atomicAdd(&gb->group[y].gen, 1u);
     } else {
       long long n = 0;
-      while (__hip_atomic_load(&gb->gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == g) {
+      while (__hip_atomic_load(&mine.gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == g) {
         __builtin_amdgcn_s_sleep(32);  // ~2000 cycles between polls of the shared line
         if (++n > spin_limit) {
           atomicExch(&gb->error, 1);

@@ -5,11 +5,17 @@
 
 namespace icr {
 
+// Blocks arrive in groups (block b in group b % NXCD), the last of a group
+// arrives for it, and every group has its own line to wait on: device-wide
+// atomics on one address are served one after the other.
 struct GridBar {
-  unsigned count;  // blocks arrived at the current barrier
-  unsigned gen;    // barrier generation
-  int error;       // 1: a bounded wait expired (a block was not resident)
-  int pad;
+  struct alignas(128) Line {
+    unsigned count;  // arrivals at the current barrier
+    unsigned gen;    // barrier generation (groups)
+  };
+  Line group[NXCD];
+  Line all;   // groups arrived
+  int error;  // 1: a bounded wait expired (a block was not resident)
 };
 
 // One run of the ensemble: stage arguments for both parities of the source
