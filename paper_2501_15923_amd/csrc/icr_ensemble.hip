@@ -1,11 +1,11 @@
 // icr_ensemble.hip -- batched ensemble of uneven runs on one GPU.
 //
 // Every run is a full solver (own grid, metric, maps, cone CMEs, clock and
-// CFL dt).  One step of the ensemble walks four work lists that span all
-// runs: boundary columns, stage-1 tiles, stage-2 tiles and one finalize per
-// run.  The persistent kernel executes n steps in a single launch with a
-// device-wide barrier between the lists; the batched mode launches one
-// kernel per list.  Both run the same tile code as the single-run kernels,
+// CFL dt).  One step of the ensemble walks three work lists that span all
+// runs: stage-1 tiles, stage-2 tiles and the step's end with the next step's
+// boundary columns (the first boundary of a launch is a list of its own).  The
+// persistent kernel executes n steps in a single launch with a device-wide
+// barrier between the lists; the batched mode launches one kernel per list.  Both run the same tile code as the single-run kernels,
 // so each run's state is bit-identical to stepping it alone.
 #include "icr_ensemble.hpp"
 
@@ -83,6 +83,12 @@ __device__ __forceinline__ void bnd_item(const RunDesc<R>* runs, const EnsTables
                     rd.ghost1, rd.tghost0, rd.tghost1);
 }
 
+// The clock a run's step began with, for the items that end it.
+template <int STAGE>
+__device__ __forceinline__ void keep_clock(DevClock* ck, int local) {
+  if (STAGE == 1 && local == 0 && threadIdx.x == 0 && threadIdx.y == 0) ck[1] = ck[0];
+}
+
 // Tracer item: 256 cells of one run, after that run's stage tiles.
 template <typename R, int STAGE>
 __device__ __forceinline__ void trc_item(const RunDesc<R>* runs, const EnsTables& e, int item,
@@ -104,6 +110,7 @@ __device__ __forceinline__ void stage_item(const RunDesc<R>* runs, const EnsTabl
   const int local = item - e.tile_off[r];
   const int par = (rd.par + step) & 1;
   const int bx = local % rd.nbx, by = (local / rd.nbx) % rd.nby, bz = local / (rd.nbx * rd.nby);
+  keep_clock<STAGE>(rd.clock, local);
   stage_tile<R, 64, 4, FLUX, LIM, STAGE, FM>(STAGE == 1 ? rd.s1[par] : rd.s2[par], rd.planes, bx,
                                              by, bz, local, smw, smf);
 }
@@ -117,16 +124,21 @@ __device__ __forceinline__ void stage_item_w5(const RunDesc<R>* runs, const EnsT
   const int local = item - e.tile_off[r];
   const int par = (rd.par + step) & 1;
   const int bx = local % rd.nbx, by = (local / rd.nbx) % rd.nby, bz = local / (rd.nbx * rd.nby);
+  keep_clock<STAGE>(rd.clock, local);
   stage_tile_w5<R, FLUX, STAGE>(STAGE == 1 ? rd.s1[par] : rd.s2[par], rd.planes, bx, by, bz,
                                 local, sm);
 }
 
+// The end of a step and a part of the run's next boundary (see end_step).
 template <typename R>
-__device__ __forceinline__ void fin_item(const RunDesc<R>* runs, int r) {
+__device__ __forceinline__ void end_item(const RunDesc<R>* runs, const EnsTables& e, int item) {
+  const int r = find_run(e.bnd_off, e.n_runs, item);
   const RunDesc<R>& rd = runs[r];
   ProbeArgs none{};
-  finalize_run<R>(rd.clock, rd.partials, rd.nbx * rd.nby * rd.nbz, rd.cfl, 1, 0, none,
-                  (const R*)nullptr, nullptr);
+  __syncthreads();  // the previous item's shared clock has been read
+  end_step<R>(item - e.bnd_off[r], rd.clock, rd.partials, rd.nbx * rd.nby * rd.nbz, rd.cfl, 0,
+              none, (const R*)nullptr, nullptr, rd.bnd, rd.ghost0, rd.ghost1, rd.tghost0,
+              rd.tghost1);
 }
 
 // FM: the passive tracer is on (stage tiles keep their face mass fluxes, a
@@ -137,9 +149,9 @@ k_ensemble(const RunDesc<R>* __restrict__ runs, EnsTables e, int nsteps) {
   const unsigned G = gridDim.x;
   __shared__ StageW<R, 64, 4> smw;
   __shared__ StageF<R, 64, 4> smf;
+  for_items(e.n_bitems, [&](int it) { bnd_item<R>(runs, e, it); });
+  if (!grid_sync(e.bar, G, e.spin_limit)) return;
   for (int s = 0; s < nsteps; ++s) {
-    for_items(e.n_bitems, [&](int it) { bnd_item<R>(runs, e, it); });
-    if (!grid_sync(e.bar, G, e.spin_limit)) return;
     for_items(e.n_tiles, [&](int it) { stage_item<R, FLUX, LIM, 1, FM>(runs, e, it, s, smw, smf); });
     if (!grid_sync(e.bar, G, e.spin_limit)) return;
     if constexpr (FM) {
@@ -152,7 +164,7 @@ k_ensemble(const RunDesc<R>* __restrict__ runs, EnsTables e, int nsteps) {
       for_items(e.n_titems, [&](int it) { trc_item<R, 2>(runs, e, it, s); });
       if (!grid_sync(e.bar, G, e.spin_limit)) return;
     }
-    for_items(e.n_runs, [&](int r) { fin_item<R>(runs, r); });
+    for_items(e.n_bitems, [&](int it) { end_item<R>(runs, e, it); });
     if (!grid_sync(e.bar, G, e.spin_limit)) return;
   }
 }
@@ -162,14 +174,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 k_ensemble_w5(const RunDesc<R>* __restrict__ runs, EnsTables e, int nsteps) {
   const unsigned G = gridDim.x;
   __shared__ StageW5<R> sm;
+  for_items(e.n_bitems, [&](int it) { bnd_item<R>(runs, e, it); });
+  if (!grid_sync(e.bar, G, e.spin_limit)) return;
   for (int s = 0; s < nsteps; ++s) {
-    for_items(e.n_bitems, [&](int it) { bnd_item<R>(runs, e, it); });
-    if (!grid_sync(e.bar, G, e.spin_limit)) return;
     for_items(e.n_tiles, [&](int it) { stage_item_w5<R, FLUX, 1>(runs, e, it, s, sm); });
     if (!grid_sync(e.bar, G, e.spin_limit)) return;
     for_items(e.n_tiles, [&](int it) { stage_item_w5<R, FLUX, 2>(runs, e, it, s, sm); });
     if (!grid_sync(e.bar, G, e.spin_limit)) return;
-    for_items(e.n_runs, [&](int r) { fin_item<R>(runs, r); });
+    for_items(e.n_bitems, [&](int it) { end_item<R>(runs, e, it); });
     if (!grid_sync(e.bar, G, e.spin_limit)) return;
   }
 }
@@ -199,8 +211,8 @@ __global__ void __launch_bounds__(256) k_ens_trc(const RunDesc<R>* __restrict__ 
   for_items(e.n_titems, [&](int it) { trc_item<R, STAGE>(runs, e, it, step); });
 }
 template <typename R>
-__global__ void __launch_bounds__(256) k_ens_fin(const RunDesc<R>* __restrict__ runs, EnsTables e) {
-  for_items(e.n_runs, [&](int r) { fin_item<R>(runs, r); });
+__global__ void __launch_bounds__(256) k_ens_end(const RunDesc<R>* __restrict__ runs, EnsTables e) {
+  for_items(e.n_bitems, [&](int it) { end_item<R>(runs, e, it); });
 }
 
 __global__ void k_ens_clock_begin(DevClock* const* __restrict__ clocks, int n, double t_end) {
@@ -229,15 +241,15 @@ static void ens_launch(const EnsLaunch& L, hipStream_t s) {
     return;
   }
   auto items = [](int n) { return dim3((unsigned)((n + NXCD - 1) / NXCD * NXCD)); };
+  hipLaunchKernelGGL(k_ens_bnd<R>, items(L.e.n_bitems), blk, 0, s, runs, L.e);
   for (int q = 0; q < L.nsteps; ++q) {
-    hipLaunchKernelGGL(k_ens_bnd<R>, items(L.e.n_bitems), blk, 0, s, runs, L.e);
     hipLaunchKernelGGL((k_ens_stage<R, FLUX, LIM, 1, FM>), items(L.e.n_tiles), blk, 0, s, runs,
                        L.e, q);
     if (FM) hipLaunchKernelGGL((k_ens_trc<R, 1>), items(L.e.n_titems), blk, 0, s, runs, L.e, q);
     hipLaunchKernelGGL((k_ens_stage<R, FLUX, LIM, 2, FM>), items(L.e.n_tiles), blk, 0, s, runs,
                        L.e, q);
     if (FM) hipLaunchKernelGGL((k_ens_trc<R, 2>), items(L.e.n_titems), blk, 0, s, runs, L.e, q);
-    hipLaunchKernelGGL(k_ens_fin<R>, items(L.e.n_runs), blk, 0, s, runs, L.e);
+    hipLaunchKernelGGL(k_ens_end<R>, items(L.e.n_bitems), blk, 0, s, runs, L.e);
   }
 }
 
@@ -250,11 +262,11 @@ static void ens_launch_w5(const EnsLaunch& L, hipStream_t s) {
     return;
   }
   auto items = [](int n) { return dim3((unsigned)((n + NXCD - 1) / NXCD * NXCD)); };
+  hipLaunchKernelGGL(k_ens_bnd<R>, items(L.e.n_bitems), blk, 0, s, runs, L.e);
   for (int q = 0; q < L.nsteps; ++q) {
-    hipLaunchKernelGGL(k_ens_bnd<R>, items(L.e.n_bitems), blk, 0, s, runs, L.e);
     hipLaunchKernelGGL((k_ens_stage_w5<R, FLUX, 1>), items(L.e.n_tiles), blk, 0, s, runs, L.e, q);
     hipLaunchKernelGGL((k_ens_stage_w5<R, FLUX, 2>), items(L.e.n_tiles), blk, 0, s, runs, L.e, q);
-    hipLaunchKernelGGL(k_ens_fin<R>, items(L.e.n_runs), blk, 0, s, runs, L.e);
+    hipLaunchKernelGGL(k_ens_end<R>, items(L.e.n_bitems), blk, 0, s, runs, L.e);
   }
 }
 

@@ -150,7 +150,7 @@ __global__ void __launch_bounds__(256) k_step_end(DevClock* ck, const double* __
                                                   double* __restrict__ log, BndArgs bnd,
                                                   R* __restrict__ g1, R* __restrict__ g2,
                                                   R* __restrict__ tg1, R* __restrict__ tg2) {
-  end_step<R>(ck, part, nblocks, cfl, log_on, pa, u, log, bnd, g1, g2, tg1, tg2);
+  end_step<R>(blockIdx.x, ck, part, nblocks, cfl, log_on, pa, u, log, bnd, g1, g2, tg1, tg2);
 }
 
 template <typename R>

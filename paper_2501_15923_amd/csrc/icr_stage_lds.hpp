@@ -605,9 +605,10 @@ __device__ __forceinline__ void finalize_run(DevClock* ck, const double* __restr
 // block reduces the partials for itself (the same order, so the same clock)
 // from the clock as it was when the step began (ck[1], written by stage 1),
 // then forms its columns' inner-boundary primitives at the new times; block 0
-// also writes the clock and the probe record.
+// of a run also writes the clock and the probe record.
 template <typename R>
-__device__ __forceinline__ void end_step(DevClock* ck, const double* __restrict__ part, int nblocks,
+__device__ __forceinline__ void end_step(int blk, DevClock* ck, const double* __restrict__ part,
+                                         int nblocks,
                                          double cfl, int log_on, const ProbeArgs& pa,
                                          const R* __restrict__ u, double* __restrict__ log,
                                          const BndArgs& bnd, R* __restrict__ g1,
@@ -617,24 +618,25 @@ __device__ __forceinline__ void end_step(DevClock* ck, const double* __restrict_
   __shared__ int s_rec, s_active;
   __shared__ long long s_row;
   __shared__ double s_t, s_dt;
+  const int tid = threadIdx.y * blockDim.x + threadIdx.x;
   if (!ck[1].active) return;  // the stage kernels did not run
   double l, a1, a0;
   int b;
   reduce_partials(part, nblocks, l, a1, a0, b, sh);
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     DevClock c = ck[1];
     s_row = c.n_log;
     s_rec = advance_clock(c, l, a1, a0, b, cfl, 1, log_on, pa);
     s_t = c.t;
     s_dt = c.dt;
     s_active = c.active;
-    if (blockIdx.x == 0) ck[0] = c;
+    if (blk == 0) ck[0] = c;
   }
   __syncthreads();
   if (s_active)
-    boundary_block<R>(bnd, s_t, s_dt, blockIdx.x, threadIdx.x, g1, g2, tg1, tg2);
-  if (blockIdx.x == 0 && s_rec && s_row < pa.log_rows && (int)threadIdx.x < pa.n)
-    probe_eval<R>(pa, u, threadIdx.x, s_t, log + (s_row * pa.max_probes + threadIdx.x) * 12);
+    boundary_block<R>(bnd, s_t, s_dt, blk, tid, g1, g2, tg1, tg2);
+  if (blk == 0 && s_rec && s_row < pa.log_rows && tid < pa.n)
+    probe_eval<R>(pa, u, tid, s_t, log + (s_row * pa.max_probes + tid) * 12);
 }
 
 }  // namespace icr

@@ -142,3 +142,20 @@ def test_ensemble_with_tracer_and_hlld_bitwise_equal_single_runs(mods, phys, per
     if phys.get("tracer"):
         assert n_tau > 0  # CME material entered
     e.close()
+
+
+@pytest.mark.parametrize("blocks", [8, 16, 40, 0])
+def test_ensemble_grids_of_blocks(mods, blocks):
+    """The device-wide barrier with one block per arrival group, a few, and as
+    many as are resident: bitwise the batched lists' states and clocks."""
+    ref, _ = build_ensemble(mods, planes=[4])
+    ref.set_mode(0, 0, 0)
+    ref.step(9)
+    e, _ = build_ensemble(mods, planes=[4])
+    e.set_mode(1, blocks, 0)
+    e.step(9)
+    for a, b in zip(ref.runs, e.runs):
+        assert a.clock() == b.clock()
+        assert np.array_equal(a.get_state(kind=1), b.get_state(kind=1))
+    ref.close()
+    e.close()
