@@ -2,6 +2,7 @@
 //
 //   k_metric        per-r / per-theta metric factors of the stretched
 //                   spherical grid (radially stretched grid, Sect. 2)
+//   k_begin         start of a call: the clock and the first step's boundary
 //   k_boundary      inner-boundary primitives at the two RK stage times:
 //                   time interpolation between maps (Sect. 3) and the
 //                   cone-CME overwrite (Sect. 3.2); one value serves both
@@ -15,7 +16,7 @@
 //                   sampling on the stretched grid (Sect. 2)
 //
 // Layouts: state [8][n_phi][n_theta][n_r] (r fastest), ghost primitives
-// [8][n_phi][n_theta], maps [n_maps][8][n_theta][n_phi] (code units).
+// [8][n_phi][n_theta], maps [n_maps][8][n_phi][n_theta] (code units).
 #include "icr_kernels.hpp"
 
 namespace icr {

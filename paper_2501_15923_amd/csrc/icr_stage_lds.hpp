@@ -12,12 +12,19 @@
 //     sit in LDS; r- and theta-face fluxes go to LDS and are shared by the
 //     two cells of each face;
 //   - the phi direction is carried in registers: each thread keeps the
-//     primitives of planes k-1 .. k+2 of its own column and the flux of
-//     face k-1/2 from the previous plane.
+//     primitives of planes k .. k+2 of its own column, the state cell k has
+//     at its upper face and the flux of face k-1/2.
 // Lanes run along r, so global loads and stores are coalesced (state layout
 // [8][n_phi][n_theta][n_r]).  Stage 2 also forms the per-block partials of
-// the next CFL dt, of the relaxation residual and of the validity flag; a
-// one-block finalize reduces them in a fixed order.
+// the next CFL dt, of the relaxation residual and of the validity flag; the
+// kernel that ends the step reduces them in a fixed order.
+//
+// Bound about equally by FP64 issue and by memory (600 x 60 x 120, minmod and
+// TVDLF, stage 1 / 2): without flux arithmetic 213 / 259 us, without loads
+// from beyond L2 260 / 290 us, as it is 256 / 291 us (4.73 TB/s is what a large
+// copy reaches here; the stages move 0.83 / 1.18 GB).  Against three barriers a
+// plane and two slopes a phi face, FP64 272 / 308 us, FP32 (HLL and MC) 143 /
+// 178 -> 138 / 167 us.
 #pragma once
 #include "icr_kernels.hpp"
 
@@ -238,9 +245,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R>& a, int kplanes, i
   // the current plane is processed.  Stage 2 (DMA) has no registers to
   // spare: the next plane's halo rows are copied global -> LDS by the LDS-DMA
   // loads, issued after the plane's face barrier (nothing reads sW until the
-  // next plane barrier), so they travel while the plane is updated; after
-  // the next plane barrier each thread converts its halo cell to primitives
-  // in place.  Those copies take, for a halo cell below r_in or beyond
+  // next plane), so they travel while the plane is updated; a wave then waits
+  // for its own copies and converts its halo cells to primitives in place.  Those copies take, for a halo cell below r_in or beyond
   // r_out, the clamped cell of its row: such cells only feed the theta
   // faces of halo lanes, which the update never reads.
   constexpr bool PF = STAGE == 1;
@@ -456,6 +462,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R>& a, int kplanes, i
     // now wa = W(k), wb = W(k+1), wc = W(k+2)
     if (body) {
       __syncthreads();  // r / theta face fluxes are in LDS
+      // from here to the next rows' barrier a wave goes before the other
+      // block's waves: all four of this block wait there for the slowest
       __builtin_amdgcn_s_setprio(2);
       if constexpr (DMA) {
         if (dma_wave && k + 1 < kend) dma_halo(k + 1);  // in flight during this update
