@@ -1296,6 +1296,18 @@ size_t ens_table_bytes(int n) {
   return b;
 }
 
+void ens_drop_graph(icr_ensemble* e) {
+  if (e->graph_ok) (void)hipGraphExecDestroy(e->g_chunk);
+  e->graph_ok = false;
+}
+
+// Stage tiles of a run, [r][theta][phi].  An ensemble's tile is the 64 x 4 one
+// (WENO5: 58 cells along r) whatever a run's own launch configuration says.
+dim3 ens_tiles(const icr_solver* s, int planes) {
+  const int ti = s->p.limiter == ICR_LIM_WENO5 ? W5_TI : tile_cells_r(64);
+  return dim3((s->g.n_r + ti - 1) / ti, (s->g.n_theta + 3) / 4, (s->g.n_phi + planes - 1) / planes);
+}
+
 template <typename R>
 RunDesc<R> make_desc(icr_solver* s, int planes) {
   RunDesc<R> d;
@@ -1319,11 +1331,10 @@ RunDesc<R> make_desc(icr_solver* s, int planes) {
   d.tghost1 = (R*)s->tg(1);
   d.clock = s->clock();
   d.partials = (double*)(s->ws + s->L.partials);
-  // the tile grid of the run's stage kernel (WENO5: 58 cells along r)
-  const int ti = s->p.limiter == ICR_LIM_WENO5 ? W5_TI : tile_cells_r(64);
-  d.nbx = (s->g.n_r + ti - 1) / ti;
-  d.nby = (s->g.n_theta + 3) / 4;
-  d.nbz = (s->g.n_phi + planes - 1) / planes;
+  const dim3 tiles = ens_tiles(s, planes);
+  d.nbx = (int)tiles.x;
+  d.nby = (int)tiles.y;
+  d.nbz = (int)tiles.z;
   d.planes = planes;
   d.par = s->cur;
   d.cfl = s->p.cfl;
@@ -1338,7 +1349,10 @@ int ens_upload(icr_ensemble* e) {
   const int slots = e->persistent ? e->grid : stage_slots(e->f32);
   const int pl = choose_planes(np_max, slots, [&](int p) {
     long long b = 0;
-    for (const icr_solver* s : e->runs) b += s->tile_blocks(p);
+    for (const icr_solver* s : e->runs) {
+      const dim3 t = ens_tiles(s, p);
+      b += (long long)t.x * t.y * t.z;
+    }
     return b;
   });
   auto planes = [&](int r) {
@@ -1360,6 +1374,8 @@ int ens_upload(icr_ensemble* e) {
     boff[r + 1] = boff[r] + boundary_blocks(s->g.n_theta, s->g.n_phi);
     coff[r + 1] = coff[r] + (s->trc() ? (int)((s->ncell() + 255) / 256) : 0);
   }
+  // a captured graph holds these lengths by value
+  if (e->n_tiles != toff[n] || e->n_bitems != boff[n] || e->n_titems != coff[n]) ens_drop_graph(e);
   e->n_tiles = toff[n];
   e->n_bitems = boff[n];
   e->n_titems = coff[n];
@@ -1394,11 +1410,6 @@ EnsLaunch ens_launch_args(icr_ensemble* e, int nsteps) {
   L.lim = e->p.limiter;
   L.tracer = e->p.tracer ? 1 : 0;
   return L;
-}
-
-void ens_drop_graph(icr_ensemble* e) {
-  if (e->graph_ok) (void)hipGraphExecDestroy(e->g_chunk);
-  e->graph_ok = false;
 }
 
 }  // namespace

@@ -159,3 +159,31 @@ def test_ensemble_grids_of_blocks(mods, blocks):
         assert np.array_equal(a.get_state(kind=1), b.get_state(kind=1))
     ref.close()
     e.close()
+
+
+@pytest.mark.parametrize("persistent", [1, 0])
+def test_a_members_own_launch_shape_leaves_the_ensemble_alone(mods, persistent):
+    """The ensemble's tiles are its own: launch configurations set on its runs
+    between steps change neither its states nor the lists its captured graph
+    was made for.  Plane counts by the rule (8 runs of 64 x 16 x 32: another
+    count for the 32-lane tile than for the 64-lane one)."""
+    _, _, ensemble = mods
+    grids = [synth.Grid(64, 16, 32)] * 8
+    states = []
+    for shapes in ([64, 64, 64], [64, 32, 64], [32, 64, 32]):
+        e = ensemble.Ensemble(grids)
+        e.set_mode(persistent, 0, 1)
+        for q, run in enumerate(e.runs):
+            run.set_maps(np.zeros(1), synth.relax_map(grids[q], 40 + q)[None])
+            run.init_radial()
+        for tile_r in shapes:
+            for run in e.runs:
+                run.set_launch(2, tile_r, 0, 1)
+            say("persistent", persistent, "members' tile", tile_r)
+            e.step(9)
+        states.append([(r.clock(), r.get_state(kind=1)) for r in e.runs])
+        e.close()
+    for other in states[1:]:
+        for (c0, u0), (c1, u1) in zip(states[0], other):
+            assert c0 == c1
+            assert np.array_equal(u0, u1)
