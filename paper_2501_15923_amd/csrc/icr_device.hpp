@@ -587,7 +587,7 @@ __device__ __forceinline__ void hlld_flux_fast(const R (&wl)[NV], const R (&wr)[
 // TVDLF and HLL in one form for the face-once kernels: with the bounding
 // speeds s_L = -alpha, s_R = alpha (TVDLF) or s_L = min(S_L, 0), s_R =
 // max(S_R, 0) (HLL, whose one-sided cases are then included) and the weights
-// h_L = s_R / (s_R - s_L), h_R = -s_L / (s_R - s_L),
+// h_R = -s_L / (s_R - s_L), h_L = 1 - h_R,
 //   F = h_L (F_L - s_L U_L) + h_R (F_R - s_R U_R).
 // A flux component is u v_n plus magnetic and pressure terms, so each side's
 // F - s U needs u (v_n - s) only: neither the physical fluxes nor the
@@ -610,9 +610,10 @@ __device__ __forceinline__ void two_wave_flux(const R (&wl)[NV], const R (&wr)[N
   } else {
     sl = rmin(rmin(wl[N] - cl, wr[N] - cr), R(0));
     sr = rmax(rmax(wl[N] + cl, wr[N] + cr), R(0));
-    const R id = rcp_fast(sr - sl);
-    hl = sr * id;
-    hr = -sl * id;
+    // one-sided cases exactly: a product of s_R and the reciprocal of s_R is
+    // 1 to an ulp only, and the upwind flux would carry that error
+    hr = sr > R(0) ? -sl * rcp_fast(sr - sl) : R(1);
+    hl = R(1) - hr;
   }
   const R al = hl * (wl[N] - sl), ar = hr * (wr[N] - sr);
   const R bl = hl * wl[4 + N], br = hr * wr[4 + N];
