@@ -375,6 +375,9 @@ __device__ __forceinline__ void stage_tile_w5(const StageArgs<R>& a, int kplanes
 #pragma unroll
     for (int v = 0; v < NV; ++v) fcar[v] = fhi[v];
   }
+  // a block goes on (to its next tile, or to wait at a barrier between lists)
+  // no sooner than the others
+  __builtin_amdgcn_s_setprio(0);
   if (STAGE == 2) write_partials(a.partials, pslot, lam, s1, s0, bad);
 }
 
