@@ -406,8 +406,16 @@ struct icr_solver {
     return a;
   }
 
-  // Both stages and the end of a step: in one launch with the next step's
-  // boundary, or (ev set) the clock alone.
+  // Whether the end of a step and the next boundary are one launch.  Every
+  // block of that launch reduces all partials, at the same time as the others
+  // and so at no cost, as long as all of them are resident (256 CUs x 4); in a
+  // second round it is done again.  600 x 240 x 480 (900 blocks) 78 us in one
+  // launch and 73 + 8 in two, 600 x 300 x 600 (1408) 194 and 113 + 11, 116 x
+  // 480 x 960 (3600) 190 and 59 + 21.
+  bool one_step_end() const { return boundary_blocks(g.n_theta, g.n_phi) <= 1024; }
+
+  // Both stages and the end of a step with the next step's boundary, or (ev
+  // set) the clock alone.
   template <typename R>
   void enqueue_stages(int from, int to, hipStream_t st, hipEvent_t* ev) {
     const StageArgs<R> a1 = stage_args<R>(from, from, 2, 0);
@@ -429,10 +437,12 @@ struct icr_solver {
       launch_stage_lds<R>(a2, 2, p.flux, p.limiter, tile_r, pl, st);
     if (trc()) launch_tracer<R>(tracer_args<R>(2, 2, from, to, 1), 2, st);
     if (ev) (void)hipEventRecord(ev[3], st);
-    if (ev)
+    if (ev || !one_step_end()) {
       launch_finalize<R>(clock(), partials(), stage_blocks(), p.cfl, 1, logging() ? 1 : 0,
                          probe_args(), u(to), (double*)(ws + L.plog), st);
-    else
+      if (!ev)
+        launch_boundary(bnd(), clock(), ghost(0), ghost(1), tg(0), tg(1), f32, st);
+    } else
       launch_step_end<R>(clock(), partials(), stage_blocks(), p.cfl, logging() ? 1 : 0,
                          probe_args(), u(to), (double*)(ws + L.plog), bnd(), ghost(0), ghost(1),
                          tg(0), tg(1), st);

@@ -617,6 +617,8 @@ __device__ __forceinline__ void finalize_run(DevClock* ck, const double* __restr
 // from the clock as it was when the step began (ck[1], written by stage 1),
 // then forms its columns' inner-boundary primitives at the new times; block 0
 // of a run also writes the clock and the probe record.
+// (Single runs of more columns than one round of blocks use finalize_run and
+// k_boundary instead.)
 template <typename R>
 __device__ __forceinline__ void end_step(int blk, DevClock* ck, const double* __restrict__ part,
                                          int nblocks,

@@ -39,3 +39,37 @@ def test_default_planes_match_forced_planes(shape, precision, limiter):
     for t, u in states[1:]:
         assert t == states[0][0]
         assert np.array_equal(u, states[0][1])
+
+
+@pytest.mark.parametrize("nt", [256, 257])  # 1024 and 1028 blocks of boundary columns
+@pytest.mark.parametrize("graphs", [1, 0])
+def test_step_end_of_many_columns_matches_the_oracle(nt, graphs):
+    """Up to 1024 blocks of boundary columns a step ends in one launch, beyond
+    that in two (clock and probes, then the next boundary): time-dependent
+    maps, a CME with its tracer, logged probes and an end time on both sides
+    of the line, replayed and launched directly."""
+    import oracle
+    import parity
+    from paper_2501_15923_amd.solver import Solver
+    g = synth.Grid(4, nt, 512)
+    times, maps = synth.dynamic_maps(g, 3, n_maps=3, cadence=100.0)
+    cme = np.array([[0.0, 7200.0, 5 * synth.DEG, 1.2, 30 * synth.DEG, 1.2e6, 1e-18, 0.8e6]])
+    s = Solver(g, tracer=True, probe_log_rows=16)
+    o = oracle.Oracle(g.nr, g.nt, g.np_, tracer=True)
+    s.set_launch(2, 64, 0, graphs)
+    s.set_probes(synth.probe_tables(synth.DAY, 1), cadence=0.0)
+    for x in (s, o):
+        x.set_maps(times, maps)
+        x.set_cmes(cme)
+        x.init_radial()
+    t_end = s.clock()["next_dt"] * 6.5
+    print("columns", g.nt * g.np_, "graphs", graphs, flush=True)
+    a, b = s.step(12, t_end=t_end), o.step(12, t_end=t_end)
+    assert a["steps"] == b["steps"] and 4 < a["steps"] < 12
+    assert s.clock()["t"] == pytest.approx(t_end, rel=1e-15)
+    parity.assert_parity(s.get_state(kind=1), o.get_state(kind=oracle.CONS_CODE))
+    assert np.max(np.abs(s.get_tracer() - o.get_tracer())) <= parity.TOL_F64
+    log, n = s.read_probe_log(16)
+    assert n == a["steps"]
+    assert np.allclose(log[-1], s.sample_probes(), rtol=1e-12, atol=0.0, equal_nan=True)
+    s.close()
