@@ -649,8 +649,8 @@ def main():
 
     # per-kernel durations with HIP events (direct launches, same stream)
     kms = s.profile_steps(args.profile_steps)
-    log(f"bench: kernel ms boundary {kms[0]:.4f} stage1 {kms[1]:.4f} stage2 {kms[2]:.4f} "
-        f"probe {kms[3]:.4f}")
+    log(f"bench: kernel ms boundary {kms[0]:.4f} (0: formed by the step's end) "
+        f"stage1 {kms[1]:.4f} stage2 {kms[2]:.4f} step end {kms[3]:.4f}")
     bpc = FP64_BYTES_STAGE if args.precision == 64 else tuple(b // 2 for b in FP64_BYTES_STAGE)
     bytes2 = bpc[1] * g.cells
     achieved = bytes2 / (kms[2] * 1e-3) / 1e9

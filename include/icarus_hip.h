@@ -319,8 +319,10 @@ int icr_set_launch(icr_solver *s, int variant, int tile_r, int planes,
 
 /* Advance n_steps (> 0) steps with direct launches, timing each kernel with
  * HIP events on the solver's stream.  avg_ms[4] receives the mean duration
- * of the boundary driver, stage 1, stage 2 and the finalize kernel (clock,
- * dt and probe record).  Same results as icr_step. */
+ * of the boundary driver (0 where the kernel that ends a step also forms the
+ * next boundary: up to 131072 columns), of stage 1, of stage 2 and of the end
+ * of the step (clock, dt and probe record).  Same launches and results as
+ * icr_step with use_graphs = 0. */
 int icr_profile_steps(icr_solver *s, int n_steps, double *avg_ms);
 
 /* Accuracy diagnostic of the FP64 reciprocal and square root the face-once

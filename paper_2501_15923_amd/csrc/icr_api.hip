@@ -414,13 +414,14 @@ struct icr_solver {
   // 480 x 960 (3600) 190 and 59 + 21.
   bool one_step_end() const { return boundary_blocks(g.n_theta, g.n_phi) <= 1024; }
 
-  // Both stages and the end of a step with the next step's boundary, or (ev
-  // set) the clock alone.
+  // Both stages and the end of a step: clock, dt, probe record and the next
+  // step's boundary.
   template <typename R>
   void enqueue_stages(int from, int to, hipStream_t st, hipEvent_t* ev) {
     const StageArgs<R> a1 = stage_args<R>(from, from, 2, 0);
     const StageArgs<R> a2 = stage_args<R>(2, from, to, 1);
     const int pl = stage_planes();
+    if (ev) (void)hipEventRecord(ev[0], st);
     if (variant == 1)
       launch_stage<R>(a1, 1, p.flux, p.limiter, grid(), block(), st);
     else if (p.limiter == ICR_LIM_WENO5)
@@ -428,7 +429,7 @@ struct icr_solver {
     else
       launch_stage_lds<R>(a1, 1, p.flux, p.limiter, tile_r, pl, st);
     if (trc()) launch_tracer<R>(tracer_args<R>(from, from, from, 2, 0), 1, st);
-    if (ev) (void)hipEventRecord(ev[2], st);
+    if (ev) (void)hipEventRecord(ev[1], st);
     if (variant == 1)
       launch_stage<R>(a2, 2, p.flux, p.limiter, grid(), block(), st);
     else if (p.limiter == ICR_LIM_WENO5)
@@ -436,16 +437,19 @@ struct icr_solver {
     else
       launch_stage_lds<R>(a2, 2, p.flux, p.limiter, tile_r, pl, st);
     if (trc()) launch_tracer<R>(tracer_args<R>(2, 2, from, to, 1), 2, st);
-    if (ev) (void)hipEventRecord(ev[3], st);
-    if (ev || !one_step_end()) {
-      launch_finalize<R>(clock(), partials(), stage_blocks(), p.cfl, 1, logging() ? 1 : 0,
-                         probe_args(), u(to), (double*)(ws + L.plog), st);
-      if (!ev)
-        launch_boundary(bnd(), clock(), ghost(0), ghost(1), tg(0), tg(1), f32, st);
-    } else
+    if (ev) (void)hipEventRecord(ev[2], st);
+    if (one_step_end()) {
       launch_step_end<R>(clock(), partials(), stage_blocks(), p.cfl, logging() ? 1 : 0,
                          probe_args(), u(to), (double*)(ws + L.plog), bnd(), ghost(0), ghost(1),
                          tg(0), tg(1), st);
+      if (ev) (void)hipEventRecord(ev[3], st);
+    } else {
+      launch_finalize<R>(clock(), partials(), stage_blocks(), p.cfl, 1, logging() ? 1 : 0,
+                         probe_args(), u(to), (double*)(ws + L.plog), st);
+      if (ev) (void)hipEventRecord(ev[3], st);
+      launch_boundary(bnd(), clock(), ghost(0), ghost(1), tg(0), tg(1), f32, st);
+      if (ev) (void)hipEventRecord(ev[4], st);
+    }
   }
 
   // Start of a call: clock and first boundary (enqueue_step expects the
@@ -454,22 +458,15 @@ struct icr_solver {
     launch_begin(bnd(), clock(), t_end, ghost(0), ghost(1), tg(0), tg(1), f32, stream);
   }
 
-  // One RK2 step from state buffer `from` into `from ^ 1`: stage 1, stage 2,
-  // end of the step (clock, dt, probe record, next boundary).  ev (timing): 5
-  // events around the boundary driver, the two stages and the finalize
-  // kernel, each launched by itself.
+  // One RK2 step from state buffer `from` into `from ^ 1`.  ev (timing): events
+  // before stage 1, after it, after stage 2, after the end of the step and,
+  // where the next boundary is a launch of its own, after that.
   void enqueue_step(int from, hipStream_t st, hipEvent_t* ev = nullptr) {
     const int to = from ^ 1;
-    if (ev) {
-      (void)hipEventRecord(ev[0], st);
-      launch_boundary(bnd(), clock(), ghost(0), ghost(1), tg(0), tg(1), f32, st);
-      (void)hipEventRecord(ev[1], st);
-    }
     if (f32)
       enqueue_stages<float>(from, to, st, ev);
     else
       enqueue_stages<double>(from, to, st, ev);
-    if (ev) (void)hipEventRecord(ev[4], st);
   }
 
   bool logging() const { return n_probes > 0 && cadence >= 0.0 && g.probe_log_rows > 0; }
@@ -1205,19 +1202,20 @@ int icr_profile_steps(icr_solver* s, int n, double* avg_ms) {
   hipEvent_t ev[5];
   for (int q = 0; q < 5; ++q) HIP_TRY(hipEventCreate(&ev[q]));
   double acc[4] = {0, 0, 0, 0};
-  launch_clock_begin(s->clock(), -1.0, s->stream);
+  s->enqueue_begin(-1.0);
+  const bool one = s->one_step_end();  // no boundary launch between the steps
   int rc = ICR_OK;
   for (int q = 0; q < n && rc == ICR_OK; ++q) {
     s->enqueue_step(s->cur, s->stream, ev);
     s->cur ^= 1;
-    if (hipEventSynchronize(ev[4]) != hipSuccess) {
+    if (hipEventSynchronize(ev[one ? 3 : 4]) != hipSuccess) {
       rc = fail(ICR_ERR_HIP, "event synchronisation failed");
       break;
     }
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < (one ? 3 : 4); ++k) {
       float ms = 0.f;
       (void)hipEventElapsedTime(&ms, ev[k], ev[k + 1]);
-      acc[k] += ms;
+      acc[(k + 1) % 4] += ms;
     }
   }
   for (int q = 0; q < 5; ++q) (void)hipEventDestroy(ev[q]);

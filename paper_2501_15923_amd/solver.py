@@ -236,7 +236,8 @@ class Solver:
         check(lib().icr_set_launch(self.h, variant, tile_r, tile_t, use_graphs))
 
     def profile_steps(self, n):
-        """Mean ms per launch of (boundary, stage 1, stage 2, probe logger)."""
+        """Mean ms per launch of (boundary, stage 1, stage 2, end of the step); the
+        boundary is 0 where the end of a step forms the next one."""
         out = np.zeros(4)
         check(lib().icr_profile_steps(self.h, int(n), _np_ptr(out)))
         return out

@@ -73,3 +73,28 @@ def test_step_end_of_many_columns_matches_the_oracle(nt, graphs):
     assert n == a["steps"]
     assert np.allclose(log[-1], s.sample_probes(), rtol=1e-12, atol=0.0, equal_nan=True)
     s.close()
+
+
+@pytest.mark.parametrize("nt", [256, 257])
+def test_profiled_steps_are_the_launches_of_a_step(nt):
+    """Timed steps launch what a step launches: the boundary has a time of its
+    own only where it has a launch of its own; state and clock bitwise."""
+    from paper_2501_15923_amd.solver import Solver
+    g = synth.Grid(4, nt, 512)
+    maps = synth.relax_map(g, 7)[None]
+    states = []
+    for profiled in (False, True):
+        s = Solver(g)
+        s.set_maps(np.zeros(1), maps)
+        s.init_radial()
+        print("columns", g.nt * g.np_, "profiled", profiled, flush=True)
+        if profiled:
+            ms = s.profile_steps(3)
+            assert (ms[0] == 0.0) == (nt == 256)
+            assert np.all(ms[1:] > 0.0)
+        else:
+            s.step(3)
+        states.append((s.clock(), s.get_state(kind=1)))
+        s.close()
+    assert states[0][0] == states[1][0]
+    assert np.array_equal(states[0][1], states[1][1])
