@@ -629,6 +629,7 @@ def main():
                                               limiter=lim)
         log(f"bench: launch tuner chose tile_r {tile_r}, {planes} phi planes per block")
     s.set_launch(args.variant, tile_r, planes, 1)
+    _, tile_r, planes = s.launch()  # what it runs, where the choice was left open too
     s.set_maps(w.times, w.maps)
     if len(w.cmes):
         s.set_cmes(w.cmes)
@@ -659,7 +660,7 @@ def main():
     if os.path.exists(args.traffic):
         try:
             tr = traffic_for(args.traffic, args.precision, args.flux, args.limiter,
-                             [tile_r or 64, planes or 8])
+                             [tile_r, planes])
             if tr is not None:
                 traffic = tr.get("bytes_per_launch")
                 vi = tr.get("valu_wave_instr_per_launch")
@@ -697,7 +698,7 @@ def main():
                    "map_variant": configs.DEFAULT_MAPS,
                    "probes": int(w.probes.shape[0]), "flux": args.flux.upper(), "limiter": args.limiter,
                    "rk": "SSP-RK2", "cfl": w.cfl, "parallelism": "single GPU",
-                   "launch": {"tile_r": tile_r or 64, "phi_planes": planes or 8}},
+                   "launch": {"tile_r": tile_r, "phi_planes": planes}},
         "roofline": roof,
     }
     if args.flux != "tvdlf" or args.limiter != "minmod":

@@ -317,6 +317,11 @@ int icr_boundary_at(icr_solver *s, double t_s, double *out);
 int icr_set_launch(icr_solver *s, int variant, int tile_r, int planes,
                    int use_graphs);
 
+/* The stage launch shape the next step uses: variant (1 or 2), lanes along r
+ * and phi planes per block (the chosen count where none was set; 1 for
+ * variant 1). */
+int icr_get_launch(icr_solver *s, int *variant, int *tile_r, int *planes);
+
 /* Advance n_steps (> 0) steps with direct launches, timing each kernel with
  * HIP events on the solver's stream.  avg_ms[4] receives the mean duration
  * of the boundary driver (0 where the kernel that ends a step also forms the

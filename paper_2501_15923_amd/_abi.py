@@ -95,6 +95,7 @@ SIGNATURES = {
     "icr_read_probe_log": (I, [P, D, I, ctypes.POINTER(ctypes.c_int)]),
     "icr_boundary_at": (I, [P, ctypes.c_double, D]),
     "icr_set_launch": (I, [P, I, I, I, I]),
+    "icr_get_launch": (I, [P, ctypes.POINTER(I), ctypes.POINTER(I), ctypes.POINTER(I)]),
     "icr_profile_steps": (I, [P, I, D]),
     "icr_fast_math": (I, [D, ctypes.c_longlong, D, D, P]),
     "icr_ens_workspace_bytes": (I, [I, ctypes.POINTER(IcrGrid), ctypes.POINTER(IcrPhys),

@@ -1262,6 +1262,14 @@ int icr_set_launch(icr_solver* s, int variant, int tile_r, int planes, int use_g
   return ICR_OK;
 }
 
+int icr_get_launch(icr_solver* s, int* variant, int* tile_r, int* planes) {
+  if (!s || !variant || !tile_r || !planes) return fail(ICR_ERR_ARG, "NULL argument");
+  *variant = s->variant;
+  *tile_r = s->variant == 1 ? s->v1_tile() : s->tile_r;
+  *planes = s->variant == 1 ? 1 : s->stage_planes();
+  return ICR_OK;
+}
+
 }  // extern "C"
 
 // ======================================================================

@@ -235,6 +235,12 @@ class Solver:
     def set_launch(self, variant=0, tile_r=0, tile_t=0, use_graphs=1):
         check(lib().icr_set_launch(self.h, variant, tile_r, tile_t, use_graphs))
 
+    def launch(self):
+        """(variant, lanes along r, phi planes per block) the next step uses."""
+        v = [ctypes.c_int() for _ in range(3)]
+        check(lib().icr_get_launch(self.h, *(ctypes.byref(x) for x in v)))
+        return tuple(x.value for x in v)
+
     def profile_steps(self, n):
         """Mean ms per launch of (boundary, stage 1, stage 2, end of the step); the
         boundary is 0 where the end of a step forms the next one."""

@@ -98,3 +98,23 @@ def test_profiled_steps_are_the_launches_of_a_step(nt):
         s.close()
     assert states[0][0] == states[1][0]
     assert np.array_equal(states[0][1], states[1][1])
+
+
+def test_the_launch_shape_reported_is_the_one_run():
+    """What a benchmark states as its launch shape: the count chosen by the
+    rule where none was set, else the one set; one plane a block for the
+    thread-per-cell variant."""
+    from paper_2501_15923_amd.solver import Solver
+    s = Solver(synth.Grid(600, 60, 120))
+    assert s.launch() == (2, 64, 12)
+    s.set_launch(2, 32, 15, 1)
+    assert s.launch() == (2, 32, 15)
+    s.set_launch(0, 0, 0, 1)
+    assert s.launch() == (2, 64, 12)
+    s.set_launch(1, 128, 8, 1)
+    assert s.launch() == (1, 128, 1)
+    s.close()
+    s = Solver(synth.Grid(9, 5, 3))
+    variant, tile_r, planes = s.launch()
+    assert (variant, tile_r) == (2, 64) and 1 <= planes <= 3
+    s.close()
