@@ -310,9 +310,10 @@ int icr_boundary_at(icr_solver *s, double t_s, double *out);
  * updates tile_r - 4 cells along r; 0 = 64; a solver with the passive
  * tracer keeps 64 for variant 2; a WENO5 solver's variant 2 is its own
  * 64-lane tile of 58 cells along r, and with the tracer it runs variant 1);
- * 256 threads per block.  planes: phi planes per block of
- * variant 2 (1..n_phi, 0 = chosen from the grid's size, also the default).  use_graphs: 1 replays steps from captured
- * HIP graphs.  All tiles and plane counts of one variant give bit-identical
+ * 256 threads per block.  planes: phi planes per block of variant 2
+ * (1..n_phi; 0 = chosen from the grid's size, as it is before the first call,
+ * but refused here below 8 phi planes).  use_graphs: 1 replays steps from
+ * captured HIP graphs.  All tiles and plane counts of one variant give bit-identical
  * results; the two variants agree to rounding. */
 int icr_set_launch(icr_solver *s, int variant, int tile_r, int planes,
                    int use_graphs);
