@@ -7,15 +7,19 @@
 // layers; a level-(l+1) block is one octant of a level-l block at twice the
 // resolution (radial edges split at the geometric mean).  One global dt,
 // SSP-RK2 on the leaves.  Per stage:
-//   k_amr_ghost   the ghost layers of every leaf, one block per leaf face:
-//                 copies from a leaf of the same level, volume-weighted
-//                 restriction of finer leaves, physical edges as in the
-//                 uniform solver; then, coarse levels first, the faces next
-//                 to a coarser leaf: conservative prolongation (minmod slopes
-//                 from its padded block, then a constant correction so the
-//                 children's volume-weighted mean is the coarse cell);
-//   k_amr_stage   reconstruct / flux / divergence / sources / RK combine of
-//                 every leaf cell, the fluxes of the block's six faces kept;
+//   k_amr_ghost   the ghost layers the stage kernel does not take from their
+//                 source itself, one block per listed leaf face (a regrid:
+//                 all faces): copies from a leaf of the same level,
+//                 volume-weighted restriction of finer leaves, physical edges
+//                 as in the uniform solver; then, coarse levels first, the
+//                 faces next to a coarser leaf: conservative prolongation
+//                 (minmod slopes from its padded block, then a constant
+//                 correction so the children's volume-weighted mean is the
+//                 coarse cell);
+//   k_amr_stage_lds (leaves that fit LDS) or k_amr_stage: reconstruct / flux /
+//                 divergence / sources / RK combine of every leaf cell, the
+//                 fluxes of the faces next to another level kept (k_amr_stage:
+//                 of all six faces);
 //   k_amr_reflux  a coarse cell next to finer leaves takes the area-weighted
 //                 sum of their face fluxes instead of its own on that face.
 // After a step: the CFL rate of every leaf cell (one-block finalize), and
@@ -57,8 +61,7 @@ struct AmrArgs {
   double* U;   // [slot][9][pp][pt][pr] U^n / U^{n+1}
   double* U1;  // [slot][9][pp][pt][pr] stage-1 state
   double* F;   // [slot][6][9][fmax] fluxes of the block faces r-, r+, t-, t+, p-, p+
-  const unsigned char* leaf;  // [slot]
-  const int* key;             // [slot][4]: level, bi, bj, bk
+  const int* key;  // [slot][4]: level, bi, bj, bk
   const AmrLevel* __restrict__ lv;  // [level], device table
   int nlev, br, bt, bp, pr, pt, pp, fmax;
   long long bvol;  // padded cells per variable of a block
@@ -1035,7 +1038,7 @@ int err(int code, const std::string& m) { return set_error(code, m.c_str()); }
   } while (0)
 
 struct AmrLayout {
-  size_t U, U1, F, leaf, key, lv, maps[AMR_MAXL + 1], m64[AMR_MAXL + 1], mr[AMR_MAXL + 1],
+  size_t U, U1, F, key, lv, maps[AMR_MAXL + 1], m64[AMR_MAXL + 1], mr[AMR_MAXL + 1],
       bmaps, tau, cme, clock, partials, ind, lists, leaves, rlist, glist, total;
 };
 
@@ -1099,7 +1102,6 @@ struct icr_amr {
     a.U = (double*)at(L.U);
     a.U1 = (double*)at(L.U1);
     a.F = (double*)at(L.F);
-    a.leaf = (const unsigned char*)at(L.leaf);
     a.key = (const int*)at(L.key);
     a.lv = (const AmrLevel*)at(L.lv);
     a.nlev = nlev;
@@ -1194,7 +1196,7 @@ struct icr_amr {
     free_slots.push_back(s);
   }
 
-  // upload key table, leaf flags and level maps
+  // upload key table and level maps
   int upload_tree() {
     const int mb = q.max_blocks;
     std::vector<int> keys(4 * (size_t)mb, 0);
@@ -1207,7 +1209,6 @@ struct icr_amr {
     }
     AMR_TRY(hipMemcpyAsync(at(L.key), keys.data(), keys.size() * sizeof(int),
                            hipMemcpyHostToDevice, stream));
-    AMR_TRY(hipMemcpyAsync(at(L.leaf), leaf.data(), leaf.size(), hipMemcpyHostToDevice, stream));
     for (int l = 1; l <= nlev; ++l)
       AMR_TRY(hipMemcpyAsync(at(L.maps[l]), hmap[l].data(), hmap[l].size() * sizeof(int),
                              hipMemcpyHostToDevice, stream));
@@ -1285,12 +1286,6 @@ struct icr_amr {
                              hipMemcpyHostToDevice, stream));
     AMR_TRY(hipStreamSynchronize(stream));
     return ICR_OK;
-  }
-
-  std::vector<int> slots(const std::vector<Key>& ks) const {
-    std::vector<int> s;
-    for (const Key& k : ks) s.push_back(slot(k));
-    return s;
   }
 
   // block size and LDS of the face-once stage kernel: 0 (the leaf does not
@@ -1538,7 +1533,6 @@ AmrLayout amr_layout(const icr_grid& g, const icr_amr_params& q) {
   L.U = take(sizeof(double) * NA * bvol * mb);
   L.U1 = take(sizeof(double) * NA * bvol * mb);
   L.F = take(sizeof(double) * 6 * NA * (size_t)fmax * mb);
-  L.leaf = take(mb);
   L.key = take(sizeof(int) * 4 * mb);
   L.lv = take(sizeof(AmrLevel) * (AMR_MAXL + 1));
   for (int l = 1; l <= q.max_level; ++l) {
