@@ -333,8 +333,8 @@ int icr_profile_steps(icr_solver *s, int n_steps, double *avg_ms);
 
 /* Accuracy diagnostic of the FP64 reciprocal and square root the face-once
  * stage kernels use instead of division and sqrt (hardware estimate refined
- * by two Newton-Raphson steps, and by two Goldschmidt iterations plus a
- * residual correction): rcp[q] = 1/x[q], sq[q] = sqrt(x[q]) for n device
+ * by one third-order step, and by one Goldschmidt iteration plus a residual
+ * correction): rcp[q] = 1/x[q], sq[q] = sqrt(x[q]) for n device
  * doubles (positive normal x).  All pointers device memory; synchronises
  * the stream. */
 int icr_fast_math(const double *x, long long n, double *rcp, double *sq, void *hip_stream);
@@ -342,9 +342,11 @@ int icr_fast_math(const double *x, long long n, double *rcp, double *sq, void *h
 /* ------------------------------------------------------------------------
  * Batched ensemble (not in the paper; many independent runs on one GPU).
  * n_runs solvers with their own grids, boundary maps, cone CMEs, clocks and
- * CFL dt, stepped together: each ensemble step walks all runs' boundary
- * columns, stage-1 tiles, stage-2 tiles and per-run finalize (with the
- * passive tracer, a tracer list of all runs' cells follows each stage).  In the
+ * CFL dt, stepped together: each ensemble step walks all runs' stage-1 tiles,
+ * stage-2 tiles and the ends of their steps with the next step's boundary
+ * columns (with the passive tracer, a tracer list of all runs' cells follows
+ * each stage).  The stage tiles are the ensemble's own (64 lanes along r):
+ * icr_set_launch on a run does not change them.  In the
  * persistent mode one kernel launch performs the steps with a device-wide
  * barrier between those phases (its grid never exceeds the resident block
  * capacity; a barrier that cannot complete turns into ICR_ERR_HIP instead of

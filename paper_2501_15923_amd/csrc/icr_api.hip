@@ -89,13 +89,16 @@ size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 // read off sweeps of p = 1 .. 120 over grids from 64x16x32 to 600x60x120:
 // one round at one block per CU or fewer costs 0.7 of a full round (a block
 // alone on a CU runs faster), a last round that is at most half full about
-// 0.4 + 0.3 f of one, a fuller one 0.6 + 0.4 f.  Measured, FP64 minmod +
-// TVDLF, stage 1 + 2, against the 8 planes of every grid before: 64x16x32
-// (p = 1) 109 -> 30 us, 150x30x60 (p = 3) 99 -> 74 us, 331x47x91 with HLLD
-// (p = 4) 356 -> 325 us, 600x60x120 (p = 12) 618 -> 610 us.  Longer marches
-// than 16 planes gained nothing on any of them.  Grids of more than 16 rounds
-// at 8 planes keep 8: the choice is worth less than 2 % there, and the block
-// counts that icr_step_noalloc accepts stay what they were.
+// 0.4 + 0.3 f of one, a fuller one 0.6 + 0.4 f.  Those sweeps ran on stage
+// kernels of three barriers a plane; with the present ones, swept over p = 1 ..
+// 16 again, the rule's count is still the fastest (WENO5: level with it).
+// Stage 1 + 2 at the rule's count against 8 planes: FP64 minmod + TVDLF
+// 64x16x32 (p = 1) 27 / 94 us, 97x23x37 (1) 36 / 86, 150x30x60 (3) 61 / 87,
+// 241x40x67 (7) 108 / 118, 600x60x120 (12) 510 / 530; HLLD + MC 331x47x91 (13)
+// 249 / 290; FP32 HLL + MC 600x60x120 (12) 263 / 266; WENO5 there (10) 1389 /
+// 1388.  Longer marches than 16 planes gained nothing on any of them.  Grids of
+// more than 16 rounds at 8 planes keep 8: the choice is worth less than 2 %
+// there, and the block counts that icr_step_noalloc accepts stay what they were.
 constexpr double PLANE_PROLOGUE = 0.45;
 constexpr int PLANES_FIXED = 8, PLANES_MOST = 16;
 
@@ -297,7 +300,7 @@ struct icr_solver {
   void* mr() { return ws + L.mr; }
   DevClock* clock() { return (DevClock*)(ws + L.clock); }
   long long ncell() const { return (long long)g.n_r * g.n_theta * g.n_phi; }
-  // thread-per-cell launches (variant 1 and the CFL kernel)
+  // thread-per-cell launches (variant 1)
   int v1_tile() const { return variant == 1 ? tile_r : 64; }
   dim3 block() const { return dim3(v1_tile(), 256 / v1_tile()); }
   dim3 grid() const {

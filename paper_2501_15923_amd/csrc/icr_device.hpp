@@ -16,9 +16,9 @@ enum : int { LIM_MINMOD = 0, LIM_MC = 1, LIM_WENO5 = 2 };  // WENO5: 3 ghost lay
 
 constexpr int BAD_NONE = 0x7fffffff;
 
-// Device-resident clock and step control.  Written by the last block of the
-// stage-2 kernel (or the CFL kernel) and by the begin-of-call kernel; read
-// by every kernel of a step so that no host round trip is needed.
+// Device-resident clock and step control.  Written by the kernel that ends a
+// step (or reduces a new state's CFL partials) and by the begin-of-call kernel;
+// read by every kernel of a step so that no host round trip is needed.
 struct DevClock {
   double t;        // current time (code units)
   double dt;       // dt of the next step (clipped to t_end)

@@ -18,7 +18,7 @@
 // WENO5 works on primitive variables like the slope
 // limiters (Jiang & Shu 1996 weights, a face state with rho or p <= 0 falls
 // back to its cell value); the weight normalisation multiplies by the
-// Newton-refined reciprocal, as the fluxes do.  Stage 2 also forms the
+// refined reciprocal, as the fluxes do.  Stage 2 also forms the
 // per-block partials of the next CFL dt, of the relaxation residual and of
 // the validity flag.
 #pragma once
@@ -33,14 +33,15 @@ constexpr int W5_TI = W5_TR - 2 * W5_H;  // cells along r per tile row
 // value at the face between c and d (weno5(a, b, c, d, e)), dn = the value
 // at the face between b and c (weno5(e, d, c, b, a)).  The mirrored stencil
 // has the same three smoothness indicators in reverse order and the same
-// eps, so they are formed once; the expressions are symmetric under
-// a..e -> e..a, so a mirror-symmetric flow keeps mirror-symmetric states.
+// eps, so they are formed once.  Reversing the stencil exchanges up and dn up
+// to the rounding of the mean square in eps, which is summed in one order.
 // Everything is written in the four differences and the three second
 // differences, the candidates as offsets from c (times 6), the indicators
 // times 4 and the weights times 10: 60 operations and two reciprocals, where
 // the textbook sums took 79.  Equal to the two weno5 calls up to rounding.
 // At 600 x 60 x 120 in FP64 stage 1 / 2 went from 764 / 874 to 659 / 818 us
-// (with the two-wave face flux and the grouped flux reads of the update).
+// (with the two-wave face flux and the grouped flux reads of the update), and
+// with the update at raised priority to 639 / 792 us.
 template <typename R, bool FAST = false>
 __device__ __forceinline__ void weno5_cell(R a, R b, R c, R d, R e, R& up, R& dn) {
   constexpr R k13 = R(13) / R(3), sixth = R(1) / R(6);
