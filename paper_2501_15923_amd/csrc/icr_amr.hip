@@ -1674,15 +1674,19 @@ int icr_amr_set_boundary_maps(icr_amr* a, int n, const double* t_s, const double
   std::vector<double> h((size_t)n * NV * plane);
   const double sc[NV] = {a->rho_unit, a->v_unit, a->v_unit, a->v_unit,
                          a->p_unit,   a->b_unit, a->b_unit, a->b_unit};
+  const size_t nt = a->g.n_theta, np = a->g.n_phi;
   for (int m = 0; m < n; ++m)
-    for (int v = 0; v < NV; ++v)
-      for (size_t qq = 0; qq < plane; ++qq) {
-        const double x = maps[((size_t)m * NV + v) * plane + qq];
-        if ((v == 0 || v == 4) && !(x > 0.0)) return err(ICR_ERR_ARG, "map rho or p <= 0");
-        if (!std::isfinite(x)) return err(ICR_ERR_ARG, "map has a non-finite value");
-        h[((size_t)m * NV + v) * plane + qq % a->g.n_phi * a->g.n_theta + qq / a->g.n_phi] =
-            x / sc[v];
-      }
+    for (int v = 0; v < NV; ++v) {
+      const double* src = maps + ((size_t)m * NV + v) * plane;
+      double* dst = h.data() + ((size_t)m * NV + v) * plane;
+      for (size_t j = 0; j < nt; ++j)
+        for (size_t k = 0; k < np; ++k) {
+          const double x = src[j * np + k];
+          if ((v == 0 || v == 4) && !(x > 0.0)) return err(ICR_ERR_ARG, "map rho or p <= 0");
+          if (!std::isfinite(x)) return err(ICR_ERR_ARG, "map has a non-finite value");
+          dst[k * nt + j] = x / sc[v];
+        }
+    }
   std::vector<double> tau(n);
   for (int m = 0; m < n; ++m) tau[m] = t_s[m] / a->t_unit;
   AMR_TRY(hipMemcpyAsync(a->at(a->L.bmaps), h.data(), h.size() * sizeof(double),

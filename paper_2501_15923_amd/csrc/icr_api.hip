@@ -694,14 +694,19 @@ int stage_maps(icr_solver* s, int n, const double* maps, int on_device, std::vec
   const size_t nt = s->g.n_theta, np = s->g.n_phi;
   const Scale sc = s->un.scale();
   for (int m = 0; m < n; ++m)
-    for (int v = 0; v < NV; ++v)
-      for (size_t q = 0; q < plane; ++q) {
-        const double x = maps[((size_t)m * NV + v) * plane + q];
-        if ((v == 0 || v == 4) && !(x > 0.0))
-          return fail(ICR_ERR_ARG, "map %d has %s <= 0 at point %zu", m, v ? "p" : "rho", q);
-        if (!std::isfinite(x)) return fail(ICR_ERR_ARG, "map %d has a non-finite value", m);
-        h[((size_t)m * NV + v) * plane + q % np * nt + q / np] = x / sc.s[v];
-      }
+    for (int v = 0; v < NV; ++v) {
+      const double* src = maps + ((size_t)m * NV + v) * plane;
+      double* dst = h.data() + ((size_t)m * NV + v) * plane;
+      for (size_t j = 0; j < nt; ++j)
+        for (size_t k = 0; k < np; ++k) {
+          const double x = src[j * np + k];
+          if ((v == 0 || v == 4) && !(x > 0.0))
+            return fail(ICR_ERR_ARG, "map %d has %s <= 0 at point %zu", m, v ? "p" : "rho",
+                        j * np + k);
+          if (!std::isfinite(x)) return fail(ICR_ERR_ARG, "map %d has a non-finite value", m);
+          dst[k * nt + j] = x / sc.s[v];
+        }
+    }
   return ICR_OK;
 }
 }  // namespace
