@@ -78,7 +78,7 @@ constexpr int GRAPH_STEPS[NGRAPH] = {16, 8, 4, 2, 1};
 // staging region of the workspace in chunks of this many cells (8 doubles
 // each): no call after creation allocates device memory.
 constexpr long long STAGE_CELLS = 65536;
-static_assert(STAGE_CELLS % INIT_CELLS == 0, "chunks hold whole blocks of CFL partials");
+static_assert(STAGE_CELLS % CHUNK_CELLS == 0, "chunks hold whole blocks of CFL partials");
 
 size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -474,10 +474,10 @@ struct icr_solver {
 
   bool logging() const { return n_probes > 0 && cadence >= 0.0 && g.probe_log_rows > 0; }
 
-  // A new state's first dt from the partials its kernel left, the clock
-  // cleared as `reset` says; waits for it.
-  int finish_state(int reset) {
-    const int nb = (int)((ncell() + INIT_CELLS - 1) / INIT_CELLS);
+  // A new state's first dt from the partials its kernel left (one per `cells`
+  // cells), the clock cleared as `reset` says; waits for it.
+  int finish_state(int reset, int cells) {
+    const int nb = (int)((ncell() + cells - 1) / cells);
     if (f32)
       launch_finalize<float>(clock(), partials(), nb, p.cfl, 0, 0, probe_args(), u(cur), nullptr,
                              stream, reset);
@@ -824,7 +824,7 @@ int icr_init_radial(icr_solver* s) {
   HIP_TRY(hipGetLastError());
   if (s->trc())
     HIP_TRY(hipMemsetAsync(s->tr(s->cur), 0, (s->f32 ? 4 : 8) * (size_t)s->ncell(), s->stream));
-  const int rc = s->finish_state(RESET_RUN);
+  const int rc = s->finish_state(RESET_RUN, INIT_CELLS);
   if (rc) return rc;
   s->have_state = true;
   return ICR_OK;
@@ -838,12 +838,13 @@ int icr_set_state(icr_solver* s, const double* data, int kind, int on_device) {
   const long long n = s->ncell();
   const Scale sc = s->un.scale();
   const int q = s->cur;
+  const int cells = on_device ? INIT_CELLS : CHUNK_CELLS;
   auto import = [&](const double* in, long long ld, long long c0, long long m) {
     if (s->f32)
-      launch_import<float>(s->stage_args<float>(q, q, q, 0), in, ld, c0, m, kind, sc, s->p.gamma,
-                           s->stream);
+      launch_import<float>(s->stage_args<float>(q, q, q, 0), in, ld, c0, m, cells, kind, sc,
+                           s->p.gamma, s->stream);
     else
-      launch_import<double>(s->stage_args<double>(q, q, q, 0), in, ld, c0, m, kind, sc,
+      launch_import<double>(s->stage_args<double>(q, q, q, 0), in, ld, c0, m, cells, kind, sc,
                             s->p.gamma, s->stream);
     return hipGetLastError();
   };
@@ -861,7 +862,7 @@ int icr_set_state(icr_solver* s, const double* data, int kind, int on_device) {
     }
   }
   if (s->trc()) HIP_TRY(hipMemsetAsync(s->tr(s->cur), 0, (s->f32 ? 4 : 8) * (size_t)n, s->stream));
-  const int rc = s->finish_state(RESET_BAD);
+  const int rc = s->finish_state(RESET_BAD, cells);
   if (rc) return rc;
   s->have_state = true;
   return ICR_OK;

@@ -451,15 +451,18 @@ template void launch_init_radial<float>(const StageArgs<float>&, const BndArgs&,
 // Cells c0 .. c0+m-1 of the state (variable stride ncell); the buffer holds
 // those m cells with variable stride ld (ld = ncell, c0 = 0 for a whole
 // state in place, ld = m for a staging chunk).  The import also forms the CFL
-// partials (a pass of its own over the state took 70 us at 600 x 60 x 120).
+// partials (a pass of its own over the state took 70 us at 600 x 60 x 120), one
+// per `cells` cells: INIT_CELLS for a whole state, 256 for a chunk, which has
+// too few blocks of more to hide its loads (64 x 180 x 360 from the host, 63
+// chunks: 10.35 ms with 1024).
 template <typename R>
 __global__ void __launch_bounds__(256) k_import(StageArgs<R> a, const double* __restrict__ in,
-                                                long long ld, long long c0, long long m, int kind,
-                                                Scale sc, double gam) {
+                                                long long ld, long long c0, long long m,
+                                                int cells, int kind, Scale sc, double gam) {
   R* u = const_cast<R*>(a.uin);
   double lam = 0.0;
-  for (int h = 0; h < INIT_CELLS / 256; ++h) {
-    const long long c = (long long)blockIdx.x * INIT_CELLS + h * 256 + threadIdx.x;
+  for (int h = 0; h < cells; h += 256) {
+    const long long c = (long long)blockIdx.x * cells + h + threadIdx.x;
     if (c >= m) break;
     double x[NV], uu[NV];
 #pragma unroll
@@ -476,7 +479,7 @@ __global__ void __launch_bounds__(256) k_import(StageArgs<R> a, const double* __
     for (int v = 0; v < NV; ++v) u[v * a.ncell + c0 + c] = (R)uu[v];
     lam = fmax(lam, stored_rate<R>(a, c0 + c, uu));
   }
-  write_partials(a.partials, (int)(c0 / INIT_CELLS) + blockIdx.x, lam, 0.0, 0.0, BAD_NONE);
+  write_partials(a.partials, (int)(c0 / cells) + blockIdx.x, lam, 0.0, 0.0, BAD_NONE);
 }
 
 template <typename R>
@@ -496,9 +499,9 @@ __global__ void k_export(const R* __restrict__ u, long long ncell, long long c0,
 
 template <typename R>
 void launch_import(const StageArgs<R>& a, const double* in, long long ld, long long c0,
-                   long long m, int kind, const Scale& sc, double gam, hipStream_t s) {
-  hipLaunchKernelGGL(k_import<R>, dim3((unsigned)((m + INIT_CELLS - 1) / INIT_CELLS)), dim3(256),
-                     0, s, a, in, ld, c0, m, kind, sc, gam);
+                   long long m, int cells, int kind, const Scale& sc, double gam, hipStream_t s) {
+  hipLaunchKernelGGL(k_import<R>, dim3((unsigned)((m + cells - 1) / cells)), dim3(256), 0, s, a,
+                     in, ld, c0, m, cells, kind, sc, gam);
 }
 template <typename R>
 void launch_export(const void* u, long long ncell, long long c0, long long m, double* out,
@@ -507,9 +510,9 @@ void launch_export(const void* u, long long ncell, long long c0, long long m, do
                      (const R*)u, ncell, c0, m, out, ld, kind, sc, gam);
 }
 template void launch_import<double>(const StageArgs<double>&, const double*, long long, long long,
-                                    long long, int, const Scale&, double, hipStream_t);
+                                    long long, int, int, const Scale&, double, hipStream_t);
 template void launch_import<float>(const StageArgs<float>&, const double*, long long, long long,
-                                   long long, int, const Scale&, double, hipStream_t);
+                                   long long, int, int, const Scale&, double, hipStream_t);
 template void launch_export<double>(const void*, long long, long long, long long, double*,
                                     long long, int, const Scale&, double, hipStream_t);
 template void launch_export<float>(const void*, long long, long long, long long, double*,

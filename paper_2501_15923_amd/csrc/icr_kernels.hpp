@@ -33,9 +33,10 @@ struct Scale {
 // What k_finalize clears when a new state has been put in: nothing, the
 // record of an invalid cell, or that and the clock.
 enum : int { RESET_NONE = 0, RESET_BAD = 1, RESET_RUN = 2 };
-// Cells per block of the kernels that put a state in and form its CFL
-// partials (4 per thread): fewer partials for the one-block reduction.
-constexpr int INIT_CELLS = 1024;
+// Cells per block of the kernels that put a whole state in and form its CFL
+// partials (4 per thread: fewer partials for the one-block reduction), and of
+// those that put in a chunk of it.
+constexpr int INIT_CELLS = 1024, CHUNK_CELLS = 256;
 
 struct MetricArgs {
   int nr, nt;
@@ -426,11 +427,11 @@ template <typename R>
 void launch_init_radial(const StageArgs<R>& a, const BndArgs& b, const double* m64, double gam,
                         hipStream_t s);
 // cells c0 .. c0+m-1 of a state with ncell cells; the double buffer holds
-// them with variable stride ld.  The import writes a.uin and its CFL partials
-// (c0 a multiple of INIT_CELLS)
+// them with variable stride ld.  The import writes a.uin and a CFL partial per
+// `cells` cells (a multiple of 256, and c0 of it)
 template <typename R>
 void launch_import(const StageArgs<R>& a, const double* in, long long ld, long long c0,
-                   long long m, int kind, const Scale& sc, double gam, hipStream_t s);
+                   long long m, int cells, int kind, const Scale& sc, double gam, hipStream_t s);
 template <typename R>
 void launch_export(const void* u, long long ncell, long long c0, long long m, double* out,
                    long long ld, int kind, const Scale& sc, double gam, hipStream_t s);

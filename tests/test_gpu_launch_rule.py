@@ -118,3 +118,31 @@ def test_the_launch_shape_reported_is_the_one_run():
     variant, tile_r, planes = s.launch()
     assert (variant, tile_r) == (2, 64) and 1 <= planes <= 3
     s.close()
+
+
+@pytest.mark.parametrize("shape", [(1, 4, 6), (64, 32, 32), (97, 23, 37)])
+@pytest.mark.parametrize("precision", [64, 32])
+def test_state_from_the_host_and_from_the_device(shape, precision):
+    """A state put in by chunks from the host (one, exactly one and two of
+    65536 cells) and as a whole from the device: the same state and first dt
+    bitwise, the dt of its fastest cell."""
+    import torch
+    from paper_2501_15923_amd.solver import Solver
+    g = synth.Grid(*shape)
+    maps = synth.relax_map(g, 3)[None]
+    src = Solver(g, precision=precision)
+    src.set_maps(np.zeros(1), maps)
+    src.init_radial()
+    dt = src.clock()["next_dt"]
+    u = src.get_state(kind=1)
+    src.close()
+    out = []
+    for state in (u, torch.from_numpy(u).cuda()):
+        s = Solver(g, precision=precision)
+        s.set_maps(np.zeros(1), maps)
+        s.set_state(state, kind=1)
+        out.append((s.clock()["next_dt"], s.get_state(kind=1)))
+        s.close()
+    for next_dt, v in out:
+        assert next_dt == dt
+        assert np.array_equal(v, u)
